@@ -930,7 +930,8 @@ constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 
 struct DecodePlan {
   size_t scores, keep, gate, a1, a2, q, k, v, attn, act, h, m2, rope, part, spart, counters, total;
-  size_t acount, scount;  // byte offsets within the counters block (zeroed together)
+  size_t part_bytes;
+  size_t acount, len_in, scount;  // byte offsets within the counters block (zeroed together)
   int64_t ncounters;
 };
 
@@ -957,16 +958,19 @@ DecodePlan make_decode_plan(const dsf_layer_desc& D, int dtype, int B, int max_p
   p.h = qwen ? take(eb * n * D.d_model) : 0;
   p.m2 = qwen ? take(eb * n * D.d_model) : 0;
   p.rope = take(4 * size_t(max_pos) * D.rotary_dims);
-  p.part = take(4 * n * D.n_heads * size_t(decode_attn_chunks(cap)) * (D.head_dim + 2));
+  p.part_bytes = 4 * n * D.n_heads * size_t(decode_attn_chunks(cap)) * (D.head_dim + 2);
+  p.part = take(p.part_bytes);
   // few-row GEMMs (bf16, B <= 16): split-K partial tiles
   const bool few = dtype == DSF_BF16 && B <= 16;
   p.spart = few ? take(gemm_skinny_partial_bytes()) : 0;
   // counters, zero at the start of a step: decode attention (B * Hq chunk
-  // counters, then B head counters), then the few-row GEMMs' tile counters
+  // counters), the lengths the current layer starts from (B words, written by
+  // its router), then the few-row GEMMs' tile counters
   const int64_t na = int64_t(n) * D.n_heads + n, ns = few ? gemm_skinny_counters() : 0;
   p.ncounters = na + ns;
   p.counters = take(sizeof(uint32_t) * size_t(p.ncounters));
   p.acount = p.counters;
+  p.len_in = p.counters + sizeof(uint32_t) * size_t(n) * D.n_heads;
   p.scount = few ? p.counters + sizeof(uint32_t) * size_t(na) : 0;
   p.total = off;
   return p;
@@ -998,9 +1002,8 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
   float* scores = scores_out ? scores_out : dat<float>(c, c.plan.scores);
   int32_t* keep = dat<int32_t>(c, c.plan.keep);
   float* gate = dat<float>(c, c.plan.gate);
-  const RouteArgs ra{thr, len, c.cap, keep, gate, keep_out};
-  DSF_HIP(launch_router(c.dtype, x, B, d, D.d_router, W->router_w1, W->router_b1, W->router_w2, W->router_b2,
-                        scores, c.s, &ra));
+  int32_t* len_in = dat<int32_t>(c, c.plan.len_in);
+  const RouteArgs ra{thr, len, c.cap, keep, len_in, gate, keep_out};
 
   NormArgs na{};
   na.dtype = c.dtype;
@@ -1019,7 +1022,6 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
     na.b2 = W->norm2_b;
     na.out2 = dat<char>(c, c.plan.a2);
   }
-  DSF_HIP(launch_norm(na, c.s));
 
   GemmArgs g{};
   g.dtype = c.dtype;
@@ -1031,17 +1033,13 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
     g.spart = dat<float>(c, c.plan.spart);
     g.scount = dat<uint32_t>(c, c.plan.scount);
   }
-  if (!qwen) {  // FFN up + GELU on LN2
-    GemmArgs u = g;
-    u.N = f; u.K = d; u.K1 = d;
-    u.a = na.out2; u.lda = d;
-    u.b = W->w_up; u.ldb = d;
-    u.epi = EPI_BIAS_GELU; u.bias = W->b_up;
-    u.out = dat<char>(c, c.plan.act); u.ldo = f;
-    DSF_HIP(launch_gemm(u, c.s));
-  }
+  // the decode attention's partial sums and counters serve the projections
+  // between its launches
+  const RowGemmSplit rs{dat<float>(c, c.plan.part), c.plan.part_bytes, dat<uint32_t>(c, c.plan.acount), B * Hq};
+  g.row_split = rs;
+  GemmArgs front[2] = {g, g};
   {  // QKV, bias, RoPE at each new token's position
-    GemmArgs q = g;
+    GemmArgs& q = front[0];
     q.T = c.max_pos;
     q.idx = pos;
     q.N = dq + 2 * dkv; q.K = d; q.K1 = d;
@@ -1052,10 +1050,39 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
     q.q = dat<char>(c, c.plan.q); q.k = dat<char>(c, c.plan.k); q.v = dat<char>(c, c.plan.v);
     q.Hq = Hq; q.Hkv = Hkv; q.hd = hd; q.R = D.rotary_dims;
     q.rope = dat<float>(c, c.plan.rope);
-    DSF_HIP(launch_gemm(q, c.s));
+  }
+  if (!qwen) {  // FFN up + GELU on LN2
+    GemmArgs& u = front[1];
+    u.N = f; u.K = d; u.K1 = d;
+    u.a = na.out2; u.lda = d;
+    u.b = W->w_up; u.ldb = d;
+    u.epi = EPI_BIAS_GELU; u.bias = W->b_up;
+    u.out = dat<char>(c, c.plan.act); u.ldo = f;
+  }
+  const int np = qwen ? 1 : 2;
+  const bool rows_ok = B <= kRowGemmMaxRows && rowgemm_ok(front[0]) && (qwen || rowgemm_ok(front[1]));
+  const bool bf = c.dtype == DSF_BF16;
+  // the launch's workgroups each take the rows' statistics: worth it for few rows
+  const bool norm_ok = rows_ok && B <= kRowGemmNormRows && size_t(d) * elem_bytes(c.dtype) <= 1024u * kRowGemmNormVecs;
+  const RouterRows rr{x, B, d, D.d_router, W->router_w1, W->router_b1, W->router_w2, W->router_b2, scores, ra};
+  if (!rows_ok || !bf)
+    DSF_HIP(launch_router(c.dtype, x, B, d, D.d_router, W->router_w1, W->router_b1, W->router_w2, W->router_b2,
+                          scores, c.s, &ra));
+  if (norm_ok) {
+    const RowGemmNorm n1{{W->norm1_w, W->norm2_w}, {W->norm1_b, W->norm2_b}, D.norm_eps, qwen};
+    front[0].a = front[1].a = x;
+    DSF_HIP(launch_rowgemm(front, np, &n1, bf ? &rr : nullptr, &rs, c.s));
+  } else {
+    DSF_HIP(launch_norm(na, c.s));
+    if (rows_ok) {
+      DSF_HIP(launch_rowgemm(front, np, nullptr, bf ? &rr : nullptr, &rs, c.s));
+    } else {
+      if (!qwen) DSF_HIP(launch_gemm(front[1], c.s));
+      DSF_HIP(launch_gemm(front[0], c.s));
+    }
   }
   // attention over the cache and the new token, appending the kept tokens' rows
-  DSF_HIP(launch_decode_attention(c.dtype, dat<char>(c, c.plan.q), ck, cv, len, dat<char>(c, c.plan.k),
+  DSF_HIP(launch_decode_attention(c.dtype, dat<char>(c, c.plan.q), ck, cv, len, len_in, dat<char>(c, c.plan.k),
                                   dat<char>(c, c.plan.v), keep, B, Hq, Hkv, hd, c.cap, dat<float>(c, c.plan.part),
                                   dat<uint32_t>(c, c.plan.acount), dat<char>(c, c.plan.attn), c.s));
   if (!qwen) {  // parallel residual: [attn | act] . [W_o | W_down]^T + biases, gated by keep
@@ -1079,25 +1106,29 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
     o.x = x; o.out = dat<char>(c, c.plan.h); o.ldo = d;
     DSF_HIP(launch_gemm(o, c.s));
   }
-  NormArgs n2{};
-  n2.dtype = c.dtype;
-  n2.src = dat<char>(c, c.plan.h);
-  n2.src_rows = 0;
-  n2.B = B;
-  n2.kk = 1;
-  n2.d = d;
-  n2.eps = D.norm_eps;
-  n2.rms = 1;
-  n2.w1 = W->norm2_w;
-  n2.out1 = dat<char>(c, c.plan.m2);
-  DSF_HIP(launch_norm(n2, c.s));
-  {  // SwiGLU
-    GemmArgs u = g;
-    u.N = f; u.K = d; u.K1 = d;
-    u.a = n2.out1; u.lda = d;
-    u.b = W->w_up; u.ldb = d;
-    u.epi = EPI_SWIGLU; u.f = f;
-    u.out = dat<char>(c, c.plan.act); u.ldo = f;
+  GemmArgs u = g;  // SwiGLU on RMS2(h)
+  u.N = f; u.K = d; u.K1 = d;
+  u.a = dat<char>(c, c.plan.h); u.lda = d;
+  u.b = W->w_up; u.ldb = d;
+  u.epi = EPI_SWIGLU; u.f = f;
+  u.out = dat<char>(c, c.plan.act); u.ldo = f;
+  if (norm_ok && rowgemm_ok(u)) {
+    const RowGemmNorm n2{{W->norm2_w, nullptr}, {nullptr, nullptr}, D.norm_eps, 1};
+    DSF_HIP(launch_rowgemm(&u, 1, &n2, nullptr, &rs, c.s));
+  } else {
+    NormArgs n2{};
+    n2.dtype = c.dtype;
+    n2.src = dat<char>(c, c.plan.h);
+    n2.src_rows = 0;
+    n2.B = B;
+    n2.kk = 1;
+    n2.d = d;
+    n2.eps = D.norm_eps;
+    n2.rms = 1;
+    n2.w1 = W->norm2_w;
+    n2.out1 = dat<char>(c, c.plan.m2);
+    DSF_HIP(launch_norm(n2, c.s));
+    u.a = n2.out1;
     DSF_HIP(launch_gemm(u, c.s));
   }
   {  // x + keep * ((h - x) + act . W_down^T)

@@ -70,6 +70,53 @@ __device__ __forceinline__ void store_vec(T* p, const float* v) {
   *reinterpret_cast<u32x4*>(p) = raw;
 }
 
+// Eight consecutive elements (one 16-byte vector of bf16, two of fp32).
+template <typename T>
+__device__ __forceinline__ void load8(const T* p, float* v) {
+  if constexpr (sizeof(T) == 2) {
+    load_vec(p, v);
+  } else {
+    load_vec(p, v);
+    load_vec(p + 4, v + 4);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void store8(T* p, const float* v) {
+  if constexpr (sizeof(T) == 2) {
+    store_vec(p, v);
+  } else {
+    store_vec(p, v);
+    store_vec(p + 4, v + 4);
+  }
+}
+
+// Eight elements of a row as raw 16-byte vectors (one for bf16, two for
+// fp32), widened to fp32 only where they are used.
+template <typename T>
+struct Raw8 {
+  u32x4 v[sizeof(T) / 2];
+};
+template <typename T>
+__device__ __forceinline__ Raw8<T> load_raw8(const T* p) {
+  Raw8<T> r;
+#pragma unroll
+  for (int i = 0; i < int(sizeof(T)) / 2; ++i) r.v[i] = reinterpret_cast<const u32x4*>(p)[i];
+  return r;
+}
+template <typename T>
+__device__ __forceinline__ void unpack8(const Raw8<T>& r, float* out) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (sizeof(T) == 2) {
+      out[2 * i] = __uint_as_float(r.v[0][i] << 16);
+      out[2 * i + 1] = __uint_as_float(r.v[0][i] & 0xffff0000u);
+    } else {
+      out[i] = __uint_as_float(r.v[0][i]);
+      out[4 + i] = __uint_as_float(r.v[1][i]);
+    }
+  }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);

@@ -39,15 +39,26 @@ inline void launch_with_timing(K kern, dim3 grid, dim3 block, hipStream_t s, A..
 // ---- router forward and backward (kernels_router.hip) ----
 // Decode-time routing of the scored tokens, folded into the router (thr null:
 // scores only): keep[t] = scores[t] >= thr[t] && len[t] < cap, gate[t] =
-// keep ? +inf : -inf, keep_out[t] (nullable) = 1 kept, 0 skipped, 2 skipped
-// because the cache is full.
+// keep ? +inf : -inf, len_in[t] = len[t] (the length the step starts from),
+// keep_out[t] (nullable) = 1 kept, 0 skipped, 2 skipped because the cache is
+// full.
 struct RouteArgs {
   const float* thr;
   const int32_t* len;
   int cap;
   int32_t* keep;
+  int32_t* len_in;
   float* gate;
   int32_t* keep_out;
+};
+// The router on a decode batch's rows inside another launch (launch_rowgemm).
+struct RouterRows {
+  const void* x;  // [n, d] bf16
+  int n, d, d_r;
+  const void* w1; const void* b1; const void* w2;
+  float b2;
+  float* scores;
+  RouteArgs route;
 };
 hipError_t launch_router(int dtype, const void* x, int64_t n, int d, int d_r, const void* w1,
                          const void* b1, const void* w2, float b2, float* scores, hipStream_t s,
@@ -135,6 +146,13 @@ enum EpiKind {
                        // out[m, n] = C * up * silu'(gate), out[m, f + n] = C * silu(gate)
 };
 
+// Workspace of a launch that splits K over workgroups (more than 16 rows):
+// part 16-byte aligned, count zero before the launch and left zero.
+struct RowGemmSplit {
+  void* part; size_t part_bytes;
+  uint32_t* count; int counts;
+};
+
 struct GemmArgs {
   int dtype;
   int M, N, K;
@@ -165,11 +183,14 @@ struct GemmArgs {
   // wait for a partial sum gives up ORs DSF_WS_STATUS_SK_TIMEOUT into it.
   // spin_limit is set by the launcher: polls of a flag before giving up.
   uint32_t* status; int spin_limit;
-  // Few-row workspace (nullable): with M <= 16 rows (decode steps) a bf16 GEMM
-  // splits K over workgroups; spart holds gemm_skinny_partial_bytes() and
-  // scount gemm_skinny_counters() words, zero before the first launch using
-  // them (each launch leaves them zero).
+  // Few-row split-K workspace (nullable): with M <= 16 rows (decode steps) a
+  // bf16 QKV projection that launch_rowgemm does not take splits K over
+  // workgroups; spart holds gemm_skinny_partial_bytes() and scount
+  // gemm_skinny_counters() words, zero before the first launch using them
+  // (each launch leaves them zero).
   float* spart; uint32_t* scount;
+  // the same for launch_rowgemm (part null: it does not split)
+  RowGemmSplit row_split;
   // set by the launcher: number of M tiles; workgroups per XCD of a persistent
   // grid (0: one tile per workgroup); 1 if its last round is split along K
   int ntm; int px; int split;
@@ -185,6 +206,29 @@ struct GemmArgs {
   // (0: the launcher's own rule, 1: 128 x 128, 2: 256 x 256)
   int tile_hint;
 };
+// Kinds whose epilogue reads the rows' sequence positions.
+constexpr bool epi_uses_positions(int epi) {
+  return epi == EPI_QKV_ROPE || epi == EPI_RESID_STORE || epi == EPI_RESID_SCATTER || epi == EPI_RESID_SCATTER_GATE;
+}
+
+// ---- few-row projections (kernels_rowgemm.hip) ----
+constexpr int kRowGemmMaxRows = 64;
+constexpr int kRowGemmNormRows = 16;  // rows the launch can normalise itself,
+constexpr int kRowGemmNormVecs = 8;   // each at most 64 x this many 16-byte vectors wide
+struct RowGemmNorm {
+  const void* w[2]; const void* b[2];  // per projection; b null: no bias
+  float eps;
+  int rms;
+};
+// Whether a projection's shape fits the few-row kernel (forward kinds, M <=
+// kRowGemmMaxRows, vectors and rotation partners aligned).
+bool rowgemm_ok(const GemmArgs& g);
+// One or two projections (np) of the same M rows in one launch. norm: A is
+// the raw rows, normalised by the launch (M <= kRowGemmNormRows, K = d);
+// router (bf16): the rows' router scores too; split (nullable).
+hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, const RouterRows* router,
+                          const RowGemmSplit* split, hipStream_t s);
+
 // Timing of a GEMM launched as two kernels: closes the record the first
 // launch claimed and opens another of the same kind for the second.
 void timing_continue();
@@ -237,15 +281,16 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
 // ---- incremental decoding (kernels_decode.hip) ----
 int decode_attn_chunks(int cap);
 constexpr int kDecodeMaxCap = 256 * 256;  // cache slots the decode attention supports
-// q [B, Hq, hd]; caches [B, Hkv, cap, hd] with cache_len[b] valid slots;
-// part: B * Hq * decode_attn_chunks(cap) * (hd + 2) floats; count: B * Hq + B
-// words, zero before the launch (the launch leaves them zero); out [B, Hq * hd].
+// q [B, Hq, hd]; caches [B, Hkv, cap, hd] with len_in[b] valid slots; part:
+// B * Hq * decode_attn_chunks(cap) * (hd + 2) floats; count: B * Hq words,
+// zero before the launch (the launch leaves them zero); out [B, Hq * hd].
 // keep (nullable): a kept sequence's new rows knew / vnew [B, Hkv, hd] join
-// the attention as slot cache_len[b], are copied into that slot, and
-// cache_len[b] grows by one (the cache append of a decode step).
+// the attention as slot len_in[b], are copied into that slot, and
+// cache_len[b] becomes len_in[b] + 1 (the cache append of a decode step).
 hipError_t launch_decode_attention(int dtype, const void* q, const void* ck, const void* cv, int32_t* cache_len,
-                                   const void* knew, const void* vnew, const int32_t* keep, int B, int Hq, int Hkv,
-                                   int hd, int cap, float* part, uint32_t* count, void* out, hipStream_t s);
+                                   const int32_t* len_in, const void* knew, const void* vnew, const int32_t* keep,
+                                   int B, int Hq, int Hkv, int hd, int cap, float* part, uint32_t* count, void* out,
+                                   hipStream_t s);
 hipError_t launch_kv_fill(int dtype, const void* ks, const void* vs, void* ck, void* cv, int32_t* cache_len, int B,
                           int Hkv, int hd, int k, int cap, hipStream_t s);
 hipError_t launch_kept_min_score(const float* scores, const int32_t* idx, int B, int T, int k, float* thr,

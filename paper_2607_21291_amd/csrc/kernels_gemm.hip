@@ -29,52 +29,6 @@ namespace dsf {
 
 // ------------------------------------------------------------- epilogue
 
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* v) {
-  if constexpr (sizeof(T) == 2) {
-    load_vec(p, v);
-  } else {
-    load_vec(p, v);
-    load_vec(p + 4, v + 4);
-  }
-}
-template <typename T>
-__device__ __forceinline__ void store8(T* p, const float* v) {
-  if constexpr (sizeof(T) == 2) {
-    store_vec(p, v);
-  } else {
-    store_vec(p, v);
-    store_vec(p + 4, v + 4);
-  }
-}
-
-// Eight elements of a row as raw 16-byte vectors (one for bf16, two for
-// fp32), widened to fp32 only where they are used.
-template <typename T>
-struct Raw8 {
-  u32x4 v[sizeof(T) / 2];
-};
-template <typename T>
-__device__ __forceinline__ Raw8<T> load_raw8(const T* p) {
-  Raw8<T> r;
-#pragma unroll
-  for (int i = 0; i < int(sizeof(T)) / 2; ++i) r.v[i] = reinterpret_cast<const u32x4*>(p)[i];
-  return r;
-}
-template <typename T>
-__device__ __forceinline__ void unpack8(const Raw8<T>& r, float* out) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (sizeof(T) == 2) {
-      out[2 * i] = __uint_as_float(r.v[0][i] << 16);
-      out[2 * i + 1] = __uint_as_float(r.v[0][i] & 0xffff0000u);
-    } else {
-      out[i] = __uint_as_float(r.v[0][i]);
-      out[4 + i] = __uint_as_float(r.v[1][i]);
-    }
-  }
-}
-
 // Rows of one thread in an epilogue of BM rows, BN columns, NT threads: its
 // chunk column, then rows rr0, rr0 + RSTEP, ... with their sequence, slot in
 // the kept list and position, and (residual kinds) the residual rows, read
@@ -87,11 +41,6 @@ struct EpiPre {
   bool live[RPT];
   Raw8<T> xr[RPT];
 };
-
-// Kinds whose epilogue reads the rows' sequence positions.
-constexpr bool epi_uses_positions(int epi) {
-  return epi == EPI_QKV_ROPE || epi == EPI_RESID_STORE || epi == EPI_RESID_SCATTER || epi == EPI_RESID_SCATTER_GATE;
-}
 
 // EPI: the kind whose rows are read; RES: also read its residual rows
 // (residual kinds).
@@ -1318,7 +1267,7 @@ constexpr int kSkinnyCounters = 1024;   // column tiles per launch
 size_t gemm_skinny_partial_bytes() { return size_t(kSkinnyMaxParts) * kSkinnyRows * kSkinnyBN * sizeof(float); }
 int gemm_skinny_counters() { return kSkinnyCounters; }
 
-template <int EPI>
+template <int EPI>  // EPI_QKV_ROPE only: the other kinds always fit the few-row kernel
 __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits, int kc) {
   constexpr int LD = kSkinnyBN + 4;
   __shared__ float stage[kSkinnyRows * LD];
@@ -1578,6 +1527,22 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
   }
 }
 
+// Few-row launches (kernels_rowgemm.hip), unless a schedule is forced. Above
+// 16 rows the widest projections keep the tile grid: from 256 tile columns on
+// it fills the chip and streams the weights as fast (Qwen2.5-7B gate|up, 37888
+// columns, 32 rows: 64 us, 4.3 TB/s).
+constexpr int kRowTileCols = 256 * 128;
+static bool use_rowgemm(const GemmArgs& g) {
+  if (!rowgemm_ok(g)) return false;
+  const char* e = getenv("DSF_ROWGEMM");
+  if (e && e[0] == '0') return false;
+  for (const char* n : {"DSF_GEMM_SCHEDULE", "DSF_GEMM_TILE", "DSF_GEMM_TAIL"})
+    if ((e = getenv(n)) && *e) return false;
+  if (g.M <= 16) return true;
+  const int cols = g.epi == EPI_SWIGLU ? 2 * g.f : g.N;
+  return g.dtype == DSF_F32 || cols < kRowTileCols;
+}
+
 template <int EPI>
 static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
   if constexpr (EPI >= EPI_STORE) {
@@ -1596,14 +1561,20 @@ static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
     launch_timed(gemm_bf16_kernel<EPI>, dim3((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM), dim3(kThreads), s, g);
     return;
   } else {
-  if (g.dtype == DSF_BF16 && g.M <= kSkinnyRows && g.spart && g.scount && g.K % 32 == 0 && g.K1 % 32 == 0 &&
-      g.lda % 8 == 0 && g.ldb % 8 == 0 && (!g.a2 || g.lda2 % 8 == 0) && (!g.b2 || g.ldb2 % 8 == 0)) {
-    const int ntn = EPI == EPI_SWIGLU ? g.f / (kSkinnyBN / 2) : (g.N + kSkinnyBN - 1) / kSkinnyBN;
-    if (ntn <= kSkinnyCounters && (EPI != EPI_SWIGLU || g.f % (kSkinnyBN / 2) == 0)) {
-      int splits = 1, kc = g.K;
-      skinny_split(ntn, g.K, &splits, &kc);
-      launch_timed(gemm_skinny_kernel<EPI>, dim3(ntn * splits), dim3(256), s, g, splits, kc);
-      return;
+  if (use_rowgemm(g)) {
+    (void)launch_rowgemm(&g, 1, nullptr, nullptr, &g.row_split, s);  // the caller reads the launch's error
+    return;
+  }
+  if constexpr (EPI == EPI_QKV_ROPE) {
+    if (g.dtype == DSF_BF16 && g.M <= kSkinnyRows && g.spart && g.scount && g.K % 32 == 0 && g.K1 == g.K &&
+        g.lda % 8 == 0 && g.ldb % 8 == 0) {
+      const int ntn = (g.N + kSkinnyBN - 1) / kSkinnyBN;
+      if (ntn <= kSkinnyCounters) {
+        int splits = 1, kc = g.K;
+        skinny_split(ntn, g.K, &splits, &kc);
+        launch_timed(gemm_skinny_kernel<EPI>, dim3(ntn * splits), dim3(256), s, g, splits, kc);
+        return;
+      }
     }
   }
 

@@ -9,6 +9,7 @@
 // floating-point atomics.
 #include "dsf_device.h"
 #include "dsf_internal.h"
+#include "router_device.h"
 #include "topk_block.h"
 
 namespace dsf {
@@ -93,16 +94,6 @@ __device__ __forceinline__ float router_hidden(const RouterPart<DR>& part, const
   return h;
 }
 
-// Decode-time routing of token t with score v (RouteArgs).
-__device__ __forceinline__ void route_token(const RouteArgs& ra, int64_t t, float v) {
-  const bool want = v >= ra.thr[t];
-  const bool room = ra.len[t] < ra.cap;
-  const int k = want && room;
-  ra.keep[t] = k;
-  ra.gate[t] = k ? INFINITY : -INFINITY;
-  if (ra.keep_out) ra.keep_out[t] = want ? (room ? 1 : 2) : 0;
-}
-
 template <int DR>
 __global__ __launch_bounds__(64 * kRouterWaves) void router_bf16_kernel(const uint16_t* __restrict__ x, int64_t n, int d,
                                                                          const uint16_t* __restrict__ w1,
@@ -128,7 +119,7 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_bf16_kernel(const ui
   v += __shfl_xor(v, 2);
   if (q == 0 && row0 + t < n) {
     scores[row0 + t] = v + b2;
-    if (ra.thr) route_token(ra, row0 + t, v + b2);
+    if (ra.thr) route_token(ra, row0 + t, v + b2, ra.thr[row0 + t], ra.len[row0 + t]);
   }
 }
 
@@ -159,7 +150,7 @@ __global__ __launch_bounds__(256) void router_f32_kernel(const float* __restrict
   }
   if (lane == 0) {
     scores[t] = score + b2;
-    if (ra.thr) route_token(ra, t, score + b2);
+    if (ra.thr) route_token(ra, t, score + b2, ra.thr[t], ra.len[t]);
   }
 }
 
