@@ -221,7 +221,7 @@ struct RowGemmNorm {
   int rms;
 };
 // Whether a projection's shape fits the few-row kernel (forward kinds, M <=
-// kRowGemmMaxRows, vectors and rotation partners aligned).
+// kRowGemmMaxRows in bf16, vectors and rotation partners aligned).
 bool rowgemm_ok(const GemmArgs& g);
 // One or two projections (np) of the same M rows in one launch. norm: A is
 // the raw rows, normalised by the launch (M <= kRowGemmNormRows, K = d);

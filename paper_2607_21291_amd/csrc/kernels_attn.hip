@@ -331,38 +331,174 @@ __global__ __launch_bounds__(256) void attn_bf16_dma_kernel(const uint16_t* __re
 }
 
 
-// fp32: one thread per query, online softmax over its causal prefix.
+// fp32 on the fp32 matrix cores: a workgroup takes 16 queries of one head, its
+// four waves every fourth tile of 32 keys, each with an online softmax of its
+// own; the four states combine through LDS in wave order. Scores: queries and
+// keys as the rows of the two operands, 16 bytes of a row per lane, element e
+// of the vectors forming one 4-deep MFMA. The probabilities go through a
+// per-wave LDS tile into the A operand of P V; a lane's HD / 16 neighbouring
+// dims of value row 4 s + grp, as they come from memory, are that many B
+// operands. A thread per query (the form it replaces) ran 60 wavefronts of
+// scalar FMA chains on the GPT-NeoX-160M heads at 307 keys: 282 us.
 template <int HD>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                      const float* __restrict__ V, int Hq, int Hkv, int n,
-                                                      float* __restrict__ out) {
-  const int qi = blockIdx.x * 64 + threadIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (qi >= n) return;
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                       const float* __restrict__ V, int Hq, int Hkv, int n,
+                                                       float* __restrict__ out) {
+  constexpr int NK = HD / 16, DPL = HD / 16, KV = 32;
+  __shared__ float ps[4][16][KV + 4];
+  __shared__ float osum[4][16][HD];
+  __shared__ float ms[4][16], ls[4][16];
+  const int qb = int(gridDim.x) - 1 - int(blockIdx.x);  // the longest prefixes first
+  const int h = blockIdx.y, b = blockIdx.z, q0 = qb * 16;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r16 = lane & 15, grp = lane >> 4;
   const int kvh = h / (Hq / Hkv);
-  const float* qr = Q + ((int64_t(b) * Hq + h) * n + qi) * HD;
+  const float* Qh = Q + (int64_t(b) * Hq + h) * n * HD;
   const float* Kh = K + (int64_t(b) * Hkv + kvh) * n * HD;
   const float* Vh = V + (int64_t(b) * Hkv + kvh) * n * HD;
-  float qv[HD], o[HD];
-  for (int d = 0; d < HD; ++d) {
-    qv[d] = qr[d];
-    o[d] = 0.f;
-  }
+  f32x4 qf[NK];
+#pragma unroll
+  for (int s = 0; s < NK; ++s)
+    qf[s] = *reinterpret_cast<const f32x4*>(Qh + int64_t(min(q0 + r16, n - 1)) * HD + 16 * s + 4 * grp);
   const float scale = 1.0f / sqrtf(float(HD));
-  float m = -INFINITY, l = 0.f;
-  for (int j = 0; j <= qi; ++j) {
-    const float* kr = Kh + int64_t(j) * HD;
-    float s = 0.f;
-    for (int d = 0; d < HD; ++d) s = fmaf(qv[d], kr[d], s);
-    s *= scale;
-    const float mn = fmaxf(m, s);
-    const float c = expf(m - mn), p = expf(s - mn);
-    l = l * c + p;
-    const float* vr = Vh + int64_t(j) * HD;
-    for (int d = 0; d < HD; ++d) o[d] = o[d] * c + p * vr[d];
-    m = mn;
+  float m[4], l[4];  // of queries q0 + 4 grp + i
+  f32x4 o[DPL];      // o[e][i]: query q0 + 4 grp + i, dim DPL r16 + e
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    m[i] = -INFINITY;
+    l[i] = 0.f;
   }
-  float* orow = out + (int64_t(b) * n + qi) * (int64_t(Hq) * HD) + int64_t(h) * HD;
-  for (int d = 0; d < HD; ++d) orow[d] = o[d] / l;
+#pragma unroll
+  for (int e = 0; e < DPL; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int qmax = min(q0 + 15, n - 1);
+  for (int key0 = KV * w; key0 <= qmax; key0 += 4 * KV) {
+    f32x4 kf[2][NK];
+    float vf[KV / 4][DPL];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int s = 0; s < NK; ++s)
+        kf[kb][s] = *reinterpret_cast<const f32x4*>(Kh + int64_t(min(key0 + 16 * kb + r16, n - 1)) * HD + 16 * s + 4 * grp);
+#pragma unroll
+    for (int s = 0; s < KV / 4; ++s) {
+      const float* vr = Vh + int64_t(min(key0 + 4 * s + grp, n - 1)) * HD + DPL * r16;
+      if constexpr (DPL == 2) {
+        const float2 t = *reinterpret_cast<const float2*>(vr);
+        vf[s][0] = t.x;
+        vf[s][1] = t.y;
+      } else {
+#pragma unroll
+        for (int j = 0; j < DPL / 4; ++j) {
+          const f32x4 t = reinterpret_cast<const f32x4*>(vr)[j];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) vf[s][4 * j + i] = t[i];
+        }
+      }
+    }
+    float sc[2][4];
+    bool in[2][4];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      f32x4 acc[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < NK; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[s][e], kf[kb][s][e], acc[e], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        in[kb][i] = key0 + 16 * kb + r16 <= q0 + 4 * grp + i;
+        sc[kb][i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) * scale;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float mx = fmaxf(in[0][i] ? sc[0][i] : -INFINITY, in[1][i] ? sc[1][i] : -INFINITY);
+      mx = fmaxf(mx, DSF_DPP(mx, 0xB1));   // over the 16 lanes of the row: quads, half rows, rows
+      mx = fmaxf(mx, DSF_DPP(mx, 0x4E));
+      mx = fmaxf(mx, DSF_DPP(mx, 0x141));
+      mx = fmaxf(mx, DSF_DPP(mx, 0x140));
+      const float mn = fmaxf(m[i], mx);
+      // a query of this tile may have no key yet (mn = -inf): nothing to rescale
+      const float c = mn == -INFINITY ? 1.f : expf(m[i] - mn);
+      float sum = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const float p = in[kb][i] ? expf(sc[kb][i] - mn) : 0.f;
+        sum += p;
+        ps[w][4 * grp + i][16 * kb + r16] = p;
+      }
+      l[i] = l[i] * c + row16_sum(sum);
+#pragma unroll
+      for (int e = 0; e < DPL; ++e) o[e][i] *= c;
+      m[i] = mn;
+    }
+    // a wave reads back only its own probabilities
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+    // A tile with keys in some query's future: its masked probabilities are
+    // zeros of the product, which an infinite or NaN value would turn into
+    // NaN. Such values are left out here and added below to the queries that
+    // attend to them.
+    bool bad = false;
+    if (key0 + KV - 1 > q0) {
+#pragma unroll
+      for (int s = 0; s < KV / 4; ++s)
+#pragma unroll
+        for (int e = 0; e < DPL; ++e) bad = bad || !(fabsf(vf[s][e]) < INFINITY);
+    }
+    const bool fix = __ballot(bad) != 0;
+#pragma unroll
+    for (int s = 0; s < KV / 4; ++s) {
+      const float pa = ps[w][r16][4 * s + grp];
+#pragma unroll
+      for (int e = 0; e < DPL; ++e)
+        o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, fix && !(fabsf(vf[s][e]) < INFINITY) ? 0.f : vf[s][e], o[e], 0,
+                                                    0, 0);
+    }
+    if (fix) {
+#pragma unroll
+      for (int s = 0; s < KV / 4; ++s)
+        for (int g = 0; g < 4; ++g) {
+          const int key = key0 + 4 * s + g;
+#pragma unroll
+          for (int e = 0; e < DPL; ++e) {
+            const float v = __shfl(vf[s][e], r16 + 16 * g, 64);
+            if (!(fabsf(v) < INFINITY))
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (key <= q0 + 4 * grp + i) o[e][i] = fmaf(ps[w][4 * grp + i][4 * s + g], v, o[e][i]);
+          }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // read before the next tile's overwrite them
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int e = 0; e < DPL; ++e) osum[w][4 * grp + i][DPL * r16 + e] = o[e][i];
+    if (r16 == 0) {
+      ms[w][4 * grp + i] = m[i];
+      ls[w][4 * grp + i] = l[i];
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < 16 * HD; e += 256) {
+    const int q = e / HD, dim = e - q * HD;
+    if (q0 + q >= n) break;
+    const float M = fmaxf(fmaxf(ms[0][q], ms[1][q]), fmaxf(ms[2][q], ms[3][q]));
+    float O = 0.f, L = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < 4; ++ww) {
+      const float c = ms[ww][q] == -INFINITY ? 0.f : expf(ms[ww][q] - M);
+      O = fmaf(osum[ww][q][dim], c, O);
+      L = fmaf(ls[ww][q], c, L);
+    }
+    out[(int64_t(b) * n + q0 + q) * (int64_t(Hq) * HD) + int64_t(h) * HD + dim] = O / L;
+  }
 }
 
 // Launch kern<<<grid, block>>>(args...), through hipExtLaunchKernelGGL when
@@ -387,12 +523,12 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
   if (n == 0 || B == 0) return hipSuccess;
   TimedScope ts(DSF_KIND_ATTN, s, true);
   if (dtype == DSF_F32) {
-    dim3 grid((n + 63) / 64, Hq, B);
+    dim3 grid((n + 15) / 16, Hq, B);
     auto Qp = (const float*)q; auto Kp = (const float*)k; auto Vp = (const float*)v; auto O = (float*)out;
     switch (hd) {
-      case 32: launch_timed(attn_f32_kernel<32>, grid, dim3(64), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
-      case 64: launch_timed(attn_f32_kernel<64>, grid, dim3(64), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
-      case 128: launch_timed(attn_f32_kernel<128>, grid, dim3(64), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 32: launch_timed(attn_f32_kernel<32>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 64: launch_timed(attn_f32_kernel<64>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 128: launch_timed(attn_f32_kernel<128>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
       default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

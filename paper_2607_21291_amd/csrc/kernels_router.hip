@@ -123,35 +123,89 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_bf16_kernel(const ui
   }
 }
 
-// fp32 hidden pre-activation of unit j for one row, by one wavefront: lane
-// strided products, then a wave sum, then the bias (forward and backward).
-__device__ __forceinline__ float router_hidden_f32(const float* __restrict__ row, int d,
-                                                   const float* __restrict__ w1, const float* __restrict__ b1,
-                                                   int j, int lane) {
-  const float* wr = w1 + int64_t(j) * d;
-  float h = 0.f;
-  for (int i = lane; i < d; i += 64) h = fmaf(row[i], wr[i], h);
-  return wave_sum(h) + (b1 ? b1[j] : 0.f);
+// fp32 hidden pre-activations of 16 rows on the fp32 matrix cores. Wave w
+// takes the 16-wide column slices w, w + 8, ...; a lane loads 16 bytes of its
+// row, and element e of every lane's vector is one v_mfma_f32_16x16x4_f32 into
+// an accumulator of its own, odd slices apart from even ones (eight short
+// chains per wave, so the sums round no worse than the lane-strided ones they
+// replace). The chains, then the waves' shares in wave order, then the bias:
+// the forward pass and
+// the backward recomputation call this, so both take the same ReLU decisions.
+// The wavefront-per-token kernel it replaces read W1 once per token (512
+// tokens of 768: 100 us).
+template <int DR>
+__device__ __forceinline__ void router_hidden16_f32(const float* __restrict__ x, int64_t n, int d,
+                                                    const float* __restrict__ w1, const float* __restrict__ b1,
+                                                    int64_t row0, float (&part)[kRouterWaves][16][DR + 1],
+                                                    float (&z)[16][DR + 1]) {
+  constexpr int NB = DR / 16, NW = kRouterWaves;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int64_t row = row0 + r < n ? row0 + r : n - 1;
+  f32x4 acc[2][NB][4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u][nb][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  for (int kc = 16 * w; kc < d; kc += 32 * NW) {
+    f32x4 xa[2], wb[2][NB];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      // d is a multiple of 8, so each lane's 4-element piece is wholly inside or past the end
+      const int k0 = kc + 16 * NW * u + 4 * g;
+      const bool ok = k0 < d;
+      xa[u] = ok ? *reinterpret_cast<const f32x4*>(x + row * d + k0) : zero;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        wb[u][nb] = ok ? *reinterpret_cast<const f32x4*>(w1 + (16 * nb + r) * int64_t(d) + k0) : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[u][nb][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[u][e], wb[u][nb][e], acc[u][nb][e], 0, 0, 0);
+  }
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      part[w][4 * g + i][16 * nb + r] =
+          ((acc[0][nb][0][i] + acc[0][nb][1][i]) + (acc[0][nb][2][i] + acc[0][nb][3][i])) +
+          ((acc[1][nb][0][i] + acc[1][nb][1][i]) + (acc[1][nb][2][i] + acc[1][nb][3][i]));
+  __syncthreads();
+  for (int e = threadIdx.x; e < 16 * DR; e += 64 * NW) {
+    const int t = e / DR, j = e - t * DR;
+    float h = 0.f;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) h += part[ww][t][j];
+    z[t][j] = h + (b1 ? b1[j] : 0.f);
+  }
+  __syncthreads();
 }
 
-// fp32 router: one wavefront per token, one hidden unit at a time.
-__global__ __launch_bounds__(256) void router_f32_kernel(const float* __restrict__ x, int64_t n, int d, int dr,
-                                                         const float* __restrict__ w1, const float* __restrict__ b1,
-                                                         const float* __restrict__ w2, float b2,
-                                                         float* __restrict__ scores, RouteArgs ra) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (t >= n) return;
-  const float* row = x + t * d;
-  float score = 0.f;
-  for (int j = 0; j < dr; ++j) {
-    const float h = router_hidden_f32(row, d, w1, b1, j, lane);
-    score = fmaf(w2[j], h > 0.f ? h : 0.f, score);
-  }
-  if (lane == 0) {
-    scores[t] = score + b2;
-    if (ra.thr) route_token(ra, t, score + b2, ra.thr[t], ra.len[t]);
-  }
+template <int DR>
+__global__ __launch_bounds__(64 * kRouterWaves) void router_f32_kernel(const float* __restrict__ x, int64_t n, int d,
+                                                                       const float* __restrict__ w1,
+                                                                       const float* __restrict__ b1,
+                                                                       const float* __restrict__ w2, float b2,
+                                                                       float* __restrict__ scores, RouteArgs ra) {
+  __shared__ float part[kRouterWaves][16][DR + 1];
+  __shared__ float z[16][DR + 1];
+  const int64_t row0 = int64_t(blockIdx.x) * 16;
+  router_hidden16_f32<DR>(x, n, d, w1, b1, row0, part, z);
+  const int t = threadIdx.x;
+  if (t >= 16 || row0 + t >= n) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < DR; ++j) v[j % 4] = fmaf(w2[j], z[t][j] > 0.f ? z[t][j] : 0.f, v[j % 4]);
+  const float score = (v[0] + v[1]) + (v[2] + v[3]);
+  scores[row0 + t] = score + b2;
+  if (ra.thr) route_token(ra, row0 + t, score + b2, ra.thr[row0 + t], ra.len[row0 + t]);
 }
 
 hipError_t launch_router(int dtype, const void* x, int64_t n, int d, int d_r, const void* w1,
@@ -161,8 +215,18 @@ hipError_t launch_router(int dtype, const void* x, int64_t n, int d, int d_r, co
   TimedScope ts(DSF_KIND_ROUTER, s, true);
   const RouteArgs ra = route ? *route : RouteArgs{};
   if (dtype == DSF_F32) {
-    launch_with_timing(router_f32_kernel, dim3(unsigned((n + 3) / 4)), dim3(256), s, (const float*)x, n, d, d_r,
-                       (const float*)w1, (const float*)b1, (const float*)w2, b2, scores, ra);
+    const dim3 g16(unsigned((n + 15) / 16)), blk(64 * kRouterWaves);
+    auto X = (const float*)x;
+    auto W1 = (const float*)w1;
+    auto B1 = (const float*)b1;
+    auto W2 = (const float*)w2;
+    switch (d_r) {
+      case 16: launch_with_timing(router_f32_kernel<16>, g16, blk, s, X, n, d, W1, B1, W2, b2, scores, ra); break;
+      case 32: launch_with_timing(router_f32_kernel<32>, g16, blk, s, X, n, d, W1, B1, W2, b2, scores, ra); break;
+      case 48: launch_with_timing(router_f32_kernel<48>, g16, blk, s, X, n, d, W1, B1, W2, b2, scores, ra); break;
+      case 64: launch_with_timing(router_f32_kernel<64>, g16, blk, s, X, n, d, W1, B1, W2, b2, scores, ra); break;
+      default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
   }
   unsigned grid = unsigned((n + kRouterTokens - 1) / kRouterTokens);
@@ -663,20 +727,24 @@ __global__ __launch_bounds__(64 * kRouterWaves) void router_bwd_tokens_f32_kerne
     const float* __restrict__ w2, const float* __restrict__ ds, float* __restrict__ dx, float* __restrict__ dz,
     float* __restrict__ terms) {
   constexpr int NT = 64 * kRouterWaves, TM = kRouterTokens;
-  __shared__ RouterPart<DR> part;
+  __shared__ union {
+    RouterPart<DR> part;
+    struct {
+      float zero[TM][DR + 1];  // part[0]: the hidden units
+      float p16[kRouterWaves][16][DR + 1];
+    } h;
+  } sh;
+  __shared__ float z16[16][DR + 1];
   __shared__ __align__(16) float dzs[TM][DR];
   __shared__ float ssum[TM];
+  RouterPart<DR>& part = sh.part;
   const int64_t row0 = int64_t(blockIdx.x) * TM;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // one wavefront per token, as in the fp32 forward; z (bias included) goes to part[0]
-  for (int t = w; t < TM; t += kRouterWaves) {
-    const int64_t row = row0 + t < n ? row0 + t : n - 1;
-    for (int j = 0; j < DR; ++j) {
-      const float h = router_hidden_f32(x + row * d, d, w1, b1, j, lane);
-      if (lane == 0) part[0][t][j] = h;
-    }
+  // sixteen tokens at a time, as in the fp32 forward; z (bias included) goes to part[0]
+  for (int tb = 0; tb < TM; tb += 16) {
+    router_hidden16_f32<DR>(x, n, d, w1, b1, row0 + tb, sh.h.p16, z16);
+    for (int e = threadIdx.x; e < 16 * DR; e += NT) part[0][tb + e / DR][e % DR] = z16[e / DR][e % DR];
+    __syncthreads();
   }
-  __syncthreads();
   router_bwd_chunk<float, DR, DR>(part, dzs, ssum, b1, w2, ds, n, row0, terms);
   for (int e = threadIdx.x; e < TM * DR; e += NT) {
     const int t = e / DR;
