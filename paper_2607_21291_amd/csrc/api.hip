@@ -732,10 +732,12 @@ int run_layer(const Ctx& c, const dsf_layer_weights* W, void* x, int k, bool den
     us = c.aux->s;
   }
   // NeoX: the up and QKV projections share the chip; one tile size for both
-  const int pair_hint = qwen ? 0 : gemm_pair_tile_hint(M, dq + 2 * dkv, d);
+  const int pair_hint = qwen ? 0 : gemm_pair_tile_hint(M, dq + 2 * dkv, f, d);
+  auto tiles128 = [&](int n) { return ((M + 127) / 128) * ((n + 127) / 128); };
   if (!qwen) {  // FFN up + GELU on LN2 of the kept rows
     GemmArgs u = g;
     u.tile_hint = pair_hint;
+    u.beside = us != c.s ? tiles128(dq + 2 * dkv) : 0;
     u.M = M; u.N = f; u.K = d; u.K1 = d;
     u.a = na.out2; u.lda = d;
     u.b = W->w_up; u.ldb = d;
@@ -752,6 +754,7 @@ int run_layer(const Ctx& c, const dsf_layer_weights* W, void* x, int k, bool den
     q.b = W->w_qkv; q.ldb = d;
     q.epi = EPI_QKV_ROPE;
     q.tile_hint = pair_hint;
+    q.beside = us != c.s ? tiles128(f) : 0;
     q.bias = W->b_qkv;
     q.q = at<char>(c, c.plan.q); q.k = at<char>(c, c.plan.k); q.v = at<char>(c, c.plan.v);
     q.Hq = Hq; q.Hkv = Hkv; q.hd = hd; q.R = D.rotary_dims;

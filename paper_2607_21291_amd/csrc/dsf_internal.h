@@ -205,6 +205,8 @@ struct GemmArgs {
   // tile size chosen by the caller for a pair of GEMMs that share the chip
   // (0: the launcher's own rule, 1: 128 x 128, 2: 256 x 256)
   int tile_hint;
+  // 128 x 128 tiles of a launch that runs at the same time on another stream
+  int beside;
 };
 // Kinds whose epilogue reads the rows' sequence positions.
 constexpr bool epi_uses_positions(int epi) {
@@ -233,9 +235,9 @@ hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, co
 // launch claimed and opens another of the same kind for the second.
 void timing_continue();
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// GemmArgs::tile_hint for two forward projections run side by side, from the
-// leading one's M x N and reduction K (0: leave each launch its own rule).
-int gemm_pair_tile_hint(int M, int N, int K);
+// GemmArgs::tile_hint for two forward projections of M rows and reduction K,
+// N1 and N2 wide, run side by side.
+int gemm_pair_tile_hint(int M, int N1, int N2, int K);
 
 // ---- backward of the routed layer (kernels_bwd.hip) ----
 // out[c][r] = op(in[r][c]) (op 0 copy, 1 GELU, 2 SiLU(in[r][c]) * in[r][C + c]);

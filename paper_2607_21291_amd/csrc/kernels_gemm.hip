@@ -562,6 +562,11 @@ __device__ __forceinline__ void dma16(const RowSrc& src, uint32_t voff, uint32_t
 struct TileSmall {
   static constexpr int BM = 128, BN = 128, WM = 64, WN = 64, NS = 2, BK = 64;
 };
+// The small tile with a four-stage ring, one workgroup per CU, for grids that
+// give a CU at most one workgroup anyway (launch_dma).
+struct TileDeep {
+  static constexpr int BM = 128, BN = 128, WM = 64, WN = 64, NS = 4, BK = 64;
+};
 struct TileLarge {
   static constexpr int BM = 256, BN = 256, WM = 64, WN = 128, NS = 2, BK = 64;
 };
@@ -576,6 +581,9 @@ constexpr int kSkMinK = 32;    // k-iterations per tile below which the partial 
 // least this many k-iterations long.
 constexpr int kTailMaxSplit = 4;
 constexpr int kTailMinK = 8;
+// Grids of at most one workgroup per CU (choose_deep): the same limits.
+constexpr int kDeepMaxSplit = 4, kDeepMinSplit = 3;
+constexpr int kDeepMinK = 8;
 constexpr int kGroupM = 4;      // tile rows per band of the grouped tile order
 constexpr int kGroupMinCols = 8;  // below this many tile columns row-major order is already compact
 constexpr size_t kSkPartBytes = size_t(kSkMaxSlots) / 2 * TileLarge::BM * TileLarge::BN * sizeof(float);
@@ -590,75 +598,102 @@ struct DmaGemm {
   static constexpr int RPL = C::kRowsPerLoad;
   typedef f32x4 Acc[MI][NI];
 
-  // acc = A[rows of tile tm, k-tiles kb..ke-1] . B[rows of tile tn, same]^T.
-  // Starts with a barrier, so the ring may still hold the previous tile.
-  __device__ static __forceinline__ void mainloop(const GemmArgs& g, char* smem, int tm, int tn, int kb, int ke,
-                                                  Acc& acc) {
+  // The multiplication of k-tiles kb .. ke - 1, the first NS in flight and tile
+  // kb published: 256 x 256 tiles, one workgroup per CU. The fragments of a
+  // substep are read while the one before it is multiplied, and the barrier
+  // sits in the middle of a tile. Against the loop of the small tiles, whose
+  // waves read twelve fragments each right behind the barrier (96 KB of LDS
+  // reads with seven MFMAs a wave to cover them): gate|up of 2000 Qwen2.5-7B
+  // rows 456 -> 419 us, the layer at 4118 kept tokens 7.34 -> 7.13 ms.
+  template <typename IssuePart>
+  __device__ static __forceinline__ void mainloop_wide(char* smem, int kb, int ke, Acc& acc, IssuePart issue_part) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / (BN / WN), wn = wave % (BN / WN);
     const int r16 = lane & 15, grp = lane >> 4;
-    const int m0 = tm * BM;
-    // DMA sources are buffer resources over A, A2, B, B2 whose size is the
-    // matrix's rows x leading dimension: a row beyond M (or N) is out of range
-    // and reads as zeros, so ragged tiles need no clamping. Load i of this
-    // wave fills tile rows RPL (wave + kWaves i) .. + RPL; the lane part of
-    // the offset (row lane / CPR, physical chunk lane % CPR holding logical
-    // chunk swz^-1) is the same for every load, the row base is uniform.
-    const int lr = lane / CPR;
-    const int lc = swz<BK>(lr, lane % CPR);  // swz is an involution for a fixed row
-    const RowSrc sa{g.a, g.M, g.lda}, sa2{g.a2, g.M, g.lda2};
-    const int nrows_b = EPI == EPI_SWIGLU ? 2 * g.f : g.N;
-    const RowSrc sb{g.b, nrows_b, g.ldb}, sb2{g.b2, nrows_b, g.ldb2};
-    const uint32_t va = uint32_t(lr * g.lda + lc * 8) * 2u, va2 = uint32_t(lr * g.lda2 + lc * 8) * 2u;
-    const uint32_t vb = uint32_t(lr * g.ldb + lc * 8) * 2u, vb2 = uint32_t(lr * g.ldb2 + lc * 8) * 2u;
-    // first B row of load i (uniform)
-    auto brow = [&](int i) {
-      const int r = RPL * (wave + C::kWaves * i);
-      if constexpr (EPI == EPI_SWIGLU) {
-        // each 128-row block of the B tile holds 64 gate units then the same 64 up units
-        const int blk = r / 128, rr = r % 128, u0 = (tn * (BN / 128) + blk) * 64;
-        return rr < 64 ? u0 + rr : g.f + u0 + (rr - 64);
-      } else {
-        return tn * BN + r;
+    static_assert(BK == 64, "two 32-deep substeps per tile");
+    auto tileA = [&](int kt) { return reinterpret_cast<const uint16_t*>(smem + (kt % NS) * C::kStage); };
+    // fragments of two substeps: one set is multiplied while the other is read
+    bf16x8 af[2][MI], bq[2][NI];
+    auto read_b = [&](const uint16_t* At, int ks, int j) -> bf16x8 {
+      const int br = wn * WN + j * 16 + r16;
+      return *reinterpret_cast<const bf16x8*>(At + BM * BK + br * BK + (swz<BK>(br, ks * 4 + grp) << 3));
+    };
+    auto read_a = [&](const uint16_t* At, int ks, int i) -> bf16x8 {
+      const int ar = wm * WM + i * 16 + r16;
+      return *reinterpret_cast<const bf16x8*>(At + ar * BK + (swz<BK>(ar, ks * 4 + grp) << 3));
+    };
+    // reads of a set in the order of their use: A 0, B 0 .. NI - 1, A 1 .. MI - 1
+    auto read_n = [&](const uint16_t* At, int set, int ks, int n) {
+      if (n == 0) af[set][0] = read_a(At, ks, 0);
+      else if (n <= NI) bq[set][n - 1] = read_b(At, ks, n - 1);
+      else af[set][n - NI] = read_a(At, ks, n - NI);
+    };
+    constexpr int R = MI + NI;
+#pragma unroll
+    for (int n = 0; n < R; ++n) read_n(tileA(kb), 0, 0, n);
+
+    // One substep: MI groups of NI MFMAs on set S, the R reads of the other
+    // set (tile At, substep ks) spread over the first MI - 1 groups, so that
+    // the last group covers their latency; and, with ISSUE, the loads of tile
+    // kn into the ring, a part per group.
+    auto substep = [&](auto Sc, const uint16_t* At, int ks, bool do_issue, int kn) {
+      constexpr int S = decltype(Sc)::value;
+      auto group = [&](auto Ic) {
+        constexpr int i = decltype(Ic)::value;
+        acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[S][i], bq[S][0], acc[i][0], 0, 0, 0);
+        DSF_SCHED_FENCE();
+        if constexpr (i < MI - 1) {
+#pragma unroll
+          for (int n = i * R / (MI - 1); n < (i + 1) * R / (MI - 1); ++n) read_n(At, 1 - S, ks, n);
+        }
+        if constexpr (S == 1)
+          if (do_issue) issue_part(kn, std::integral_constant<int, i>(), std::integral_constant<int, MI>());
+        DSF_SCHED_FENCE();
+#pragma unroll
+        for (int j = 1; j < NI; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[S][i], bq[S][j], acc[i][j], 0, 0, 0);
+        DSF_SCHED_FENCE();
+      };
+      static_assert(MI == 4, "groups");
+      group(std::integral_constant<int, 0>());
+      group(std::integral_constant<int, 1>());
+      group(std::integral_constant<int, 2>());
+      group(std::integral_constant<int, 3>());
+    };
+    // One tile. Every fragment of a tile is in registers by the middle of its
+    // multiplication (substep 0 reads substep 1's), so the workgroup crosses
+    // its one barrier there, with a whole substep of MFMAs whose operands are
+    // at hand behind it: no wave waits for LDS right after the barrier. The
+    // barrier publishes tile kt + 1 (each wave has waited for its own loads)
+    // and frees tile kt's buffer for tile kt + NS, whose loads are issued
+    // through substep 1, which also reads tile kt + 1's first fragments. (The
+    // last tile reads stale LDS there; nothing uses it.) With the barrier
+    // after the last substep and reads one MFMA group ahead, all waves read
+    // nine or twelve fragments at once behind it.
+    for (int kt = kb; kt < ke; ++kt) {
+      substep(std::integral_constant<int, 0>(), tileA(kt), 1, false, 0);
+      if (kt + 1 < ke) {
+        // tile kt + 1 has landed once the tiles issued after it are all that remain
+        if (kt + NS - 1 < ke) wait_vmcnt<(NS - 2) * C::kLoads>();
+        else wait_vmcnt<0>();
+        ring_barrier();
       }
-    };
-    auto issue = [&](int kt) {
-      const int k0 = kt * BK;
-      const bool second = k0 >= g.K1;
-      const int kc = second ? k0 - g.K1 : k0;
-      char* st = smem + (kt % NS) * C::kStage;
-      const RowSrc& A = second ? sa2 : sa;
-      const RowSrc& Bm = second ? sb2 : sb;
-      const uint32_t vA = second ? va2 : va, vB = second ? vb2 : vb;
-#pragma unroll
-      for (int i = 0; i < C::kLoadsA; ++i)
-        dma16(A, vA, uint32_t((m0 + RPL * (wave + C::kWaves * i)) * A.ld + kc) * 2u,
-              st + 1024 * (wave + C::kWaves * i));
-#pragma unroll
-      for (int i = 0; i < C::kLoadsB; ++i)
-        dma16(Bm, vB, uint32_t(brow(i) * Bm.ld + kc) * 2u, st + BM * C::kRowBytes + 1024 * (wave + C::kWaves * i));
-    };
+      substep(std::integral_constant<int, 1>(), tileA(kt + 1), 0, kt + NS < ke, kt + NS);
+    }
+  }
 
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // Every wave is done with the LDS before the ring is refilled. Stores of
-    // an earlier tile may still be in flight: they only add to the counter,
-    // so each wait below still covers the loads it is for (whether or not the
-    // stores retire in order), and they drain under this tile's first loads.
-    ring_barrier();
-    // Ring of NS buffers, all filled ahead: tile kt lives in buffer kt % NS,
-    // and tile kt + NS is issued into it as soon as tile kt has been read.
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (kb + s < ke) issue(kb + s);
-    if (kb + NS - 1 < ke) wait_vmcnt<(NS - 1) * C::kLoads>();  // tile kb has landed
-    else wait_vmcnt<0>();
-    ring_barrier();
-
+  // The same for the 128 x 128 tiles, whose CU holds a second workgroup (or a
+  // four-stage ring): reads one MFMA group ahead, the barrier at the end of a
+  // tile. The loop above is 3-9 % slower here (Qwen2.5-7B down projection of
+  // 2000 rows 302 -> 331 us): the second workgroup already covers the reads
+  // behind the barrier.
+  template <typename Issue>
+  __device__ static __forceinline__ void mainloop_small(char* smem, int kb, int ke, Acc& acc, Issue issue) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / (BN / WN), wn = wave % (BN / WN);
+    const int r16 = lane & 15, grp = lane >> 4;
     constexpr int KS = BK / 32;   // 32-deep MFMA substeps per tile
     constexpr int G = KS * MI;    // MFMA groups per tile (one A fragment each)
     auto tileA = [&](int kt) { return reinterpret_cast<const uint16_t*>(smem + (kt % NS) * C::kStage); };
@@ -729,6 +764,89 @@ struct DmaGemm {
         step(kt + 1, std::integral_constant<int, 1>());
       }
       if (kt < ke) step(kt, std::integral_constant<int, 0>());
+    }
+  }
+
+  // acc = A[rows of tile tm, k-tiles kb..ke-1] . B[rows of tile tn, same]^T.
+  // Starts with a barrier, so the ring may still hold the previous tile.
+  __device__ static __forceinline__ void mainloop(const GemmArgs& g, char* smem, int tm, int tn, int kb, int ke,
+                                                  Acc& acc) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / (BN / WN), wn = wave % (BN / WN);
+    const int r16 = lane & 15, grp = lane >> 4;
+    const int m0 = tm * BM;
+    // DMA sources are buffer resources over A, A2, B, B2 whose size is the
+    // matrix's rows x leading dimension: a row beyond M (or N) is out of range
+    // and reads as zeros, so ragged tiles need no clamping. Load i of this
+    // wave fills tile rows RPL (wave + kWaves i) .. + RPL; the lane part of
+    // the offset (row lane / CPR, physical chunk lane % CPR holding logical
+    // chunk swz^-1) is the same for every load, the row base is uniform.
+    const int lr = lane / CPR;
+    const int lc = swz<BK>(lr, lane % CPR);  // swz is an involution for a fixed row
+    const RowSrc sa{g.a, g.M, g.lda}, sa2{g.a2, g.M, g.lda2};
+    const int nrows_b = EPI == EPI_SWIGLU ? 2 * g.f : g.N;
+    const RowSrc sb{g.b, nrows_b, g.ldb}, sb2{g.b2, nrows_b, g.ldb2};
+    const uint32_t va = uint32_t(lr * g.lda + lc * 8) * 2u, va2 = uint32_t(lr * g.lda2 + lc * 8) * 2u;
+    const uint32_t vb = uint32_t(lr * g.ldb + lc * 8) * 2u, vb2 = uint32_t(lr * g.ldb2 + lc * 8) * 2u;
+    // first B row of load i (uniform)
+    auto brow = [&](int i) {
+      const int r = RPL * (wave + C::kWaves * i);
+      if constexpr (EPI == EPI_SWIGLU) {
+        // each 128-row block of the B tile holds 64 gate units then the same 64 up units
+        const int blk = r / 128, rr = r % 128, u0 = (tn * (BN / 128) + blk) * 64;
+        return rr < 64 ? u0 + rr : g.f + u0 + (rr - 64);
+      } else {
+        return tn * BN + r;
+      }
+    };
+    // part P of NP of tile kt's loads (A's, then B's)
+    auto issue_part = [&](int kt, auto Pc, auto NPc) {
+      constexpr int P = decltype(Pc)::value, NP = decltype(NPc)::value;
+      const int k0 = kt * BK;
+      const bool second = k0 >= g.K1;
+      const int kc = second ? k0 - g.K1 : k0;
+      char* st = smem + (kt % NS) * C::kStage;
+      const RowSrc& A = second ? sa2 : sa;
+      const RowSrc& Bm = second ? sb2 : sb;
+      const uint32_t vA = second ? va2 : va, vB = second ? vb2 : vb;
+#pragma unroll
+      for (int l = P * C::kLoads / NP; l < (P + 1) * C::kLoads / NP; ++l) {
+        if (l < C::kLoadsA) {
+          const int i = l;
+          dma16(A, vA, uint32_t((m0 + RPL * (wave + C::kWaves * i)) * A.ld + kc) * 2u,
+                st + 1024 * (wave + C::kWaves * i));
+        } else {
+          const int i = l - C::kLoadsA;
+          dma16(Bm, vB, uint32_t(brow(i) * Bm.ld + kc) * 2u, st + BM * C::kRowBytes + 1024 * (wave + C::kWaves * i));
+        }
+      }
+    };
+    auto issue = [&](int kt) { issue_part(kt, std::integral_constant<int, 0>(), std::integral_constant<int, 1>()); };
+
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Every wave is done with the LDS before the ring is refilled. Stores of
+    // an earlier tile may still be in flight: they only add to the counter,
+    // so each wait below still covers the loads it is for (whether or not the
+    // stores retire in order), and they drain under this tile's first loads.
+    ring_barrier();
+    // Ring of NS buffers, all filled ahead: tile kt lives in buffer kt % NS,
+    // and tile kt + NS is issued into it as soon as tile kt has been read.
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (kb + s < ke) issue(kb + s);
+    if (kb + NS - 1 < ke) wait_vmcnt<(NS - 1) * C::kLoads>();  // tile kb has landed
+    else wait_vmcnt<0>();
+    ring_barrier();
+
+    if constexpr (C::kWaveEpi) {
+      mainloop_wide(smem, kb, ke, acc, issue_part);
+    } else {
+      mainloop_small(smem, kb, ke, acc, issue);
     }
   }
 
@@ -963,8 +1081,13 @@ __global__ __launch_bounds__((DmaCfg<BM, BN, WM, WN, NS, BK>::kThreads)) void ge
   }
   __syncthreads();  // the partials' loads below are issued after their flags were seen
   // a partial not seen is left out (and reported) rather than waited for
-  G::template epilogue<kTailMaxSplit - 1>(g, smem, tt.tm, tt.tn, acc, t * (s - 1),
-                                          __builtin_amdgcn_readfirstlane(n_seen));
+  const int seen = __builtin_amdgcn_readfirstlane(n_seen);
+  if constexpr (G::C::kWaveEpi) {
+    G::template epilogue<kTailMaxSplit - 1>(g, smem, tt.tm, tt.tn, acc, t * (s - 1), seen);
+  } else {
+    G::template add_partials<kDeepMaxSplit - 1>(g, t * (s - 1), seen, acc);
+    G::template epilogue<0, false>(g, smem, tt.tm, tt.tn, acc);
+  }
 }
 
 // Persistent grid of 8 * px workgroups (workgroup w runs on XCD w % 8 as the
@@ -1165,6 +1288,17 @@ static int resident_slots(const void* fn, int threads) {
   return v;
 }
 
+// CUs of the current device (0 if it cannot be asked).
+static int device_cus() {
+  static std::atomic<int> cache[64];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  if ((cus = cache[dev].load(std::memory_order_relaxed))) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  cache[dev].store(cus, std::memory_order_relaxed);
+  return cus;
+}
+
 // Schedule of a launch: px = workgroups per XCD of a persistent grid (0: one
 // tile per workgroup) and split (1: stream-K split of the last round).
 //  - Long reductions (at least kSkMinK k-iterations per tile) whose last
@@ -1225,6 +1359,25 @@ static TailSplit choose_tail(int nt, int nk, int slots, int part_slots, bool ava
   for (int sp = kTailMaxSplit; sp >= 2; --sp)
     if (sp * r <= P && r * (sp - 1) <= part_slots && nk / sp >= kTailMinK) return {r, sp};
   return {0, 1};
+}
+
+// A grid of small tiles that leaves every CU at most one workgroup. With the
+// two-stage ring such a workgroup takes 0.7-0.9 us per k-tile whatever the
+// width of the projection, the latency of its loads (Qwen2.5-7B down
+// projection of 70-900 rows, 296 k-tiles: 257-289 us); four stages keep three
+// tiles in flight (172-206 us), and while three or four workgroups per tile
+// fit the CUs, its k-tiles are split between them (gemm_bf16_tail_kernel;
+// 113 us at 70-150 rows; two pieces lost to the unsplit ring at every width
+// tried, 96-128 tiles). beside: tiles of a launch that runs at the same time
+// on another stream. Returns the pieces per tile, 0: not such a grid.
+// DSF_GEMM_TAIL=0 (read at every launch) turns the split off.
+static int choose_deep(int nt, int nk, int cus, int beside, int part_slots, bool avail) {
+  if (schedule_override() || nt + beside > cus) return 0;
+  const char* e = getenv("DSF_GEMM_TAIL");
+  if (!avail || (e && e[0] == '0')) return 1;
+  for (int sp = kDeepMaxSplit; sp >= kDeepMinSplit; --sp)
+    if (sp * nt + beside <= cus && nt * (sp - 1) <= part_slots && nk / sp >= kDeepMinK) return sp;
+  return 1;
 }
 
 // The DMA kernels address each operand through a buffer resource with a
@@ -1411,40 +1564,68 @@ static void skinny_split(int ntn, int K, int* splits, int* kc) {
   *splits = (K + c - 1) / c;
 }
 
-// Large tiles when the grid of 256 x 256 tiles still fills the chip for more
-// than a round (at least kLargeMinTiles tiles), and the SwiGLU units split
-// into whole 128-unit tiles; small tiles otherwise. Measured on one layer of
-// each workload: the large tiles win on every Qwen2.5-7B projection (gate/up
-// 0.38 -> 0.47 of peak, down 0.32 -> 0.46), on the NeoX-1.4B QKV and up, and
-// on the NeoX-160M QKV alone; the small ones on the 768- to 2048-wide down
-// projections, whose grids of large tiles cover the chip once or less. In
-// the stacks, forward projections with shallow reductions (K below
-// kLargeMinDepth: 896 and 1536 on the Qwen2.5-0.5B and -1.5B shapes) keep
-// the small tiles up to kLargeShallowMinTiles tiles, where a large tile's
-// short main loop leaves its epilogue a bigger share (stacks 1.5 and 0.6 %
-// faster). A caller that runs two projections side by side on two streams
-// picks one size for both (GemmArgs::tile_hint, gemm_pair_tile_hint): a
-// 256 x 256 workgroup takes most of a CU's LDS and cannot share the CU with
-// a 128 x 128 one, so mixed sizes starve the large-tile launch.
+// The tile size of a projection, from what a grid of each is expected to take
+// (microseconds), nt tiles of nk 64-deep k-tiles on cus CUs:
+//  - 128 x 128, two workgroups per CU: a k-tile takes a full round 1.0 us, a
+//    last round of at most one workgroup per CU 0.65; 4 us of epilogue per
+//    round. A last round that the stream-K grid would take is spread instead.
+//    The gate|up launches, which stream the widest weights, take a tenth more.
+//  - 256 x 256, one workgroup per CU: 1.45 us a k-tile and 12 us of epilogue
+//    per round; a last round split along K in 2, 3 or 4 pieces (choose_tail)
+//    about 1.3, 0.55 or 0.45 us and 20 us for the hand-over.
+// The constants come from a sweep of every projection of the five workload
+// shapes at 300 to 16384 rows, weights and activations from memory; over that
+// sweep the rule's choice is within 9 % of the better size, and it replaces
+// one that took the large tiles from 320 of them: the Qwen2.5-1.5B down
+// projection of 7000-9800 rows (168-234 large tiles) 276-295 -> 217-232 us, the
+// NeoX-1.4B one 301 -> 240, Qwen2.5-7B QKV at 2718 rows 108 -> 97. Grids that
+// leave each CU at most one small workgroup keep the small tiles (choose_deep).
+// The NeoX QKV and up projections, which share the chip on two streams, take
+// one size for both, from the sum of their tiles (GemmArgs::tile_hint): a
+// 256 x 256 workgroup takes most of a CU's LDS and cannot share the CU with a
+// 128 x 128 one, so mixed sizes starve the large-tile launch.
 // DSF_GEMM_TILE=small|large (read at every launch) forces one of them.
-constexpr int kLargeMinTiles = 320;
-constexpr int kLargeMinDepth = 2048;
-constexpr int kLargeShallowMinTiles = 640;
-constexpr int kLargePairMinTiles = 400;
-
-// The tile size for a pair of forward projections that share the chip,
-// from the leading one's shape (M x N, reduction K): deep reductions keep
-// each launch's own rule (large from kLargeMinTiles tiles for both NeoX-1.4B
-// projections); shallow ones take one size for both, large from
-// kLargePairMinTiles tiles of the leading grid. NeoX-130M shape (QKV grids
-// of 405-522 large tiles): large for both 2-8 % faster than small for both;
-// NeoX-160M (171-441): small for both 1.5 % faster than the sizes chosen
-// one launch at a time.
-int gemm_pair_tile_hint(int M, int N, int K) {
-  if (K >= kLargeMinDepth) return 0;
-  const int64_t nt = int64_t((M + TileLarge::BM - 1) / TileLarge::BM) * ((N + TileLarge::BN - 1) / TileLarge::BN);
-  return nt >= kLargePairMinTiles ? 2 : 1;
+static double small_tile_us(int64_t nt, int nk, int cus, bool stream_k, bool wide) {
+  const int64_t P = 2 * int64_t(cus), full = nt / P, rem = nt % P;
+  double rounds = double(full) + (rem == 0 ? 0.0 : rem <= cus ? 0.65 : 1.0), over = 4.0 * double(full + (rem > 0));
+  if (stream_k && nk >= kSkMinK && full > 0 && rem > 0 && 4 * rem <= P) {
+    rounds = 1.15 * double(nt) / double(P);
+    over = 14.0;
+  }
+  return nk * rounds * (wide ? 1.1 : 1.0) + over + 8.0;
 }
+static double large_tile_us(int64_t nt, int nk, int cus, bool tail) {
+  const int64_t full = nt / cus, rem = nt % cus;
+  double rounds = 1.45 * double(full), over = 12.0 * double(full + (rem > 0)) + 8.0;
+  if (rem > 0) {
+    const TailSplit ts = tail ? choose_tail(int(nt), nk, cus, kSkMaxSlots / 2, true) : TailSplit{0, 1};
+    rounds += ts.s == 4 ? 0.45 : ts.s == 3 ? 0.55 : ts.s == 2 ? 1.3 : 1.45;
+    if (ts.s > 1) over += 20.0;
+  }
+  return nk * rounds + over;
+}
+static bool large_tiles_win(int64_t nt_small, int64_t nt_large, int nk, bool tail, bool stream_k, bool wide) {
+  const int cus = device_cus();
+  if (nt_small <= cus || cus <= 0) return false;
+  return large_tile_us(nt_large, nk, cus, tail) < small_tile_us(nt_small, nk, cus, stream_k, wide);
+}
+template <class TC>
+static int64_t tile_count(int M, int N) {
+  return int64_t((M + TC::BM - 1) / TC::BM) * ((N + TC::BN - 1) / TC::BN);
+}
+
+// GemmArgs::tile_hint for two forward projections of M rows and reduction K,
+// N1 and N2 wide, run side by side.
+int gemm_pair_tile_hint(int M, int N1, int N2, int K) {
+  return large_tiles_win(tile_count<TileSmall>(M, N1) + tile_count<TileSmall>(M, N2),
+                         tile_count<TileLarge>(M, N1) + tile_count<TileLarge>(M, N2), K / 64, false, false, false)
+             ? 2
+             : 1;
+}
+
+// The backward's weight gradients (EPI_STORE_F32) take the large tiles from
+// this many of them: smaller grids go to the stream-K grid of small tiles.
+constexpr int kLargeMinTiles = 320;
 
 template <int EPI>
 static bool use_large_tiles(const GemmArgs& g) {
@@ -1453,11 +1634,12 @@ static bool use_large_tiles(const GemmArgs& g) {
   if (e && !strcmp(e, "small")) return false;
   if (e && !strcmp(e, "large")) return true;
   if (g.tile_hint) return g.tile_hint == 2;
-  const int64_t ntm = (g.M + TileLarge::BM - 1) / TileLarge::BM;
-  const int64_t ntn = EPI == EPI_SWIGLU ? g.f / (TileLarge::BN / 2) : (g.N + TileLarge::BN - 1) / TileLarge::BN;
-  const int64_t nt = ntm * ntn;
-  if (EPI < EPI_STORE && g.K < kLargeMinDepth) return nt >= kLargeShallowMinTiles;
-  return nt >= kLargeMinTiles;
+  const int cols = EPI == EPI_SWIGLU ? 2 * g.f : g.N;
+  const int64_t nt = tile_count<TileLarge>(g.M, cols);
+  if (EPI == EPI_STORE_F32) return nt >= kLargeMinTiles;
+  const bool split = EPI < EPI_STORE && g.part && g.flags;
+  return large_tiles_win(tile_count<TileSmall>(g.M, cols), nt, g.K / 64, split && EPI != EPI_SWIGLU, split,
+                         EPI == EPI_SWIGLU);
 }
 
 template <int EPI, class TC>
@@ -1476,6 +1658,29 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
     // stream-K kernel's partial-sum hand-over does not fit their register
     // budget beside 128 accumulators per lane. Among the backward kinds only
     // the weight gradients (fp32 output) take them.
+    if constexpr (BM == TileSmall::BM && BN == TileSmall::BN && EPI != EPI_STORE_F32) {
+      using TD = TileDeep;
+      auto fn = gemm_bf16_dma_kernel<EPI, TD::BM, TD::BN, TD::WM, TD::WN, TD::NS, TD::BK>;
+      const int nt = ntn * ga.ntm, cus = resident_slots<std::integral_constant<int, 96 + EPI>>((const void*)fn, Cfg::kThreads);
+      const int sp = choose_deep(nt, g.K / BK, cus, g.beside, std::min(kPartSlots, gemm_flag_count()), g.part && g.flags);
+      if (sp > 0) {
+        ga.ntn = ntn;
+        ga.group_m = 0;
+        if constexpr (EPI < EPI_STORE) {
+          if (sp > 1) {
+            ga.tail0 = 0;
+            ga.tail_r = nt;
+            ga.tail_s = sp;
+            ga.spin_limit = spin_limit();
+            launch_timed(gemm_bf16_tail_kernel<EPI, TD::BM, TD::BN, TD::WM, TD::WN, TD::NS, TD::BK>,
+                         dim3(kXcds * sp * ((nt + kXcds - 1) / kXcds)), dim3(Cfg::kThreads), s, ga);
+            return;
+          }
+        }
+        launch_timed(fn, dim3(nt), dim3(Cfg::kThreads), s, ga);
+        return;
+      }
+    }
     if constexpr (BM == TileSmall::BM && BN == TileSmall::BN && (EPI < EPI_STORE || EPI == EPI_STORE_F32)) {
       if (g.part && g.flags) {
         auto fn = gemm_bf16_sk_kernel<EPI, BM, BN, WM, WN, NS, BK>;
