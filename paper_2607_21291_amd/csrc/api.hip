@@ -626,13 +626,14 @@ uint32_t* at_flags(const Ctx& c) { return at_status(c) + kCtlFlagsWord; }
 // per-sequence counters of the router + Top-K launch (bf16), after the flags
 uint32_t* at_route_count(const Ctx& c) { return at_flags(c) + gemm_flag_count(); }
 
-// Zero the control block at the start of a call (one launch): the status
-// word, the stream-K flags and the router counters. GEMM launches then take
-// epochs 1, 2, ... (the flags of a finished launch never equal a later
-// epoch), and each router + Top-K launch leaves its counters zero again.
-int reset_stream_k(const Ctx& c) {
+// Start of a call (one launch): the RoPE table, and the control block zeroed
+// (the status word, the stream-K flags and the router counters). GEMM launches
+// then take epochs 1, 2, ... (the flags of a finished launch never equal a
+// later epoch), and each router + Top-K launch leaves its counters zero again.
+int start_call(const Ctx& c) {
   c.epoch = 0;
-  DSF_HIP(launch_zero_u32(at_status(c), int64_t(ctl_words(c.B)), c.s));
+  DSF_HIP(launch_call_start(reinterpret_cast<float*>(c.ws + c.plan.rope), c.T, c.D->rotary_dims, c.D->rope_theta,
+                            at_status(c), int64_t(ctl_words(c.B)), c.s));
   return DSF_OK;
 }
 
@@ -875,9 +876,8 @@ extern "C" int dsf_sparse_block_forward(const dsf_layer_desc* desc, const dsf_la
   Ctx c{desc, dtype, B, T, (char*)workspace, plan, stream, 0, nullptr};
   rc = get_aux(&c.aux);
   if (rc) return rc;
-  rc = reset_stream_k(c);
+  rc = start_call(c);
   if (rc) return rc;
-  DSF_HIP(launch_rope_table(at<float>(c, plan.rope), T, desc->rotary_dims, desc->rope_theta, stream));
   return run_layer(c, weights, x, k, dense, (flags & DSF_FLAG_GATE) != 0, scores_out, idx_out, idx_in);
 }
 
@@ -908,9 +908,8 @@ extern "C" int dsf_stack_forward(const dsf_layer_desc* desc, const dsf_layer_wei
   Ctx c{desc, dtype, B, T, (char*)workspace, plan, stream, 0, nullptr};
   rc = get_aux(&c.aux);
   if (rc) return rc;
-  rc = reset_stream_k(c);
+  rc = start_call(c);
   if (rc) return rc;
-  DSF_HIP(launch_rope_table(at<float>(c, plan.rope), T, desc->rotary_dims, desc->rope_theta, stream));
   const size_t xbytes = elem_bytes(dtype) * size_t(B) * T * desc->d_model;
   for (int l = 0; l < L; ++l) {
     if (with_sim) DSF_HIP(launch_copy(x, at<char>(c, plan.xin), xbytes, stream));
@@ -1208,8 +1207,8 @@ int decode_step_impl(const dsf_layer_desc* desc, const dsf_layer_weights* weight
     if (rc) return rc;
   }
   DecCtx c{desc, dtype, B, max_pos, cap, (char*)workspace, plan, stream};
-  DSF_HIP(launch_rope_table(dat<float>(c, plan.rope), max_pos, desc->rotary_dims, desc->rope_theta, stream));
-  DSF_HIP(launch_zero_u32(dat<uint32_t>(c, plan.counters), plan.ncounters, stream));
+  DSF_HIP(launch_call_start(dat<float>(c, plan.rope), max_pos, desc->rotary_dims, desc->rope_theta,
+                            dat<uint32_t>(c, plan.counters), plan.ncounters, stream));
   for (int l = 0; l < L; ++l) {
     rc = run_decode_layer(c, &weights[l], x, pos, thr + size_t(l) * B, scores_out ? scores_out + size_t(l) * B : nullptr,
                           keep_out ? keep_out + size_t(l) * B : nullptr, cache_k[l], cache_v[l],
@@ -1293,9 +1292,10 @@ extern "C" int dsf_stack_prefill(const dsf_layer_desc* desc, const dsf_layer_wei
   Ctx c{desc, dtype, B, T, (char*)workspace, plan, stream, 0, nullptr};
   rc = get_aux(&c.aux);
   if (rc) return rc;
-  rc = reset_stream_k(c);
-  if (rc) return rc;
-  if (T > 0) DSF_HIP(launch_rope_table(at<float>(c, plan.rope), T, desc->rotary_dims, desc->rope_theta, stream));
+  if (k_max > 0) {  // without kept tokens no layer runs (and the workspace was not checked)
+    rc = start_call(c);
+    if (rc) return rc;
+  }
   for (int l = 0; l < L; ++l) {
     if (k[l] > 0) {
       rc = run_layer(c, &weights[l], x, k[l], false, false, nullptr, nullptr, nullptr);
@@ -1385,9 +1385,8 @@ extern "C" int dsf_align_stack_forward(const dsf_layer_desc* desc, const dsf_lay
   Ctx c{desc, dtype, B, T, (char*)workspace, plan, stream, 0, nullptr};
   rc = get_aux(&c.aux);
   if (rc) return rc;
-  rc = reset_stream_k(c);
+  rc = start_call(c);
   if (rc) return rc;
-  DSF_HIP(launch_rope_table(at<float>(c, plan.rope), T, desc->rotary_dims, desc->rope_theta, stream));
   const bool gate = (flags & DSF_FLAG_GATE) != 0;
   for (int l = 0; l < L; ++l) {
     rc = run_layer(c, &weights[l], x_dense, T, true, false, nullptr, nullptr, nullptr);  // teacher
@@ -1558,7 +1557,8 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   // zero the control block: the status word and the stream-K flags
   BwdSk sk{reinterpret_cast<float*>(ws + p.skpart), reinterpret_cast<uint32_t*>(ws + p.ctl) + kCtlFlagsWord,
            reinterpret_cast<uint32_t*>(ws + p.ctl), 0};
-  DSF_HIP(launch_zero_u32(sk.status, int64_t(kCtlFlagsWord) + gemm_flag_count(), s));
+  const int64_t nctl = int64_t(kCtlFlagsWord) + gemm_flag_count();
+  DSF_HIP(launch_call_start((float*)(ws + p.rope), k > 0 ? T : 0, D.rotary_dims, D.rope_theta, sk.status, nctl, s));
   const size_t xbytes = size_t(B) * T * D.d_model * 2;
   DSF_HIP(launch_copy(dy, dx, xbytes, s));  // skipped rows: dx = dy
   if (k == 0) return DSF_OK;                // (the weight gradients are then not written)
@@ -1568,7 +1568,6 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   const int dq = Hq * hd, dkv = Hkv * hd, N = B * k, Np = p.Np, fup = p.fup, cq = p.dqkv_cols;
 
   // ---- recompute the forward's activations of the kept rows
-  DSF_HIP(launch_rope_table(F(p.rope), T, D.rotary_dims, D.rope_theta, s));
   DSF_HIP(launch_gather(dtype, x, B, T, d, idx, k, P(p.xc), s));
   NormArgs na{};
   na.dtype = dtype; na.src = P(p.xc); na.src_rows = 0; na.B = B; na.kk = k; na.d = d; na.eps = D.norm_eps;

@@ -96,8 +96,9 @@ hipError_t launch_kl_align(int dtype, const void* ld, const void* ls, int64_t ro
                            double* partial, double* accum, hipStream_t s);
 
 // ---- streaming kernels (kernels_misc.hip) ----
-// table[p][i] = (cos, sin)(p * theta^(-2i/R)), p < T, i < R/2, computed in fp64.
-hipError_t launch_rope_table(float* table, int T, int R, double theta, hipStream_t s);
+// table[p][i] = (cos, sin)(p * theta^(-2i/R)), p < T, i < R/2, computed in
+// fp64; and zero[0 .. nz) = 0 (nz 0: only the table).
+hipError_t launch_call_start(float* table, int T, int R, double theta, uint32_t* zero, int64_t nz, hipStream_t s);
 int sim_grid(int64_t n_tokens);
 hipError_t launch_sim_stats(int dtype, const void* a, const void* c, int64_t n, int d, float* per_tok,
                             double* partial, double* accum, hipStream_t s);
