@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -50,6 +51,11 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // The current device must exist and be gfx950 (the only code object built).
 static int check_device() {
+  // devices found to be gfx950 by an earlier call: one query per call
+  static std::atomic<uint64_t> known{0};
+  int cur = 0;
+  if (hipGetDevice(&cur) == hipSuccess && cur >= 0 && cur < 64 && (known.load(std::memory_order_relaxed) >> cur & 1))
+    return DSF_OK;
   int n = 0;
   if (hipGetDeviceCount(&n) != hipSuccess || n <= 0) {
     (void)hipGetLastError();
@@ -67,6 +73,7 @@ static int check_device() {
     arch_ok[dev] = std::strncmp(prop.gcnArchName, "gfx950", 6) == 0 ? 1 : 0;
   }
   if (!arch_ok[dev]) return fail(DSF_EUNSUPPORTED, "device %d is not gfx950 (MI355X)", dev);
+  if (dev < 64) known.fetch_or(uint64_t(1) << dev, std::memory_order_relaxed);
   return DSF_OK;
 }
 

@@ -44,3 +44,12 @@ def test_prefill_that_keeps_nothing(dev):
     P.stack_prefill(make_desc(w), [dl.weights for dl in dls], [0, 0], x, ck, cv, clen, ws)
     torch.cuda.synchronize()
     assert torch.equal(x, x0) and (clen == 0).all() and (ws == 0xA5).all()
+
+
+def test_current_stream_handle(dev):
+    from paper_2607_21291_amd import _binding
+    side = torch.cuda.Stream()
+    assert _binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert _binding._stream(None) == side.cuda_stream
+    assert _binding._stream(side) == side.cuda_stream
