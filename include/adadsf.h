@@ -278,28 +278,32 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * thread exits. DSF_SINGLE_STREAM=1, read at every call, keeps all work on
  * the caller's stream (results are bitwise the same).
  *
- * Projection schedule. Each bf16 projection GEMM takes 256 x 256 output
- * tiles when they still fill the chip for more than a round (at least 320
- * tiles; 640 for forward projections with a reduction shorter than 2048;
- * the GPT-NeoX QKV and up projections, which run side by side, take one size
- * for both), 128 x 128 tiles otherwise; the environment variable
- * DSF_GEMM_TILE=small or =large, read at every launch, forces one size. With
- * 256 x 256 tiles each workgroup runs one tile; for the forward projections
- * other than the SwiGLU gate|up (bf16, on the call's workspace), when the
- * tiles would end in a last round at most half as many as the resident
- * workgroups, those last tiles go to a second launch that cuts each along K
- * into 2-4 pieces, the last piece adding the others' partial sums in a
- * fixed order (deterministic; rounds differently from the unsplit grid).
- * DSF_GEMM_TAIL=0, read at every launch, turns that split off. With
- * 128 x 128 tiles each
- * GEMM runs one output tile per workgroup; or, with more tiles than resident
- * workgroups, a persistent grid
- * taking whole tiles (same arithmetic); or, when that would end in a short
- * last round of tiles on a long reduction, a stream-K grid (workgroups split
- * the k-iterations of the last tiles and add their partial sums in a fixed
+ * Projection schedule. Up to 64 rows (kept tokens of all sequences), a
+ * projection runs on the few-row kernel, which streams the weights; the
+ * widest bf16 ones (32768 columns) only up to 16 rows. Above, each bf16
+ * projection takes 128 x 128 or 256 x 256 output tiles, whichever an
+ * estimate of both grids' rounds puts first (the GPT-NeoX QKV and up
+ * projections, which run side by side, take one size for both); the
+ * environment variable DSF_GEMM_TILE=small or =large, read at every launch,
+ * forces one size. A grid that gives each CU at most one 128 x 128 tile
+ * keeps four LDS stages in flight and, while three or four workgroups per
+ * tile still fit the CUs and the reduction is long enough, cuts each tile
+ * along K into as many pieces. With 256 x 256 tiles each workgroup runs one
+ * tile; for the forward projections other than the SwiGLU gate|up (bf16, on
+ * the call's workspace), when the tiles would end in a last round at most
+ * half as many as the resident workgroups, those last tiles go to a second
+ * launch that cuts each along K into 2-4 pieces. In both, the last piece
+ * adds the others' partial sums in a fixed order (deterministic; rounds
+ * differently from the unsplit grid), and DSF_GEMM_TAIL=0, read at every
+ * launch, turns the split off. With more 128 x 128 tiles than resident
+ * workgroups, one output tile per workgroup; or a persistent grid taking
+ * whole tiles (same arithmetic); or, when that would end in a short last
+ * round of tiles on a long reduction, a stream-K grid (workgroups split the
+ * k-iterations of the last tiles and add their partial sums in a fixed
  * order, which rounds differently). All are deterministic. The environment
  * variable DSF_GEMM_SCHEDULE=classic, =persistent or =streamk, read at every
- * launch, forces one of them (testing and tuning).
+ * launch, forces one of them (testing and tuning); any of these variables
+ * also takes few-row projections to the tiles.
  *
  * Call status. The first 4 bytes of the workspace hold a status word that
  * each call of dsf_sparse_block_forward, dsf_stack_forward,
@@ -307,8 +311,9 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * clears at its start and that
  * its kernels OR bits into; read it with dsf_workspace_status once the call's
  * work is enqueued. A call with nothing to do (B, T or k zero), which
- * launches nothing, leaves the word as it was. DSF_WS_STATUS_SK_TIMEOUT: a stream-K workgroup, or the last
- * piece of a split tile, that must add an earlier workgroup's partial sum waits for it with a bounded spin of
+ * launches nothing, leaves the word as it was. DSF_WS_STATUS_SK_TIMEOUT: a
+ * stream-K workgroup, or the last piece of a split tile, that must add an
+ * earlier workgroup's partial sum waits for it with a bounded spin of
  * 2^22 polls of its flag (the partial is normally ready within microseconds,
  * because the hardware dispatches workgroups in order); if the wait gives
  * up, the tile is written without that partial, so the call's output is
@@ -397,12 +402,12 @@ size_t dsf_backward_workspace_size(const dsf_layer_desc* desc, int dtype, int B,
  * forward's kernels) rather than kept by the forward. bf16 only
  * (DSF_EUNSUPPORTED for DSF_F32); fp32 accumulation, deterministic. k == 0
  * copies dy into dx and leaves the gradients unwritten. The weight gradients
- * reduce over every kept token into few output tiles: when that would leave
- * most of the chip idle, their GEMMs take the stream-K grid (equal pieces of
- * the k-iterations per workgroup, partial sums added in a fixed order). The
- * workspace starts with the same status word as the forward's (cleared by
- * every call with B, T > 0; DSF_WS_STATUS_SK_TIMEOUT if a stream-K wait gave
- * up), read with dsf_workspace_status. Errors: DSF_EINVAL for null or
+ * reduce over every kept token into few output tiles, so up to eight
+ * workgroups share a tile's tokens; the last of them adds the others' partial
+ * sums in a fixed order. The workspace starts with the same status word as
+ * the forward's (cleared by every call with B, T > 0; DSF_WS_STATUS_SK_TIMEOUT
+ * if the wait for a partial sum gave up), read with dsf_workspace_status.
+ * Errors: DSF_EINVAL for null or
  * misaligned pointers and bad sizes, DSF_EWORKSPACE for a short workspace. */
 int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_layer_weights* weights, int dtype,
                               const void* x, const void* dy, int B, int T, int k, const int32_t* idx,

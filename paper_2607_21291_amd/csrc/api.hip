@@ -1413,8 +1413,8 @@ extern "C" int dsf_align_stack_forward(const dsf_layer_desc* desc, const dsf_lay
 namespace {
 struct BwdPlan {
   size_t ctl, skpart, rope, xc, a1, a2, h, m2, q, k, v, attn, u, dd, du, dm, dao, dattn, dqf, dkf, dvf, lse, dvec, dqkv, da, acc;
-  size_t mean1, rstd1, mean2, rstd2, wdT, wuT, woT, wqT, tdd, tact, tdu, tm, tdao, tattn, tdqkv, ta1, part, total;
-  int Np, fup, dqkv_cols;
+  size_t wdT, wuT, woT, wqT, act, bpart, bpart_bytes, total;
+  int fup, dqkv_cols;
 };
 
 BwdPlan make_bwd_plan(const dsf_layer_desc& D, int B, int T, int k) {
@@ -1422,18 +1422,17 @@ BwdPlan make_bwd_plan(const dsf_layer_desc& D, int B, int T, int k) {
                dkv = size_t(D.n_kv_heads) * D.head_dim, f = D.d_ff;
   const bool qwen = D.block == DSF_BLOCK_QWEN_SEQ;
   BwdPlan p{};
-  p.Np = int((N + 63) / 64 * 64);
   p.fup = int(qwen ? 2 * f : f);
   p.dqkv_cols = int(dq + 2 * dkv);
-  const size_t Np = size_t(p.Np), fup = size_t(p.fup), cq = size_t(p.dqkv_cols);
+  const size_t fup = size_t(p.fup), cq = size_t(p.dqkv_cols);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
     off += up256(bytes > 0 ? bytes : 1);
     return o;
   };
-  // control block at offset 0 (status word, then the stream-K flags), as in
-  // the forward's workspace, and the stream-K partial tiles
+  // control block at offset 0 (status word, then the weight gradients'
+  // flags), as in the forward's workspace, and their partial tiles
   p.ctl = take(sizeof(uint32_t) * (size_t(kCtlFlagsWord) + size_t(gemm_flag_count())));
   p.skpart = take(gemm_partial_bytes());
   p.rope = take(4 * size_t(T) * D.rotary_dims);
@@ -1460,24 +1459,14 @@ BwdPlan make_bwd_plan(const dsf_layer_desc& D, int B, int T, int k) {
   p.dqkv = take(2 * N * cq);
   p.da = take(2 * N * d);
   p.acc = take(4 * N * d);
-  p.mean1 = take(4 * N);
-  p.rstd1 = take(4 * N);
-  p.mean2 = take(4 * N);
-  p.rstd2 = take(4 * N);
   p.wdT = take(2 * f * d);
   p.wuT = take(2 * d * fup);
   p.woT = take(2 * dq * d);
   p.wqT = take(2 * d * cq);
-  p.tdd = take(2 * d * Np);
-  p.tact = take(2 * f * Np);
-  p.tdu = take(2 * fup * Np);
-  p.tm = take(2 * d * Np);
-  p.tdao = qwen ? take(2 * d * Np) : p.tdd;
-  p.tattn = take(2 * dq * Np);
-  p.tdqkv = take(2 * cq * Np);
-  p.ta1 = take(2 * d * Np);
+  p.act = take(2 * N * f);
   const size_t cmax = std::max(std::max(d, fup), cq);
-  p.part = take(4 * size_t(colsum_chunks(int(N))) * cmax);
+  p.bpart_bytes = 4 * kWgradMaxSplit * (cmax + 128);
+  p.bpart = take(p.bpart_bytes);
   p.total = off;
   return p;
 }
@@ -1491,21 +1480,10 @@ int check_bwd(const dsf_layer_desc* desc, int dtype, int B, int T, int k) {
   return DSF_OK;
 }
 
-// The stream-K state of one backward call: partial tiles, flags and status
-// word in its workspace, and the last epoch handed out since the flags were
-// zeroed.
-struct BwdSk {
-  float* part;
-  uint32_t *flags, *status;
-  uint32_t epoch;
-};
-
 // C[M, N] = A[M, K] . Bm[N, K]^T with one of the backward epilogues (plain
-// token rows: no positions, one "sequence" of M rows). With sk, a launch may
-// take the stream-K grid (the weight gradients, whose few output tiles would
-// leave most of the chip idle while each reduces over every kept token).
+// token rows: no positions, one "sequence" of M rows).
 int bwd_gemm(int epi, int M, int N, int K, const void* A, int lda, const void* Bm, int ldb, void* out, int ldo,
-             const void* bias, const void* res, int f, hipStream_t s, BwdSk* sk = nullptr) {
+             const void* bias, const void* res, int f, hipStream_t s, void* act = nullptr) {
   if (M == 0 || N == 0) return DSF_OK;
   GemmArgs g{};
   g.dtype = DSF_BF16;
@@ -1513,13 +1491,8 @@ int bwd_gemm(int epi, int M, int N, int K, const void* A, int lda, const void* B
   g.a = A; g.lda = lda; g.b = Bm; g.ldb = ldb;
   g.epi = epi; g.bias = bias; g.res = res; g.f = f;
   g.out = out; g.ldo = ldo;
+  g.x = act;
   g.B = 1; g.kk = M; g.T = M;
-  if (sk) {
-    g.part = sk->part;
-    g.flags = sk->flags;
-    g.status = sk->status;
-    g.epoch = ++sk->epoch;
-  }
   DSF_HIP(launch_gemm(g, s));
   return DSF_OK;
 }
@@ -1561,18 +1534,25 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   if (rc) return rc;
   hipStream_t s = stream;
   char* ws = (char*)workspace;
-  // zero the control block: the status word and the stream-K flags
-  BwdSk sk{reinterpret_cast<float*>(ws + p.skpart), reinterpret_cast<uint32_t*>(ws + p.ctl) + kCtlFlagsWord,
-           reinterpret_cast<uint32_t*>(ws + p.ctl), 0};
+  // the weight gradients' scratch, shared by them in turn; their flags lie in
+  // the control block, which the first launch clears
+  uint32_t* ctl = reinterpret_cast<uint32_t*>(ws + p.ctl);
+  float* part = reinterpret_cast<float*>(ws + p.skpart);
+  WgradScratch wg{part, gemm_partial_bytes(), reinterpret_cast<float*>(ws + p.bpart), p.bpart_bytes,
+                  ctl + kCtlFlagsWord, gemm_flag_count(), ctl, 0};
+  auto wgrad = [&](const void* dout, int rows, const void* in, int cols, float* dw, float* db) {
+    ++wg.epoch;
+    return launch_wgrad(dout, rows, rows, in, cols, cols, B * k, dw, db, wg, s);
+  };
   const int64_t nctl = int64_t(kCtlFlagsWord) + gemm_flag_count();
-  DSF_HIP(launch_call_start((float*)(ws + p.rope), k > 0 ? T : 0, D.rotary_dims, D.rope_theta, sk.status, nctl, s));
+  DSF_HIP(launch_call_start((float*)(ws + p.rope), k > 0 ? T : 0, D.rotary_dims, D.rope_theta, ctl, nctl, s));
   const size_t xbytes = size_t(B) * T * D.d_model * 2;
   DSF_HIP(launch_copy(dy, dx, xbytes, s));  // skipped rows: dx = dy
   if (k == 0) return DSF_OK;                // (the weight gradients are then not written)
   auto P = [&](size_t off) { return (void*)(ws + off); };
   auto F = [&](size_t off) { return (float*)(ws + off); };
   const int d = D.d_model, hd = D.head_dim, Hq = D.n_heads, Hkv = D.n_kv_heads, f = D.d_ff;
-  const int dq = Hq * hd, dkv = Hkv * hd, N = B * k, Np = p.Np, fup = p.fup, cq = p.dqkv_cols;
+  const int dq = Hq * hd, dkv = Hkv * hd, N = B * k, fup = p.fup, cq = p.dqkv_cols;
 
   // ---- recompute the forward's activations of the kept rows
   DSF_HIP(launch_gather(dtype, x, B, T, d, idx, k, P(p.xc), s));
@@ -1618,50 +1598,29 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
 
   // ---- the adjoint: d(delta) = gate * dy at the kept rows
   DSF_HIP(launch_gather_scale(dy, B, T, d, idx, k, gate ? scores : nullptr, P(p.dd), s));
-  // FFN down projection
-  if (G.w_down) {
-    DSF_HIP(launch_transpose(0, P(p.dd), N, d, d, P(p.tdd), Np, s));
-    DSF_HIP(launch_transpose(qwen ? 2 : 1, P(p.u), N, f, fup, P(p.tact), Np, s));
-    rc = bwd_gemm(EPI_STORE_F32, d, f, Np, P(p.tdd), Np, P(p.tact), Np, G.w_down, f, nullptr, nullptr, 0, s, &sk);
-    if (rc) return rc;
-  }
-  if (G.b_down && !qwen) DSF_HIP(launch_colsum(P(p.dd), N, d, d, nullptr, nullptr, nullptr, F(p.part), G.b_down, s));
-  DSF_HIP(launch_transpose(0, weights->w_down, d, f, f, P(p.wdT), d, s));
+  // FFN down projection (the adjoint's epilogue rebuilds the activation, the
+  // weight gradient's other factor)
+  DSF_HIP(launch_transpose(weights->w_down, d, f, f, P(p.wdT), d, s));
   rc = bwd_gemm(qwen ? EPI_SWIGLU_BWD : EPI_GELU_BWD, N, f, d, P(p.dd), d, P(p.wdT), d, P(p.du), fup, nullptr, P(p.u),
-                f, s);
+                f, s, G.w_down ? P(p.act) : nullptr);
   if (rc) return rc;
+  DSF_HIP(wgrad(P(p.dd), d, P(p.act), f, G.w_down, qwen ? nullptr : G.b_down));
   // FFN up projection
-  if (G.w_up) {
-    DSF_HIP(launch_transpose(0, P(p.du), N, fup, fup, P(p.tdu), Np, s));
-    DSF_HIP(launch_transpose(0, mrows, N, d, d, P(p.tm), Np, s));
-    rc = bwd_gemm(EPI_STORE_F32, fup, d, Np, P(p.tdu), Np, P(p.tm), Np, G.w_up, d, nullptr, nullptr, 0, s, &sk);
-    if (rc) return rc;
-  }
-  if (G.b_up && !qwen) DSF_HIP(launch_colsum(P(p.du), N, f, f, nullptr, nullptr, nullptr, F(p.part), G.b_up, s));
-  DSF_HIP(launch_transpose(0, weights->w_up, fup, d, d, P(p.wuT), fup, s));
+  DSF_HIP(wgrad(P(p.du), fup, mrows, d, G.w_up, qwen ? nullptr : G.b_up));
+  DSF_HIP(launch_transpose(weights->w_up, fup, d, d, P(p.wuT), fup, s));
   rc = bwd_gemm(EPI_STORE, N, d, fup, P(p.du), fup, P(p.wuT), fup, P(p.dm), d, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // second norm: NeoX's LN2 of the kept rows, Qwen's RMS2 of h = x + attention
   if (!qwen) {
     DSF_HIP(launch_norm_bwd(false, P(p.xc), P(p.dm), weights->norm2_w, N, d, D.norm_eps, F(p.acc), false, nullptr,
-                            nullptr, F(p.mean2), F(p.rstd2), s));
+                            nullptr, G.norm2_w, G.norm2_b, part, s));
   } else {
     DSF_HIP(launch_norm_bwd(true, P(p.h), P(p.dm), weights->norm2_w, N, d, D.norm_eps, F(p.acc), false, P(p.dd),
-                            P(p.dao), F(p.mean2), F(p.rstd2), s));
+                            P(p.dao), G.norm2_w, nullptr, part, s));
   }
-  if (G.norm2_w)
-    DSF_HIP(launch_colsum(P(p.dm), N, d, d, qwen ? P(p.h) : P(p.xc), qwen ? nullptr : F(p.mean2), F(p.rstd2),
-                          F(p.part), G.norm2_w, s));
-  if (G.norm2_b && !qwen) DSF_HIP(launch_colsum(P(p.dm), N, d, d, nullptr, nullptr, nullptr, F(p.part), G.norm2_b, s));
   // attention output projection
-  if (G.w_o) {
-    if (qwen || !G.w_down) DSF_HIP(launch_transpose(0, P(p.dao), N, d, d, P(p.tdao), Np, s));
-    DSF_HIP(launch_transpose(0, P(p.attn), N, dq, dq, P(p.tattn), Np, s));
-    rc = bwd_gemm(EPI_STORE_F32, d, dq, Np, P(p.tdao), Np, P(p.tattn), Np, G.w_o, dq, nullptr, nullptr, 0, s, &sk);
-    if (rc) return rc;
-  }
-  if (G.b_o && !qwen) DSF_HIP(launch_colsum(P(p.dao), N, d, d, nullptr, nullptr, nullptr, F(p.part), G.b_o, s));
-  DSF_HIP(launch_transpose(0, weights->w_o, d, dq, dq, P(p.woT), d, s));
+  DSF_HIP(wgrad(P(p.dao), d, P(p.attn), dq, G.w_o, qwen ? nullptr : G.b_o));
+  DSF_HIP(launch_transpose(weights->w_o, d, dq, dq, P(p.woT), d, s));
   rc = bwd_gemm(EPI_STORE, N, dq, d, P(p.dao), d, P(p.woT), d, P(p.dattn), dq, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // attention over the kept tokens, then RoPE turned back into token-major dqkv
@@ -1670,23 +1629,13 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   DSF_HIP(launch_rope_bwd(F(p.dqf), F(p.dkf), F(p.dvf), F(p.rope), idx, B, k, T, Hq, Hkv, hd, D.rotary_dims,
                           P(p.dqkv), s));
   // QKV projection
-  if (G.w_qkv) {
-    DSF_HIP(launch_transpose(0, P(p.dqkv), N, cq, cq, P(p.tdqkv), Np, s));
-    DSF_HIP(launch_transpose(0, P(p.a1), N, d, d, P(p.ta1), Np, s));
-    rc = bwd_gemm(EPI_STORE_F32, cq, d, Np, P(p.tdqkv), Np, P(p.ta1), Np, G.w_qkv, d, nullptr, nullptr, 0, s, &sk);
-    if (rc) return rc;
-  }
-  if (G.b_qkv) DSF_HIP(launch_colsum(P(p.dqkv), N, cq, cq, nullptr, nullptr, nullptr, F(p.part), G.b_qkv, s));
-  DSF_HIP(launch_transpose(0, weights->w_qkv, cq, d, d, P(p.wqT), cq, s));
+  DSF_HIP(wgrad(P(p.dqkv), cq, P(p.a1), d, G.w_qkv, G.b_qkv));
+  DSF_HIP(launch_transpose(weights->w_qkv, cq, d, d, P(p.wqT), cq, s));
   rc = bwd_gemm(EPI_STORE, N, d, cq, P(p.dqkv), cq, P(p.wqT), cq, P(p.da), d, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // first norm of the kept rows
   DSF_HIP(launch_norm_bwd(qwen, P(p.xc), P(p.da), weights->norm1_w, N, d, D.norm_eps, F(p.acc), true, nullptr,
-                          nullptr, F(p.mean1), F(p.rstd1), s));
-  if (G.norm1_w)
-    DSF_HIP(launch_colsum(P(p.da), N, d, d, P(p.xc), qwen ? nullptr : F(p.mean1), F(p.rstd1), F(p.part), G.norm1_w,
-                          s));
-  if (G.norm1_b && !qwen) DSF_HIP(launch_colsum(P(p.da), N, d, d, nullptr, nullptr, nullptr, F(p.part), G.norm1_b, s));
+                          nullptr, G.norm1_w, qwen ? nullptr : G.norm1_b, part, s));
   // kept rows: dx = dy + the block's gradient (the residual path carries dy)
   DSF_HIP(launch_scatter_grad(dy, F(p.acc), B, T, d, idx, k, dx, s));
   return DSF_OK;

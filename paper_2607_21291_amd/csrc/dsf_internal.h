@@ -141,10 +141,11 @@ enum EpiKind {
   EPI_RESID_SCATTER_GATE = 5,  // x[b, pos, n] += sigmoid(gate[b, pos]) * (resid + C + bias + bias2 - x[b, pos])
   // backward of the block (bf16 only; one output tile per workgroup):
   EPI_STORE = 6,       // out[m, n] = C (+ bias), bf16
-  EPI_STORE_F32 = 7,   // out[m, n] = C, fp32 (weight gradients)
-  EPI_GELU_BWD = 8,    // out[m, n] = C * gelu'(res[m, n]) (res: the up projection's pre-activation, ld = ldo)
-  EPI_SWIGLU_BWD = 9,  // N = f; res = [gate | up] pre-activations [M, 2f] (ld = ldo = 2f):
-                       // out[m, n] = C * up * silu'(gate), out[m, f + n] = C * silu(gate)
+  EPI_GELU_BWD = 7,    // out[m, n] = C * gelu'(res[m, n]) (res: the up projection's pre-activation, ld = ldo);
+                       // x[m, n] = gelu(res[m, n]), ld = N (x nullable)
+  EPI_SWIGLU_BWD = 8,  // N = f; res = [gate | up] pre-activations [M, 2f] (ld = ldo = 2f):
+                       // out[m, n] = C * up * silu'(gate), out[m, f + n] = C * silu(gate);
+                       // x[m, n] = silu(gate) * up, ld = N (x nullable)
 };
 
 // Workspace of a launch that splits K over workgroups (more than 16 rows):
@@ -239,23 +240,38 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // GemmArgs::tile_hint for two forward projections of M rows and reduction K,
 // N1 and N2 wide, run side by side.
 int gemm_pair_tile_hint(int M, int N1, int N2, int K);
+// Polls of a flag before a wait for a partial sum gives up (DSF_SK_SPIN_LIMIT).
+int spin_limit();
+
+// ---- weight gradients (kernels_wgrad.hip) ----
+// Scratch of a launch: partial tiles (16-byte aligned), column sums, flags
+// that do not hold the launch's epoch, and the call's status word.
+constexpr int kWgradMaxSplit = 8;  // token slices per weight gradient, at most
+struct WgradScratch {
+  float* part; size_t part_bytes;
+  float* bias_part; size_t bias_bytes;
+  uint32_t* flags; int nflags;
+  uint32_t* status;
+  uint32_t epoch;
+};
+// out[M, N] (fp32, dense) = sum over T rows of P[t, m] Q[t, n], P [T, ldp] and
+// Q [T, ldq] bf16; bias (nullable): out's row sums of P. 16-byte aligned rows.
+hipError_t launch_wgrad(const void* p, int ldp, int M, const void* q, int ldq, int N, int T, float* out, float* bias,
+                        const WgradScratch& ws, hipStream_t s);
 
 // ---- backward of the routed layer (kernels_bwd.hip) ----
-// out[c][r] = op(in[r][c]) (op 0 copy, 1 GELU, 2 SiLU(in[r][c]) * in[r][C + c]);
-// out's leading dimension ldo >= R, columns R .. ldo - 1 written as zeros.
-hipError_t launch_transpose(int op, const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s);
-// out[c] = sum_r a[r][c] (x null) or sum_r a[r][c] (x[r][c] - mean[r]) rstd[r]
-// (mean nullable: 0), in a fixed order; partial: colsum_chunks(R) * C floats.
-int colsum_chunks(int R);
-hipError_t launch_colsum(const void* a, int R, int C, int lda, const void* x, const float* mean, const float* rstd,
-                         float* partial, float* out, hipStream_t s);
+// out[c][r] = in[r][c], bf16 [R, C] (leading dimension ldi) to [C, ldo], ldo >= R.
+hipError_t launch_transpose(const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s);
 // out[b kk + j] = (scores ? sigmoid(scores[b, idx]) : 1) * dy[b, idx[b kk + j]]
 hipError_t launch_gather_scale(const void* dy, int B, int T, int d, const int32_t* idx, int kk, const float* scores,
                                void* out, hipStream_t s);
 // LayerNorm (rms false) or RMSNorm adjoint of M rows: acc (fp32) = or += dx;
-// sum_out = add + dx (both nullable); mean/rstd [M] of each row kept.
+// sum_out = add + dx (both nullable). dw, db [d] (nullable, fp32): the
+// gradients of gain and bias; partial: norm_bwd_partials(M) * 2 d floats.
+int norm_bwd_partials(int M);
 hipError_t launch_norm_bwd(bool rms, const void* x, const void* dyn, const void* w, int M, int d, float eps, float* acc,
-                           bool accumulate, const void* add, void* sum_out, float* mean, float* rstd, hipStream_t s);
+                           bool accumulate, const void* add, void* sum_out, float* dw, float* db, float* partial,
+                           hipStream_t s);
 // dqkv [B kk, (Hq + 2 Hkv) hd] (bf16) from head-major fp32 dq, dk, dv; RoPE turned back.
 hipError_t launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* table, const int32_t* idx,
                            int B, int kk, int T, int Hq, int Hkv, int hd, int R, void* out, hipStream_t s);

@@ -25,38 +25,28 @@ namespace dsf {
 
 // ----------------------------------------------------------- transposes
 
-// out[c][r] = op(in[r][c]) for r < R, c < C; out has leading dimension ldo
-// >= R and its columns R .. ldo-1 are written as zeros (so that a token
-// count padded to a multiple of 64 can be a GEMM reduction). op: 0 copy,
-// 1 GELU, 2 SiLU(in[r][c]) * in[r][C + c] (SwiGLU of a [R, 2C] gate|up row).
-template <int OP>
+// out[c][r] = in[r][c] for r < R, c < C; out has leading dimension ldo >= R
+// and its columns R .. ldo-1 are written as zeros. (The weights, which the
+// adjoint GEMMs read along their other dimension.)
 __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in, int R, int C, int ldi,
                                                         uint16_t* __restrict__ out, int ldo) {
-  __shared__ float tile[64][65];
+  __shared__ uint16_t tile[64][66];
   const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   for (int rr = ty; rr < 64; rr += 4) {
     const int r = r0 + rr, c = c0 + tx;
-    float v = 0.f;
-    if (r < R && c < C) {
-      const int64_t o = int64_t(r) * ldi + c;
-      v = bf2f(in[o]);
-      if constexpr (OP == 1) v = gelu_bf16(v);
-      if constexpr (OP == 2) v = silu_bf16(v) * bf2f(in[o + C]);
-    }
-    tile[rr][tx] = v;
+    tile[rr][tx] = r < R && c < C ? in[int64_t(r) * ldi + c] : uint16_t(0);
   }
   __syncthreads();
   for (int cc = ty; cc < 64; cc += 4) {
     const int c = c0 + cc, r = r0 + tx;
-    if (c < C && r < ldo) out[int64_t(c) * ldo + r] = f2bf(tile[tx][cc]);
+    if (c < C && r < ldo) out[int64_t(c) * ldo + r] = tile[tx][cc];
   }
 }
 
 // The same with 16-byte accesses on both sides (C, ldi and ldo multiples of
 // 8, 16-byte aligned bases): a thread loads 8 columns of an input row and
 // stores 8 rows of an output row.
-template <int OP>
 __global__ __launch_bounds__(256) void transpose_vec_kernel(const uint16_t* __restrict__ in, int R, int C, int ldi,
                                                             uint16_t* __restrict__ out, int ldo) {
   __shared__ float tile[64][65];
@@ -67,23 +57,7 @@ __global__ __launch_bounds__(256) void transpose_vec_kernel(const uint16_t* __re
     const int rr = q + 32 * i, r = r0 + rr, c = c0 + 8 * v;
     float x[8];
     if (r < R && c < C) {
-      const int64_t o = int64_t(r) * ldi + c;
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(in + o);
-      u32x4 up{};
-      if constexpr (OP == 2) up = *reinterpret_cast<const u32x4*>(in + o + C);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[2 * e] = __uint_as_float(raw[e] << 16);
-        x[2 * e + 1] = __uint_as_float(raw[e] & 0xffff0000u);
-        if constexpr (OP == 1) {
-          x[2 * e] = gelu_bf16(x[2 * e]);
-          x[2 * e + 1] = gelu_bf16(x[2 * e + 1]);
-        }
-        if constexpr (OP == 2) {
-          x[2 * e] = silu_bf16(x[2 * e]) * __uint_as_float(up[e] << 16);
-          x[2 * e + 1] = silu_bf16(x[2 * e + 1]) * __uint_as_float(up[e] & 0xffff0000u);
-        }
-      }
+      load_vec(in + int64_t(r) * ldi + c, x);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = 0.f;
@@ -96,155 +70,23 @@ __global__ __launch_bounds__(256) void transpose_vec_kernel(const uint16_t* __re
   for (int i = 0; i < 2; ++i) {
     const int cc = q + 32 * i, c = c0 + cc, r = r0 + 8 * v;
     if (c < C && r < ldo) {
-      u32x4 pk;
+      float x[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        pk[e] = uint32_t(f2bf(tile[8 * v + 2 * e][cc])) | (uint32_t(f2bf(tile[8 * v + 2 * e + 1][cc])) << 16);
-      *reinterpret_cast<u32x4*>(out + int64_t(c) * ldo + r) = pk;
+      for (int e = 0; e < 8; ++e) x[e] = tile[8 * v + e][cc];
+      store_vec(out + int64_t(c) * ldo + r, x);
     }
   }
 }
 
-hipError_t launch_transpose(int op, const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s) {
+hipError_t launch_transpose(const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s) {
   if (R <= 0 || C <= 0) return hipSuccess;
   const dim3 grid((C + 63) / 64, (ldo + 63) / 64);
   const auto* i = (const uint16_t*)in;
   auto* o = (uint16_t*)out;
   const bool vec = C % 8 == 0 && ldi % 8 == 0 && ldo % 8 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(out) % 16 == 0;
-  if (vec) {
-    if (op == 0) transpose_vec_kernel<0><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-    else if (op == 1) transpose_vec_kernel<1><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-    else transpose_vec_kernel<2><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-  } else {
-    if (op == 0) transpose_kernel<0><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-    else if (op == 1) transpose_kernel<1><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-    else transpose_kernel<2><<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-  }
-  return hipGetLastError();
-}
-
-// ----------------------------------------------------------- column sums
-
-// partial[chunk][c] = sum over the kColRows rows of chunk of a[r][c]
-// (xhat == null) or a[r][c] * (x[r][c] - mean[r]) * rstd[r]; then out[c] =
-// sum over chunks in order. With 16-byte rows (C, lda multiples of 8, aligned
-// bases) a workgroup is 32 column vectors of 8 columns by 8 row lanes: row
-// lane j adds rows j, j + 8, ... of the chunk in order, then the 8 lane sums
-// are added in lane order. Otherwise a thread adds one column's rows in
-// order. Every order is fixed by the shape.
-constexpr int kColRows = 256;
-constexpr int kColLanes = 8;
-
-__global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const uint16_t* __restrict__ a, int R, int C,
-                                                                 int lda, const uint16_t* __restrict__ x,
-                                                                 const float* __restrict__ mean,
-                                                                 const float* __restrict__ rstd,
-                                                                 float* __restrict__ partial) {
-  __shared__ float red[kColLanes][32 * 8 + 4];
-  const int cv = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const int c0 = (blockIdx.x * 32 + cv) * 8;
-  const int r0 = blockIdx.y * kColRows, r1 = min(R, r0 + kColRows);
-  float s[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) s[e] = 0.f;
-  if (c0 < C) {
-    constexpr int U = 4;  // rows of this lane loaded before they are added
-    for (int rb = r0 + rl; rb < r1; rb += U * kColLanes) {
-      u32x4 va[U], vx[U];
-      float mu[U], rs[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = rb + u * kColLanes;
-        if (r < r1) {
-          va[u] = *reinterpret_cast<const u32x4*>(a + int64_t(r) * lda + c0);
-          if (x) {
-            vx[u] = *reinterpret_cast<const u32x4*>(x + int64_t(r) * lda + c0);
-            mu[u] = mean ? mean[r] : 0.f;
-            rs[u] = rstd[r];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (rb + u * kColLanes < r1) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const uint32_t wa = va[u][e >> 1];
-            float v = __uint_as_float((e & 1) ? (wa & 0xffff0000u) : (wa << 16));
-            if (x) {
-              const uint32_t wx = vx[u][e >> 1];
-              v *= (__uint_as_float((e & 1) ? (wx & 0xffff0000u) : (wx << 16)) - mu[u]) * rs[u];
-            }
-            s[e] += v;
-          }
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[rl][cv * 8 + e] = s[e];
-  __syncthreads();
-  // thread t sums column t of the workgroup's 256 over the lanes in order
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c < C) {
-    float t = 0.f;
-#pragma unroll
-    for (int l = 0; l < kColLanes; ++l) t += red[l][threadIdx.x];
-    partial[int64_t(blockIdx.y) * C + c] = t;
-  }
-}
-
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const uint16_t* __restrict__ a, int R, int C, int lda,
-                                                             const uint16_t* __restrict__ x,
-                                                             const float* __restrict__ mean,
-                                                             const float* __restrict__ rstd,
-                                                             float* __restrict__ partial) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  const int r0 = blockIdx.y * kColRows, r1 = min(R, r0 + kColRows);
-  if (c >= C) return;
-  float s = 0.f;
-  for (int r = r0; r < r1; ++r) {
-    float v = bf2f(a[int64_t(r) * lda + c]);
-    if (x) v *= (bf2f(x[int64_t(r) * lda + c]) - (mean ? mean[r] : 0.f)) * rstd[r];
-    s += v;
-  }
-  partial[int64_t(blockIdx.y) * C + c] = s;
-}
-
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ partial, int chunks, int C,
-                                                           float* __restrict__ out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= C) return;
-  float s = 0.f;
-  constexpr int U = 8;  // partials loaded before they are added (in order)
-  for (int k = 0; k < chunks; k += U) {
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k + u < chunks) v[u] = partial[int64_t(k + u) * C + c];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k + u < chunks) s += v[u];
-  }
-  out[c] = s;
-}
-
-int colsum_chunks(int R) { return (R + kColRows - 1) / kColRows; }
-
-hipError_t launch_colsum(const void* a, int R, int C, int lda, const void* x, const float* mean, const float* rstd,
-                         float* partial, float* out, hipStream_t s) {
-  if (C <= 0) return hipSuccess;
-  const int chunks = colsum_chunks(R);
-  const bool vec = C % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(a) % 16 == 0 &&
-                   (!x || reinterpret_cast<uintptr_t>(x) % 16 == 0);
-  if (chunks > 0) {
-    const uint16_t *ap = (const uint16_t*)a, *xp = (const uint16_t*)x;
-    const dim3 grid((C + 255) / 256, chunks);
-    if (vec) colsum_partial_vec_kernel<<<grid, 256, 0, s>>>(ap, R, C, lda, xp, mean, rstd, partial);
-    else colsum_partial_kernel<<<grid, 256, 0, s>>>(ap, R, C, lda, xp, mean, rstd, partial);
-  }
-  colsum_final_kernel<<<(C + 255) / 256, 256, 0, s>>>(partial, chunks, C, out);
+  if (vec) transpose_vec_kernel<<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
+  else transpose_kernel<<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
   return hipGetLastError();
 }
 
@@ -283,100 +125,250 @@ hipError_t launch_gather_scale(const void* dy, int B, int T, int d, const int32_
 
 // ------------------------------------------------------ norm adjoints
 
-// One wavefront per row m of x [M, d] (the norm's input) and dyn [M, d] (the
-// gradient at the norm's output), gain w [d]:
+// Row m of x [M, d] (the norm's input) and dyn [M, d] (the gradient at the
+// norm's output), gain w [d]:
 //   LayerNorm: xhat = (x - mean) * rstd, g = dyn * w,
 //              dx = rstd * (g - mean(g) - xhat * mean(g * xhat));
 //   RMSNorm:   xhat = x * rstd, dx = rstd * (g - xhat * mean(g * xhat)).
 // dx goes to acc (fp32 [M, d]): acc = dx, or acc += dx with accumulate. With
 // add and sum_out (both bf16 [M, d]): sum_out = add + dx (Qwen's
-// d(attention output) = d(delta) + d(h)). mean/rstd of each row are kept for
-// the gain gradient (a column sum over rows).
-template <bool RMS>
+// d(attention output) = d(delta) + d(h)).
+//
+// With partial, the gradients of gain (sum of dyn * xhat over the rows) and
+// bias (sum of dyn) ride along: a workgroup takes `rows` consecutive rows and
+// keeps the sums of its columns in registers, partial[workgroup][0, d) for
+// the gain, [d, 2d) for the bias, which norm_sums_kernel adds. Column sums of
+// their own read x and dyn once more and ended in a kernel of a few
+// workgroups. Every order is fixed by the shape.
+//
+// A lane holds VC vectors of 8 columns of a row, the next row's on the way
+// while it works on one. BLOCK false: one wavefront per row (d <= 512 VC),
+// wave w taking rows w, w + 4, ...; true: the workgroup's four waves share a
+// row (d <= 2048 VC), so that the sums of 8192 columns still fit registers.
+constexpr int kNormBwdChunks = 512;  // workgroups, at most
+constexpr int kNormBwdRows = 16;     // rows per workgroup, at least
+
+static int norm_bwd_rows(int M) { return std::max(kNormBwdRows, (M + kNormBwdChunks - 1) / kNormBwdChunks); }
+int norm_bwd_partials(int M) { return (M + norm_bwd_rows(M) - 1) / norm_bwd_rows(M); }
+
+template <bool RMS, int VC, bool BLOCK>
 __global__ __launch_bounds__(256) void norm_bwd_kernel(const uint16_t* __restrict__ x,
                                                        const uint16_t* __restrict__ dyn,
                                                        const uint16_t* __restrict__ w, int M, int d, float eps,
                                                        float* __restrict__ acc, int accumulate,
                                                        const uint16_t* __restrict__ add, uint16_t* __restrict__ sum_out,
-                                                       float* __restrict__ mean_out, float* __restrict__ rstd_out) {
-  const int lane = threadIdx.x & 63;
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (m >= M) return;
-  const uint16_t* xr = x + int64_t(m) * d;
-  const uint16_t* gr = dyn + int64_t(m) * d;
-  float s1 = 0.f, s2 = 0.f;
-  for (int c = lane * 8; c < d; c += 512) {
-    float v[8];
-    load_vec(xr + c, v);
+                                                       int rows, float* __restrict__ partial) {
+  constexpr int kStep = BLOCK ? 1 : 4;
+  __shared__ float red[BLOCK ? 16 : 4 * VC * 512];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int v0 = BLOCK ? int(threadIdx.x) : lane;  // this lane's vectors: v0 + kVecStep c
+  constexpr int kVecStep = BLOCK ? 256 : 64;
+  // the sum over a row, in every lane that holds a part of it; slot: the
+  // row's place among its sums (the four waves' parts are read behind one
+  // barrier, and a slot is written again two barriers later)
+  auto row_sum = [&](float v, int slot) {
+    v = wave_sum_fast(v);
+    if constexpr (BLOCK) {
+      if (lane == 0) red[slot * 4 + wave] = v;
+      __syncthreads();
+      v = (red[slot * 4] + red[slot * 4 + 1]) + (red[slot * 4 + 2] + red[slot * 4 + 3]);
+    }
+    return v;
+  };
+  const int m0 = int(blockIdx.x) * rows + (BLOCK ? 0 : wave), m1 = min(M, (int(blockIdx.x) + 1) * rows);
+  const u32x4 zero{0u, 0u, 0u, 0u};
+  auto load_row = [&](const uint16_t* src, u32x4(&r)[VC]) {
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      const int col = (v0 + kVecStep * c) * 8;
+      r[c] = col < d ? *reinterpret_cast<const u32x4*>(src + col) : zero;
+    }
+  };
+  auto unpack = [](const u32x4& r, float(&v)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(r[i] << 16);
+      v[2 * i + 1] = __uint_as_float(r[i] & 0xffff0000u);
+    }
+  };
+  float gw[VC][8], gb[RMS ? 1 : VC][8];
+#pragma unroll
+  for (int c = 0; c < VC; ++c)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      s1 += v[i];
-      s2 += v[i] * v[i];
+      gw[c][i] = 0.f;
+      if constexpr (!RMS) gb[c][i] = 0.f;
+    }
+  u32x4 wv[VC], xv[VC], gv[VC];
+  load_row(w, wv);
+  if (m0 < m1) {
+    load_row(x + int64_t(m0) * d, xv);
+    load_row(dyn + int64_t(m0) * d, gv);
+  }
+  for (int m = m0; m < m1; m += kStep) {
+    u32x4 xn[VC], gn[VC];
+    const int mn = min(m + kStep, M - 1);  // (the last row's successor is loaded but not used)
+    load_row(x + int64_t(mn) * d, xn);
+    load_row(dyn + int64_t(mn) * d, gn);
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      float v[8];
+      unpack(xv[c], v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        s1 += v[i];
+        s2 += v[i] * v[i];
+      }
+    }
+    if constexpr (!RMS) s1 = row_sum(s1, 0);
+    s2 = row_sum(s2, 1);
+    const float mean = RMS ? 0.f : s1 / float(d);
+    const float var = RMS ? s2 / float(d) : fmaxf(s2 / float(d) - mean * mean, 0.f);
+    const float rstd = 1.f / sqrtf(var + eps);
+    float sg = 0.f, sgx = 0.f;
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      float v[8], g[8], ww[8];
+      unpack(xv[c], v);
+      unpack(gv[c], g);
+      unpack(wv[c], ww);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {  // columns past d: g = 0
+        const float gi = g[i] * ww[i], xh = (v[i] - mean) * rstd;
+        sg += gi;
+        sgx += gi * xh;
+        gw[c][i] += g[i] * xh;
+        if constexpr (!RMS) gb[c][i] += g[i];
+      }
+    }
+    if constexpr (!RMS) sg = row_sum(sg, 2) / float(d);
+    sgx = row_sum(sgx, 3) / float(d);
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      const int col = (v0 + kVecStep * c) * 8;
+      if (col >= d) continue;
+      float v[8], g[8], ww[8], dx[8];
+      unpack(xv[c], v);
+      unpack(gv[c], g);
+      unpack(wv[c], ww);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float xh = (v[i] - mean) * rstd;
+        dx[i] = rstd * (g[i] * ww[i] - (RMS ? 0.f : sg) - xh * sgx);
+      }
+      f32x4* ar = reinterpret_cast<f32x4*>(acc + int64_t(m) * d + col);
+      f32x4 o0{dx[0], dx[1], dx[2], dx[3]}, o1{dx[4], dx[5], dx[6], dx[7]};
+      if (accumulate) {
+        o0 += ar[0];
+        o1 += ar[1];
+      }
+      ar[0] = o0;
+      ar[1] = o1;
+      if (sum_out) {
+        float a[8];
+        load_vec(add + int64_t(m) * d + col, a);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] += dx[i];
+        store_vec(sum_out + int64_t(m) * d + col, a);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      xv[c] = xn[c];
+      gv[c] = gn[c];
     }
   }
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
-  const float mean = RMS ? 0.f : s1 / float(d);
-  const float var = RMS ? s2 / float(d) : fmaxf(s2 / float(d) - mean * mean, 0.f);
-  const float rstd = 1.f / sqrtf(var + eps);
-  float sg = 0.f, sgx = 0.f;
-  for (int c = lane * 8; c < d; c += 512) {
-    float v[8], g[8], wv[8];
-    load_vec(xr + c, v);
-    load_vec(gr + c, g);
-    load_vec(w + c, wv);
+  if (!partial) return;
+  float* dst = partial + int64_t(blockIdx.x) * 2 * d;
+  auto put = [&](const float(*g)[8], float* to) {
+    if constexpr (BLOCK) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float gi = g[i] * wv[i];
-      sg += gi;
-      sgx += gi * (v[i] - mean) * rstd;
-    }
-  }
-  sg = wave_sum(sg) / float(d);
-  sgx = wave_sum(sgx) / float(d);
-  for (int c = lane * 8; c < d; c += 512) {
-    float v[8], g[8], wv[8], dx[8];
-    load_vec(xr + c, v);
-    load_vec(gr + c, g);
-    load_vec(w + c, wv);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float xh = (v[i] - mean) * rstd;
-      dx[i] = rstd * (g[i] * wv[i] - (RMS ? 0.f : sg) - xh * sgx);
-    }
-    float* ar = acc + int64_t(m) * d + c;
-    if (accumulate) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ar[i] += dx[i];
+      for (int c = 0; c < VC; ++c) {
+        const int col = (v0 + kVecStep * c) * 8;
+        if (col >= d) continue;
+        f32x4* o = reinterpret_cast<f32x4*>(to + col);
+        o[0] = f32x4{g[c][0], g[c][1], g[c][2], g[c][3]};
+        o[1] = f32x4{g[c][4], g[c][5], g[c][6], g[c][7]};
+      }
     } else {
+      __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ar[i] = dx[i];
+      for (int c = 0; c < VC; ++c) {
+        f32x4* o = reinterpret_cast<f32x4*>(red + wave * VC * 512 + (lane + 64 * c) * 8);
+        o[0] = f32x4{g[c][0], g[c][1], g[c][2], g[c][3]};
+        o[1] = f32x4{g[c][4], g[c][5], g[c][6], g[c][7]};
+      }
+      __syncthreads();
+      for (int col = threadIdx.x; col < d; col += 256)
+        to[col] = (red[col] + red[VC * 512 + col]) + (red[2 * VC * 512 + col] + red[3 * VC * 512 + col]);
     }
-    if (sum_out) {
-      float a[8];
-      load_vec(add + int64_t(m) * d + c, a);
+  };
+  put(gw, dst);
+  if constexpr (!RMS) put(gb, dst + d);
+}
+
+// out0[c] = sum over chunks of partial[chunk][c], out1[c] of [chunk][d + c]
+// (either nullable): 16 columns by 16 chunk lanes per workgroup, lane j adding
+// chunks j, j + 16, ... in order, then the lanes in order.
+__global__ __launch_bounds__(256) void norm_sums_kernel(const float* __restrict__ partial, int chunks, int d,
+                                                        float* __restrict__ out0, float* __restrict__ out1) {
+  __shared__ float red[16][17];
+  const int cl = threadIdx.x & 15, kl = threadIdx.x >> 4, c = blockIdx.x * 16 + cl;
+  float s = 0.f;
+  if (c < 2 * d) {
+    constexpr int U = 8;  // partials loaded before they are added
+    for (int k = kl; k < chunks; k += 16 * U) {
+      float v[U];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] += dx[i];
-      store_vec(sum_out + int64_t(m) * d + c, a);
+      for (int u = 0; u < U; ++u) v[u] = k + 16 * u < chunks ? partial[int64_t(k + 16 * u) * 2 * d + c] : 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += v[u];
     }
   }
-  if (lane == 0) {
-    mean_out[m] = mean;
-    rstd_out[m] = rstd;
-  }
+  red[kl][cl] = s;
+  __syncthreads();
+  if (kl != 0 || c >= 2 * d) return;
+#pragma unroll
+  for (int j = 1; j < 16; ++j) s += red[j][cl];
+  float* out = c < d ? out0 : out1;
+  if (out) out[c < d ? c : c - d] = s;
+}
+
+template <int VC, bool BLOCK>
+static void launch_norm_bwd_t(bool rms, const uint16_t* x, const uint16_t* dyn, const uint16_t* w, int M, int d,
+                              float eps, float* acc, bool accumulate, const uint16_t* add, uint16_t* sum_out,
+                              float* partial, hipStream_t s) {
+  const int rows = norm_bwd_rows(M), grid = norm_bwd_partials(M);
+  if (rms)
+    norm_bwd_kernel<true, VC, BLOCK><<<grid, 256, 0, s>>>(x, dyn, w, M, d, eps, acc, accumulate, add, sum_out, rows,
+                                                          partial);
+  else
+    norm_bwd_kernel<false, VC, BLOCK><<<grid, 256, 0, s>>>(x, dyn, w, M, d, eps, acc, accumulate, add, sum_out, rows,
+                                                           partial);
 }
 
 hipError_t launch_norm_bwd(bool rms, const void* x, const void* dyn, const void* w, int M, int d, float eps, float* acc,
-                           bool accumulate, const void* add, void* sum_out, float* mean, float* rstd, hipStream_t s) {
+                           bool accumulate, const void* add, void* sum_out, float* dw, float* db, float* partial,
+                           hipStream_t s) {
   if (M == 0) return hipSuccess;
-  const dim3 grid((M + 3) / 4);
   const auto *xx = (const uint16_t*)x, *g = (const uint16_t*)dyn, *ww = (const uint16_t*)w, *ad = (const uint16_t*)add;
-  if (rms)
-    norm_bwd_kernel<true><<<grid, 256, 0, s>>>(xx, g, ww, M, d, eps, acc, accumulate, ad, (uint16_t*)sum_out, mean,
-                                               rstd);
-  else
-    norm_bwd_kernel<false><<<grid, 256, 0, s>>>(xx, g, ww, M, d, eps, acc, accumulate, ad, (uint16_t*)sum_out,
-                                                mean, rstd);
+  auto* so = (uint16_t*)sum_out;
+  float* part = dw || db ? partial : nullptr;
+  auto run = [&](auto vc, auto block) {
+    launch_norm_bwd_t<decltype(vc)::value, decltype(block)::value>(rms, xx, g, ww, M, d, eps, acc, accumulate, ad, so,
+                                                                   part, s);
+  };
+  using std::integral_constant;
+  if (d <= 512) run(integral_constant<int, 1>{}, std::false_type{});
+  else if (d <= 1024) run(integral_constant<int, 2>{}, std::false_type{});
+  else if (d <= 2048) run(integral_constant<int, 4>{}, std::false_type{});
+  else if (d <= 4096) run(integral_constant<int, 2>{}, std::true_type{});
+  else run(integral_constant<int, 4>{}, std::true_type{});  // d <= 8192
+  // RMSNorm has no bias: its half of the partials is not written and not read
+  if (part)
+    norm_sums_kernel<<<((rms ? 1 : 2) * d + 15) / 16, 256, 0, s>>>(part, norm_bwd_partials(M), d, dw,
+                                                                  rms ? nullptr : db);
   return hipGetLastError();
 }
 

@@ -221,18 +221,6 @@ __device__ __forceinline__ void gemm_epilogue_rows(const GemmArgs& g, const floa
     }
     return;
   }
-  if constexpr (EPI == EPI_STORE_F32) {
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      if (!live[q]) continue;
-      const int m = m0 + rr0 + q * RSTEP;
-      const float* row = stage + (rr0 + q * RSTEP) * LD;
-      float* dst = (float*)g.out + int64_t(m) * g.ldo + n;
-      store_vec(dst, row + cc);
-      store_vec(dst + 4, row + cc + 4);
-    }
-    return;
-  }
   if constexpr (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) {
     // gradient at the activation's input from the gradient at its output (C)
     // and the forward pre-activation(s) in res
@@ -256,6 +244,11 @@ __device__ __forceinline__ void gemm_epilogue_rows(const GemmArgs& g, const floa
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = row[cc + i] * gelu_grad_bf16(a[i]);
         store8(dst, v);
+        if (g.x) {  // the activation itself, for the down projection's weight gradient
+#pragma unroll
+          for (int i = 0; i < 8; ++i) a[i] = gelu_bf16(a[i]);
+          store8((T*)g.x + int64_t(m) * g.N + n, a);
+        }
       } else {
         float up[8], w[8];
         unpack8(rb[q], up);
@@ -266,6 +259,11 @@ __device__ __forceinline__ void gemm_epilogue_rows(const GemmArgs& g, const floa
         }
         store8(dst, v);
         store8(dst + g.f, w);
+        if (g.x) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) a[i] = silu_bf16(a[i]) * up[i];
+          store8((T*)g.x + int64_t(m) * g.N + n, a);
+        }
       }
     }
     return;
@@ -1252,7 +1250,7 @@ int gemm_flag_count() { return kSkMaxSlots; }
 // by a short sleep). DSF_SK_SPIN_LIMIT, read at every launch, overrides it:
 // a test sets 0 so that every finisher with a predecessor gives up at once
 // and the status report can be checked without any wait being broken.
-static int spin_limit() {
+int spin_limit() {
   const char* e = getenv("DSF_SK_SPIN_LIMIT");
   if (!e || !*e) return 1 << 22;
   const long v = strtol(e, nullptr, 10);
@@ -1314,11 +1312,7 @@ static int device_cus() {
 struct Schedule {
   int px, split;
 };
-// underfilled: also split a grid of at most half as many tiles as slots
-// whose reduction is long (the backward's weight gradients: few output
-// tiles, a reduction over every kept token), every workgroup taking an equal
-// piece of all the tiles' k-iterations.
-static Schedule choose_schedule(int nt, int nk, int slots, bool underfilled = false) {
+static Schedule choose_schedule(int nt, int nk, int slots) {
   const int px = slots / kXcds;
   if (px < 1) return {0, 0};
   const int mode = schedule_override();
@@ -1328,7 +1322,6 @@ static Schedule choose_schedule(int nt, int nk, int slots, bool underfilled = fa
   const int64_t P = int64_t(px) * kXcds;
   const int64_t last = nt % P;
   if (nk >= kSkMinK) {
-    if (underfilled && 2 * int64_t(nt) <= P && int64_t(nt) * nk >= P * kSkMinIters) return {px, 1};
     if (nt <= P || last == 0 || 4 * last > P) return {0, 0};
     if (int64_t(nt) * nk < P * kSkMinIters) return {0, 0};
     return {px, 1};
@@ -1623,10 +1616,6 @@ int gemm_pair_tile_hint(int M, int N1, int N2, int K) {
              : 1;
 }
 
-// The backward's weight gradients (EPI_STORE_F32) take the large tiles from
-// this many of them: smaller grids go to the stream-K grid of small tiles.
-constexpr int kLargeMinTiles = 320;
-
 template <int EPI>
 static bool use_large_tiles(const GemmArgs& g) {
   if (EPI == EPI_SWIGLU && g.f % (TileLarge::BN / 2) != 0) return false;
@@ -1636,7 +1625,6 @@ static bool use_large_tiles(const GemmArgs& g) {
   if (g.tile_hint) return g.tile_hint == 2;
   const int cols = EPI == EPI_SWIGLU ? 2 * g.f : g.N;
   const int64_t nt = tile_count<TileLarge>(g.M, cols);
-  if (EPI == EPI_STORE_F32) return nt >= kLargeMinTiles;
   const bool split = EPI < EPI_STORE && g.part && g.flags;
   return large_tiles_win(tile_count<TileSmall>(g.M, cols), nt, g.K / 64, split && EPI != EPI_SWIGLU, split,
                          EPI == EPI_SWIGLU);
@@ -1656,9 +1644,8 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
     // Persistent and stream-K grids only with small tiles: the large tiles'
     // grids run many rounds (a short last round costs a few percent), and the
     // stream-K kernel's partial-sum hand-over does not fit their register
-    // budget beside 128 accumulators per lane. Among the backward kinds only
-    // the weight gradients (fp32 output) take them.
-    if constexpr (BM == TileSmall::BM && BN == TileSmall::BN && EPI != EPI_STORE_F32) {
+    // budget beside 128 accumulators per lane.
+    if constexpr (BM == TileSmall::BM && BN == TileSmall::BN) {
       using TD = TileDeep;
       auto fn = gemm_bf16_dma_kernel<EPI, TD::BM, TD::BN, TD::WM, TD::WN, TD::NS, TD::BK>;
       const int nt = ntn * ga.ntm, cus = resident_slots<std::integral_constant<int, 96 + EPI>>((const void*)fn, Cfg::kThreads);
@@ -1681,12 +1668,12 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
         return;
       }
     }
-    if constexpr (BM == TileSmall::BM && BN == TileSmall::BN && (EPI < EPI_STORE || EPI == EPI_STORE_F32)) {
+    if constexpr (BM == TileSmall::BM && BN == TileSmall::BN && EPI < EPI_STORE) {
       if (g.part && g.flags) {
         auto fn = gemm_bf16_sk_kernel<EPI, BM, BN, WM, WN, NS, BK>;
         const int slots = std::min(kPartSlots, resident_slots<std::integral_constant<int, EPI * 2 + (BM > 128)>>(
                                                    (const void*)fn, Cfg::kThreads));
-        const Schedule sch = choose_schedule(ntn * ga.ntm, g.K / BK, slots, EPI == EPI_STORE_F32);
+        const Schedule sch = choose_schedule(ntn * ga.ntm, g.K / BK, slots);
         ga.px = sch.px;
         ga.split = sch.split;
         ga.spin_limit = spin_limit();
@@ -1814,7 +1801,6 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     case EPI_RESID_SCATTER: launch_gemm_t<EPI_RESID_SCATTER>(g, s); break;
     case EPI_RESID_SCATTER_GATE: launch_gemm_t<EPI_RESID_SCATTER_GATE>(g, s); break;
     case EPI_STORE: launch_gemm_t<EPI_STORE>(g, s); break;
-    case EPI_STORE_F32: launch_gemm_t<EPI_STORE_F32>(g, s); break;
     case EPI_GELU_BWD: launch_gemm_t<EPI_GELU_BWD>(g, s); break;
     case EPI_SWIGLU_BWD: launch_gemm_t<EPI_SWIGLU_BWD>(g, s); break;
     default: return hipErrorInvalidValue;
