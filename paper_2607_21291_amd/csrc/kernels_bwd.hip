@@ -550,36 +550,49 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
   return r;
 }
 
-// Pass 1: one workgroup per (sequence, query head, 64-query block); wave w
-// owns queries q0 + 16 w .. + 15 (lane l: query 16 w + l % 16). Scores are
-// formed transposed (S^T = K Q^T, keys as MFMA rows), so a lane holds 16
-// scores of its own query per 64-key block. With P = exp(S scale - lse):
-// writes D = sum_c dout * o for pass 2, and dQ = scale * sum_keys dS K with
-// dS = P (dP - D), dP = dout V^T.
-template <int HD>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const uint16_t* __restrict__ Q,
+// Both passes are bound by their vector instructions per score (exponential,
+// difference, products, conversion) and by LDS reads, not by the matrix cores
+// (a fifth of the time). Scores enter the exponential as one fused
+// multiply-add in base 2, the causal test runs only in blocks that the
+// diagonal crosses, and the scale is left to the accumulators. With 16 queries
+// (keys) per wave every fragment read feeds one MFMA; G = 2 gives a wave two
+// groups of 16 that share the fragments: for head dimensions up to 64 (the
+// accumulators of 128 do not fit) where the larger blocks still give every CU
+// two workgroups (kAttnBwdWide). Blocks are launched longest first, all heads
+// of a block index together, so the short ones fill the end and, with heads in
+// multiples of 8, an XCD's L2 keeps its heads' tiles. 96 heads of 64, 1563
+// tokens: 100 -> 82 us (pass 1) and 170 -> 98 us (pass 2).
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kAttnBwdWide = 512;  // workgroups of 128 queries (keys) from which they are used
+
+// Pass 1: one workgroup per (sequence, query head, block of 64 G queries);
+// wave w owns queries q0 + 16 G w .. + 16 G - 1 (lane l: query l % 16 of each
+// group). Scores are formed transposed (S^T = K Q^T, keys as MFMA rows), so a
+// lane holds 16 scores of each of its queries per 64-key block. With
+// P = exp(S scale - lse): writes D = sum_c dout * o for pass 2, and
+// dQ = scale * sum_keys dS K with dS = P (dP - D), dP = dout V^T. Queries past
+// the end are columns of their own that are not stored.
+template <int HD, int G>
+__global__ __launch_bounds__(256, HD == 64 && G == 2 ? 3 : 1) void attn_bwd_dq_kernel(const uint16_t* __restrict__ Q,
                                                           const uint16_t* __restrict__ K,
                                                           const uint16_t* __restrict__ V,
                                                           const uint16_t* __restrict__ O,
                                                           const uint16_t* __restrict__ dO, int n, int Hq, int Hkv,
-                                                          const float* __restrict__ lse,
+                                                          int nbh, const float* __restrict__ lse,
                                                           float* __restrict__ dvec_out, float* __restrict__ dq_out) {
   using A = AttnTile<HD>;
   constexpr int NS = HD / 32, NC = HD / 16;
   __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes];  // stage: K tile, then V tile
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, grp = lane >> 4;
-  const int nqb = (n + kAB - 1) / kAB;
-  const int qb = blockIdx.x % nqb, bh = blockIdx.x / nqb;
+  const int nqb = (n + kAB * G - 1) / (kAB * G);
+  const int qb = nqb - 1 - int(blockIdx.x) / nbh, bh = int(blockIdx.x) % nbh;
   const int h = bh % Hq, b = bh / Hq, kvh = h / (Hq / Hkv);
-  const int q0 = qb * kAB;
-  const int query = q0 + 16 * wave + r16;
-  const bool qok = query < n;
-  const float scale = 1.f / sqrtf(float(HD));
+  const int qw = (qb * 4 + wave) * 16 * G;  // the wave's first query
+  const float scale = 1.f / sqrtf(float(HD)), scale2 = scale * kLog2e;
   const uint16_t* Kh = K + (int64_t(b) * Hkv + kvh) * n * HD;
   const uint16_t* Vh = V + (int64_t(b) * Hkv + kvh) * n * HD;
-  const int64_t orow = (int64_t(b) * n + (qok ? query : 0)) * (int64_t(Hq) * HD) + int64_t(h) * HD;
-  const int nkb = qb + 1;
+  const int nkb = min((n + kAB - 1) / kAB, (qb + 1) * G);
   auto issue = [&](int kt) {
     char* st = smem + (kt & 1) * 2 * A::kTileBytes;
     attn_tile_dma<HD>(Kh, HD, kt * kAB, n, st, wave, lane);
@@ -587,157 +600,181 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const uint16_t* __rest
   };
   issue(0);
 
-  // this lane's query as MFMA B operand: Q and dout rows, k slots 32 s + 8 grp ..
-  bf16x8 qf[NS], df[NS];
-  float dsum = 0.f;
+  // this lane's queries as MFMA B operand: Q and dout rows, k slots 32 s + 8 grp ..
+  bf16x8 qf[G][NS], df[G][NS];
+  float Dq[G], lq[G];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    u32x4 z = {0u, 0u, 0u, 0u};
-    u32x4 qv = z, dv = z, ov = z;
-    if (qok) {
-      qv = *reinterpret_cast<const u32x4*>(Q + ((int64_t(bh) * n + query) * HD) + 32 * s + 8 * grp);
-      dv = *reinterpret_cast<const u32x4*>(dO + orow + 32 * s + 8 * grp);
-      ov = *reinterpret_cast<const u32x4*>(O + orow + 32 * s + 8 * grp);
-    }
-    qf[s] = __builtin_bit_cast(bf16x8, qv);
-    df[s] = __builtin_bit_cast(bf16x8, dv);
+  for (int g = 0; g < G; ++g) {
+    const int query = qw + 16 * g + r16;
+    const bool qok = query < n;
+    const int64_t orow = (int64_t(b) * n + (qok ? query : 0)) * (int64_t(Hq) * HD) + int64_t(h) * HD;
+    float dsum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dsum += __uint_as_float(dv[i] << 16) * __uint_as_float(ov[i] << 16);
-      dsum += __uint_as_float(dv[i] & 0xffff0000u) * __uint_as_float(ov[i] & 0xffff0000u);
+    for (int s = 0; s < NS; ++s) {
+      u32x4 z = {0u, 0u, 0u, 0u};
+      u32x4 qv = z, dv = z, ov = z;
+      if (qok) {
+        qv = *reinterpret_cast<const u32x4*>(Q + ((int64_t(bh) * n + query) * HD) + 32 * s + 8 * grp);
+        dv = *reinterpret_cast<const u32x4*>(dO + orow + 32 * s + 8 * grp);
+        ov = *reinterpret_cast<const u32x4*>(O + orow + 32 * s + 8 * grp);
+      }
+      qf[g][s] = __builtin_bit_cast(bf16x8, qv);
+      df[g][s] = __builtin_bit_cast(bf16x8, dv);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        dsum += __uint_as_float(dv[i] << 16) * __uint_as_float(ov[i] << 16);
+        dsum += __uint_as_float(dv[i] & 0xffff0000u) * __uint_as_float(ov[i] & 0xffff0000u);
+      }
     }
+    Dq[g] = rows4_sum(dsum);
+    lq[g] = qok ? lse[int64_t(bh) * n + query] * kLog2e : 0.f;
+    if (qok && grp == 0) dvec_out[int64_t(bh) * n + query] = Dq[g];
   }
-  const float Dq = rows4_sum(dsum);
-  const float lq = qok ? lse[int64_t(bh) * n + query] : 0.f;
-  if (qok && grp == 0) dvec_out[int64_t(bh) * n + query] = Dq;
 
   // dQ^T[c][query] = scale * sum_keys K^T[c][key] dS^T[key][query]
   const AttnTrans<HD> tr(lane);
-  f32x4 acc[NC];
+  f32x4 acc[G][NC];
 #pragma unroll
-  for (int cb = 0; cb < NC; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int kt = 0; kt < nkb; ++kt) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's share of tile kt has landed
     __syncthreads();                                   // ... and every wave's; tile kt - 1 is retired
     if (kt + 1 < nkb) issue(kt + 1);
+    if (kt * kAB > qw + 16 * G - 1) continue;  // every key after the wave's queries
     const char* Kt = smem + (kt & 1) * 2 * A::kTileBytes;
     const char* Vt = Kt + A::kTileBytes;
-    float ds[4][4];
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
-      f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const bf16x8 kf = attn_row_frag<HD>(Kt, 16 * blk + r16, 4 * s + grp);
-        const bf16x8 vf = attn_row_frag<HD>(Vt, 16 * blk + r16, 4 * s + grp);
-        st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[s], st, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, df[s], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int key = kt * kAB + 16 * blk + 4 * grp + e;
-        const float p = (key <= query && key < n && qok) ? __expf(st[e] * scale - lq) : 0.f;
-        ds[blk][e] = p * (dp[e] - Dq) * scale;
-      }
-    }
-    bf16x8 dsb[2];
+    const bool edge = kt * kAB + kAB - 1 > qw;  // some of the block's keys come after some of the queries
+    bf16x8 dsb[G][2];
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      float v[8];
+      float ds[G][8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = ds[2 * s2][e];
-        v[4 + e] = ds[2 * s2 + 1][e];
+      for (int hb = 0; hb < 2; ++hb) {
+        const int blk = 2 * s2 + hb;
+        f32x4 st[G], dp[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) st[g] = dp[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const bf16x8 kf = attn_row_frag<HD>(Kt, 16 * blk + r16, 4 * s + grp);
+          const bf16x8 vf = attn_row_frag<HD>(Vt, 16 * blk + r16, 4 * s + grp);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            st[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[g][s], st[g], 0, 0, 0);
+            dp[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, df[g][s], dp[g], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float p = __builtin_amdgcn_exp2f(fmaf(st[g][e], scale2, -lq[g]));
+            if (edge && kt * kAB + 16 * blk + 4 * grp + e > qw + 16 * g + r16) p = 0.f;
+            ds[g][4 * hb + e] = p * (dp[g][e] - Dq[g]);
+          }
       }
-      dsb[s2] = pack8(v);
+#pragma unroll
+      for (int g = 0; g < G; ++g) dsb[g][s2] = pack8(ds[g]);
     }
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) {
       bf16x8 kt2[2];
       tr.read(Kt, cb, kt2);
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt2[s2], dsb[s2], acc[cb], 0, 0, 0);
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          acc[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt2[s2], dsb[g][s2], acc[g][cb], 0, 0, 0);
     }
   }
-  // lane holds dQ^T[16 cb + 4 grp + e][query]
-  if (qok) {
+  // lane holds dQ^T[16 cb + 4 grp + e][query] / scale
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int query = qw + 16 * g + r16;
+    if (query >= n) continue;
     float* dst = dq_out + (int64_t(bh) * n + query) * HD;
 #pragma unroll
-    for (int cb = 0; cb < NC; ++cb) *reinterpret_cast<f32x4*>(dst + 16 * cb + 4 * grp) = acc[cb];
+    for (int cb = 0; cb < NC; ++cb) *reinterpret_cast<f32x4*>(dst + 16 * cb + 4 * grp) = acc[g][cb] * scale;
   }
 }
 
-// Pass 2: one workgroup per (sequence, kv head, 64-key block); wave w owns
-// keys k0 + 16 w .. + 15 (lane l: key 16 w + l % 16). For every query head of
-// the kv head's group and every query block at or after the key block (one
-// work item each, in that order), scores are formed with keys as MFMA
-// columns (S = Q K^T), so a lane holds the probabilities of its own key, and
+// Pass 2: one workgroup per (sequence, kv head, block of 64 G keys); wave w
+// owns keys k0 + 16 G w .. + 16 G - 1 (lane l: key l % 16 of each group). For
+// every query head of the kv head's group and every query block that reaches
+// the key block (one work item each, in that order), scores are formed with
+// keys as MFMA columns (S = Q K^T), so a lane holds the probabilities of its
+// own keys, and
 //   dV^T[c][key] += sum_queries dout^T[c][query] P[query][key],
 //   dK^T[c][key] += scale * sum_queries Q^T[c][query] dS[query][key].
 // Each item's lse and D are loaded by wave 0 one item ahead and published in
-// LDS with the item's tiles.
-template <int HD>
+// LDS with the item's tiles. Queries past the end are zero rows of Q and dout
+// (finite probabilities times zeros); keys past it are not stored.
+template <int HD, int G>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ K,
                                                            const uint16_t* __restrict__ V,
                                                            const uint16_t* __restrict__ dO,
                                                            const float* __restrict__ lse,
                                                            const float* __restrict__ dvec, int n, int Hq, int Hkv,
-                                                           float* __restrict__ dk_out, float* __restrict__ dv_out) {
+                                                           int nbkv, float* __restrict__ dk_out,
+                                                           float* __restrict__ dv_out) {
   using A = AttnTile<HD>;
   constexpr int NS = HD / 32, NC = HD / 16;
   __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes];  // stage: Q tile, then dout tile
-  __shared__ float lse_s[2][kAB], dvec_s[2][kAB];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(16))) float lse_s[2][kAB], dvec_s[2][kAB];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, grp = lane >> 4;
-  const int nkb = (n + kAB - 1) / kAB;
-  const int kb = blockIdx.x % nkb, bkv = blockIdx.x / nkb;
+  const int kb = int(blockIdx.x) / nbkv, bkv = int(blockIdx.x) % nbkv;
   const int kvh = bkv % Hkv, b = bkv / Hkv;
-  const int G = Hq / Hkv;
-  const int key = kb * kAB + 16 * wave + r16;
-  const bool kok = key < n;
-  const float scale = 1.f / sqrtf(float(HD));
+  const int R = Hq / Hkv;
+  const int kw = (kb * 4 + wave) * 16 * G;  // the wave's first key
+  const float scale = 1.f / sqrtf(float(HD)), scale2 = scale * kLog2e;
   const uint16_t* Kh = K + int64_t(bkv) * n * HD;
   const uint16_t* Vh = V + int64_t(bkv) * n * HD;
-  const int nq = nkb - kb;  // query blocks at or after the key block
-  const int items = G * nq;
-  // item i: query head kvh G + i / nq, query block kb + i % nq
+  const int qb0 = kb * G, nq = (n + kAB - 1) / kAB - qb0;  // query blocks that reach the key block
+  const int items = R * nq;
+  // item i: query head kvh R + i / nq, query block qb0 + i % nq
   auto issue = [&](int i) {
-    const int h = kvh * G + i / nq, qb = kb + i % nq;
+    const int h = kvh * R + i / nq, qb = qb0 + i % nq;
     const int64_t bh = int64_t(b) * Hq + h;
     char* st = smem + (i & 1) * 2 * A::kTileBytes;
     attn_tile_dma<HD>(Q + bh * n * HD, HD, qb * kAB, n, st, wave, lane);
     attn_tile_dma<HD>(dO + int64_t(b) * n * (int64_t(Hq) * HD) + int64_t(h) * HD, int64_t(Hq) * HD, qb * kAB, n,
                       st + A::kTileBytes, wave, lane);
   };
-  float pl = 0.f, pd = 0.f;  // wave 0, lane = query of the next item: its lse and D
+  float pl = 0.f, pd = 0.f;  // wave 0, lane = query of the next item: its lse (base 2) and D
   auto fetch_stats = [&](int i) {
-    const int h = kvh * G + i / nq, qq = (kb + i % nq) * kAB + lane;
+    const int h = kvh * R + i / nq, qq = (qb0 + i % nq) * kAB + lane;
     const int64_t bh = int64_t(b) * Hq + h;
-    pl = qq < n ? lse[bh * n + qq] : 0.f;
+    pl = qq < n ? lse[bh * n + qq] * kLog2e : 0.f;
     pd = qq < n ? dvec[bh * n + qq] : 0.f;
   };
   issue(0);
   if (wave == 0) fetch_stats(0);
 
-  bf16x8 kf[NS], vf[NS];
+  bf16x8 kf[G][NS], vf[G][NS];
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    u32x4 z = {0u, 0u, 0u, 0u}, kv = z, vv = z;
-    if (kok) {
-      kv = *reinterpret_cast<const u32x4*>(Kh + int64_t(key) * HD + 32 * s + 8 * grp);
-      vv = *reinterpret_cast<const u32x4*>(Vh + int64_t(key) * HD + 32 * s + 8 * grp);
+  for (int g = 0; g < G; ++g) {
+    const int key = kw + 16 * g + r16;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      u32x4 z = {0u, 0u, 0u, 0u}, kv = z, vv = z;
+      if (key < n) {
+        kv = *reinterpret_cast<const u32x4*>(Kh + int64_t(key) * HD + 32 * s + 8 * grp);
+        vv = *reinterpret_cast<const u32x4*>(Vh + int64_t(key) * HD + 32 * s + 8 * grp);
+      }
+      kf[g][s] = __builtin_bit_cast(bf16x8, kv);
+      vf[g][s] = __builtin_bit_cast(bf16x8, vv);
     }
-    kf[s] = __builtin_bit_cast(bf16x8, kv);
-    vf[s] = __builtin_bit_cast(bf16x8, vv);
   }
   const AttnTrans<HD> tr(lane);
-  f32x4 adk[NC], adv[NC];
+  f32x4 adk[G][NC], adv[G][NC];
 #pragma unroll
-  for (int cb = 0; cb < NC; ++cb) {
-    adk[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    adv[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) adk[g][cb] = adv[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int i = 0; i < items; ++i) {
     const int slot = i & 1;
     if (wave == 0) {  // slot's previous readers finished item i - 2 before the last barrier
@@ -750,42 +787,48 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
       issue(i + 1);
       if (wave == 0) fetch_stats(i + 1);
     }
-    const int qb = kb + i % nq;
+    const int q0 = (qb0 + i % nq) * kAB;
+    if (q0 + kAB - 1 < kw) continue;  // every query before the wave's keys
+    const bool edge = q0 < kw + 16 * G - 1;  // some of the block's queries come before some of the keys
     const char* Qt = smem + slot * 2 * A::kTileBytes;
     const char* Dt = Qt + A::kTileBytes;
-    float p[4][4], ds[4][4];
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
-      f32x4 st = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const bf16x8 qa = attn_row_frag<HD>(Qt, 16 * blk + r16, 4 * s + grp);
-        const bf16x8 da = attn_row_frag<HD>(Dt, 16 * blk + r16, 4 * s + grp);
-        st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, kf[s], st, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, vf[s], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int ql = 16 * blk + 4 * grp + e;
-        const int qq = qb * kAB + ql;
-        const float pv = (kok && qq < n && key <= qq) ? __expf(st[e] * scale - lse_s[slot][ql]) : 0.f;
-        p[blk][e] = pv;
-        ds[blk][e] = pv * (dp[e] - dvec_s[slot][ql]) * scale;
-      }
-    }
-    bf16x8 pb[2], db[2];
+    bf16x8 pb[G][2], db[G][2];
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      float pv[8], dv[8];
+      float p[G][8], ds[G][8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        pv[e] = p[2 * s2][e];
-        pv[4 + e] = p[2 * s2 + 1][e];
-        dv[e] = ds[2 * s2][e];
-        dv[4 + e] = ds[2 * s2 + 1][e];
+      for (int hb = 0; hb < 2; ++hb) {
+        const int blk = 2 * s2 + hb;
+        f32x4 st[G], dp[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) st[g] = dp[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const bf16x8 qa = attn_row_frag<HD>(Qt, 16 * blk + r16, 4 * s + grp);
+          const bf16x8 da = attn_row_frag<HD>(Dt, 16 * blk + r16, 4 * s + grp);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            st[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, kf[g][s], st[g], 0, 0, 0);
+            dp[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, vf[g][s], dp[g], 0, 0, 0);
+          }
+        }
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&lse_s[slot][16 * blk + 4 * grp]);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&dvec_s[slot][16 * blk + 4 * grp]);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float pv = __builtin_amdgcn_exp2f(fmaf(st[g][e], scale2, -l4[e]));
+            if (edge && kw + 16 * g + r16 > q0 + 16 * blk + 4 * grp + e) pv = 0.f;
+            p[g][4 * hb + e] = pv;
+            ds[g][4 * hb + e] = pv * (dp[g][e] - d4[e]);
+          }
       }
-      pb[s2] = pack8(pv);
-      db[s2] = pack8(dv);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        pb[g][s2] = pack8(p[g]);
+        db[g][s2] = pack8(ds[g]);
+      }
     }
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) {
@@ -793,19 +836,24 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
       tr.read(Dt, cb, dt2);
       tr.read(Qt, cb, qt2);
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        adv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dt2[s2], pb[s2], adv[cb], 0, 0, 0);
-        adk[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qt2[s2], db[s2], adk[cb], 0, 0, 0);
-      }
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          adv[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dt2[s2], pb[g][s2], adv[g][cb], 0, 0, 0);
+          adk[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qt2[s2], db[g][s2], adk[g][cb], 0, 0, 0);
+        }
     }
   }
-  if (kok) {
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int key = kw + 16 * g + r16;
+    if (key >= n) continue;
     float* dk = dk_out + (int64_t(bkv) * n + key) * HD;
     float* dv = dv_out + (int64_t(bkv) * n + key) * HD;
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) {
-      *reinterpret_cast<f32x4*>(dk + 16 * cb + 4 * grp) = adk[cb];
-      *reinterpret_cast<f32x4*>(dv + 16 * cb + 4 * grp) = adv[cb];
+      *reinterpret_cast<f32x4*>(dk + 16 * cb + 4 * grp) = adk[g][cb] * scale;
+      *reinterpret_cast<f32x4*>(dv + 16 * cb + 4 * grp) = adv[g][cb];
     }
   }
 }
@@ -814,22 +862,35 @@ hipError_t launch_attention_bwd(const void* q, const void* k, const void* v, con
                                 int Hq, int Hkv, int n, int hd, const float* lse, float* dvec, float* dq, float* dk,
                                 float* dv, hipStream_t s) {
   if (B == 0 || n == 0) return hipSuccess;
-  const int nb = (n + kAB - 1) / kAB;
   const auto *Qp = (const uint16_t*)q, *Kp = (const uint16_t*)k, *Vp = (const uint16_t*)v;
   const auto *Op = (const uint16_t*)o, *Dp = (const uint16_t*)dout;
-  const dim3 g1(B * Hq * nb), g2(B * Hkv * nb);
+  auto run_dq = [&](auto hdc, auto gc) {
+    constexpr int HD = decltype(hdc)::value, G = decltype(gc)::value;
+    attn_bwd_dq_kernel<HD, G><<<B * Hq * ((n + kAB * G - 1) / (kAB * G)), 256, 0, s>>>(Qp, Kp, Vp, Op, Dp, n, Hq, Hkv,
+                                                                                       B * Hq, lse, dvec, dq);
+  };
+  auto run_dkv = [&](auto hdc, auto gc) {
+    constexpr int HD = decltype(hdc)::value, G = decltype(gc)::value;
+    attn_bwd_dkv_kernel<HD, G><<<B * Hkv * ((n + kAB * G - 1) / (kAB * G)), 256, 0, s>>>(
+        Qp, Kp, Vp, Dp, lse, dvec, n, Hq, Hkv, B * Hkv, dk, dv);
+  };
+  std::integral_constant<int, 1> one;
+  std::integral_constant<int, 2> two;
+  const int64_t wide = (n + 2 * kAB - 1) / (2 * kAB);
+  auto run = [&](auto hdc) {
+    if (B * Hq * wide >= kAttnBwdWide) run_dq(hdc, two);
+    else run_dq(hdc, one);
+    if (B * Hkv * wide >= kAttnBwdWide) run_dkv(hdc, two);
+    else run_dkv(hdc, one);
+  };
   switch (hd) {
-#define DSF_ATTN_BWD(H)                                                                         \
-  case H:                                                                                       \
-    attn_bwd_dq_kernel<H><<<g1, 256, 0, s>>>(Qp, Kp, Vp, Op, Dp, n, Hq, Hkv, lse, dvec, dq);   \
-    attn_bwd_dkv_kernel<H><<<g2, 256, 0, s>>>(Qp, Kp, Vp, Dp, lse, dvec, n, Hq, Hkv, dk, dv); \
-    break;
-    DSF_ATTN_BWD(32)
-    DSF_ATTN_BWD(64)
-    DSF_ATTN_BWD(128)
-#undef DSF_ATTN_BWD
-    default:
-      return hipErrorInvalidValue;
+    case 32: run(std::integral_constant<int, 32>{}); break;
+    case 64: run(std::integral_constant<int, 64>{}); break;
+    case 128:
+      run_dq(std::integral_constant<int, 128>{}, one);
+      run_dkv(std::integral_constant<int, 128>{}, one);
+      break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

@@ -1,0 +1,35 @@
+"""Attention's share of the layer's backward where its blocks of 64 and 128
+queries (keys) begin and end, for each head dimension and grouping, below and
+above the number of workgroups from which a wavefront takes two groups of 16
+(512 blocks of 128, counted apart for query heads and for kv heads). All
+gradients are held to the oracle's float64 ones, 2e-2 of each one's infinity
+norm, and repeated calls are equal."""
+import pytest
+import torch
+
+import synthetic as S
+
+from gpu_util import announce
+from test_gpu_12_backward import check_backward, run_backward
+from test_gpu_18_weight_grads import _case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("case", [
+    (S.NEOX, 128, 2, 2, 32, 128, 1, 70, 63),
+    (S.NEOX, 128, 2, 2, 32, 128, 1, 140, 129),
+    (S.NEOX, 512, 16, 16, 32, 128, 16, 290, 257),   # 768 blocks: two groups per wave
+    (S.NEOX, 512, 8, 8, 64, 128, 16, 520, 511),     # 512: the first grid that takes them
+    (S.NEOX, 512, 8, 8, 64, 128, 16, 390, 384),     # 384: one group
+    (S.QWEN, 512, 16, 2, 64, 128, 16, 270, 193),    # queries with two groups, keys with one
+    (S.QWEN, 256, 14, 2, 64, 128, 2, 130, 65),
+    (S.QWEN, 256, 6, 2, 128, 128, 3, 200, 191),
+], ids=lambda c: f"{c[0]}-h{c[2]}.{c[3]}x{c[4]}-B{c[6]}-k{c[8]}")
+def test_attention_blocks(dev, case):
+    w, W, x, dy, idx = _case(*case)
+    announce(f"attention backward {case}")
+    dx, g = run_backward(dev, w, W, x, dy, idx, False)
+    check_backward(w, W, x, dy, idx, False, dx, g)
+    dx2, g2 = run_backward(dev, w, W, x, dy, idx, False)
+    assert torch.equal(dx, dx2) and all(torch.equal(g[n], g2[n]) for n in g)
