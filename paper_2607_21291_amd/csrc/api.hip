@@ -1412,7 +1412,7 @@ extern "C" int dsf_align_stack_forward(const dsf_layer_desc* desc, const dsf_lay
 
 namespace {
 struct BwdPlan {
-  size_t ctl, skpart, rope, xc, a1, a2, h, m2, q, k, v, attn, u, dd, du, dm, dao, dattn, dqf, dkf, dvf, lse, dvec, dqkv, da, acc;
+  size_t ctl, skpart, rope, xc, a1, a2, h, m2, q, k, v, attn, u, dd, du, dm, dao, dattn, lse, dvec, dqkv, da, acc;
   size_t wdT, wuT, woT, wqT, act, bpart, bpart_bytes, total;
   int fup, dqkv_cols;
 };
@@ -1451,9 +1451,6 @@ BwdPlan make_bwd_plan(const dsf_layer_desc& D, int B, int T, int k) {
   p.dm = take(2 * N * d);
   p.dao = qwen ? take(2 * N * d) : p.dd;
   p.dattn = take(2 * N * dq);
-  p.dqf = take(4 * N * dq);
-  p.dkf = take(4 * N * dkv);
-  p.dvf = take(4 * N * dkv);
   p.lse = take(4 * size_t(B) * D.n_heads * k);
   p.dvec = take(4 * size_t(B) * D.n_heads * k);
   p.dqkv = take(2 * N * cq);
@@ -1623,11 +1620,9 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   DSF_HIP(launch_transpose(weights->w_o, d, dq, dq, P(p.woT), d, s));
   rc = bwd_gemm(EPI_STORE, N, dq, d, P(p.dao), d, P(p.woT), d, P(p.dattn), dq, nullptr, nullptr, 0, s);
   if (rc) return rc;
-  // attention over the kept tokens, then RoPE turned back into token-major dqkv
+  // attention over the kept tokens, RoPE turned back, into token-major dqkv
   DSF_HIP(launch_attention_bwd(P(p.q), P(p.k), P(p.v), P(p.attn), P(p.dattn), B, Hq, Hkv, k, hd, F(p.lse),
-                               F(p.dvec), F(p.dqf), F(p.dkf), F(p.dvf), s));
-  DSF_HIP(launch_rope_bwd(F(p.dqf), F(p.dkf), F(p.dvf), F(p.rope), idx, B, k, T, Hq, Hkv, hd, D.rotary_dims,
-                          P(p.dqkv), s));
+                               F(p.dvec), F(p.rope), idx, T, D.rotary_dims, P(p.dqkv), s));
   // QKV projection
   DSF_HIP(wgrad(P(p.dqkv), cq, P(p.a1), d, G.w_qkv, G.b_qkv));
   DSF_HIP(launch_transpose(weights->w_qkv, cq, d, d, P(p.wqT), cq, s));

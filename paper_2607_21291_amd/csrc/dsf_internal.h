@@ -272,19 +272,16 @@ int norm_bwd_partials(int M);
 hipError_t launch_norm_bwd(bool rms, const void* x, const void* dyn, const void* w, int M, int d, float eps, float* acc,
                            bool accumulate, const void* add, void* sum_out, float* dw, float* db, float* partial,
                            hipStream_t s);
-// dqkv [B kk, (Hq + 2 Hkv) hd] (bf16) from head-major fp32 dq, dk, dv; RoPE turned back.
-hipError_t launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* table, const int32_t* idx,
-                           int B, int kk, int T, int Hq, int Hkv, int hd, int R, void* out, hipStream_t s);
 // dx[b, idx] = dy[b, idx] + acc (fp32 add, one rounding)
 hipError_t launch_scatter_grad(const void* dy, const float* acc, int B, int T, int d, const int32_t* idx, int kk,
                                void* dx, hipStream_t s);
 // causal attention backward; q, k, v head-major (RoPE applied), o and dout
 // token-major [B n, Hq hd]; lse [B, Hq, n] from the forward (launch_attention);
-// dvec [B, Hq, n] (written, then read); dq [B, Hq, n, hd], dk and dv
-// [B, Hkv, n, hd] fp32.
+// dvec [B, Hq, n] (written, then read). dqkv [B n, (Hq + 2 Hkv) hd] (bf16):
+// the gradients at q, k and v, RoPE turned back at positions idx [B, n] < T.
 hipError_t launch_attention_bwd(const void* q, const void* k, const void* v, const void* o, const void* dout, int B,
-                                int Hq, int Hkv, int n, int hd, const float* lse, float* dvec, float* dq, float* dk,
-                                float* dv, hipStream_t s);
+                                int Hq, int Hkv, int n, int hd, const float* lse, float* dvec, const float* table,
+                                const int32_t* idx, int T, int R, void* dqkv, hipStream_t s);
 size_t gemm_partial_bytes();
 int gemm_flag_count();
 size_t gemm_skinny_partial_bytes();

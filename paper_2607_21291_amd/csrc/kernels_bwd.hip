@@ -372,123 +372,6 @@ hipError_t launch_norm_bwd(bool rms, const void* x, const void* dyn, const void*
   return hipGetLastError();
 }
 
-// --------------------------------------------- RoPE adjoint and relayout
-
-// dqkv[m][col] (bf16, token-major [M, (Hq + 2 Hkv) hd]) from the head-major
-// fp32 gradients at the rotated q and k (and at v). A rotated pair (i,
-// i + R/2) at position p was turned by the angle a = p * theta^(-2i/R); its
-// gradient turns back: d_i' = d_i cos a + d_{i+R/2} sin a,
-// d_{i+R/2}' = d_{i+R/2} cos a - d_i sin a. table: [T][R/2][2] (cos, sin).
-__global__ __launch_bounds__(256) void rope_bwd_kernel(const float* __restrict__ dq, const float* __restrict__ dk,
-                                                       const float* __restrict__ dv, const float* __restrict__ table,
-                                                       const int32_t* __restrict__ idx, int kk, int T, int Hq,
-                                                       int Hkv, int hd, int R, int M, uint16_t* __restrict__ out) {
-  const int cols = (Hq + 2 * Hkv) * hd;
-  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= int64_t(M) * cols) return;
-  const int m = int(e / cols), col = int(e - int64_t(m) * cols);
-  const int b = m / kk, j = m - b * kk;
-  const int p = idx ? clamp_pos(idx[m], T) : j;
-  const int qc = Hq * hd, kc = Hkv * hd;
-  const float* src;
-  int head, dim, heads;
-  bool rot = true;
-  if (col < qc) {
-    src = dq; heads = Hq; head = col / hd; dim = col % hd;
-  } else if (col < qc + kc) {
-    src = dk; heads = Hkv; head = (col - qc) / hd; dim = (col - qc) % hd;
-  } else {
-    src = dv; heads = Hkv; head = (col - qc - kc) / hd; dim = (col - qc - kc) % hd; rot = false;
-  }
-  const float* row = src + ((int64_t(b) * heads + head) * kk + j) * hd;
-  float v = row[dim];
-  if (rot && dim < R) {
-    const int half = R / 2;
-    if (dim < half) {
-      const float* cs = table + (int64_t(p) * half + dim) * 2;
-      v = v * cs[0] + row[dim + half] * cs[1];
-    } else {
-      const float* cs = table + (int64_t(p) * half + dim - half) * 2;
-      v = v * cs[0] - row[dim - half] * cs[1];
-    }
-  }
-  out[e] = f2bf(v);
-}
-
-// The same, eight columns per thread (one 16-byte store): the eight dims of
-// a chunk lie in one head and, with R a multiple of 16, in one half of the
-// rotated dims, so their partners and their (cos, sin) pairs are contiguous.
-// The index arithmetic is done once per chunk in 32 bits (the launcher checks
-// that the chunks fit) and the head dim is a power of two. Each element's
-// arithmetic is the one of rope_bwd_kernel.
-__global__ __launch_bounds__(256) void rope_bwd_vec_kernel(const float* __restrict__ dq, const float* __restrict__ dk,
-                                                           const float* __restrict__ dv,
-                                                           const float* __restrict__ table,
-                                                           const int32_t* __restrict__ idx, int kk, int T, int Hq,
-                                                           int Hkv, int hshift, int R, uint32_t chunks,
-                                                           uint16_t* __restrict__ out) {
-  const int hd = 1 << hshift;
-  const uint32_t cpr = uint32_t(Hq + 2 * Hkv) << (hshift - 3);  // 8-column chunks per row
-  const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-  if (e >= chunks) return;
-  const uint32_t m = e / cpr;
-  const int col0 = int(e - m * cpr) * 8;
-  const int b = int(m) / kk, j = int(m) - b * kk;
-  const int p = idx ? clamp_pos(idx[m], T) : j;
-  const int qc = Hq << hshift, kc = Hkv << hshift;
-  const float* src;
-  int c = col0, heads;
-  bool rot = true;
-  if (c < qc) {
-    src = dq; heads = Hq;
-  } else if (c < qc + kc) {
-    src = dk; heads = Hkv; c -= qc;
-  } else {
-    src = dv; heads = Hkv; c -= qc + kc; rot = false;
-  }
-  const int head = c >> hshift, dim0 = c & (hd - 1);
-  const float* row = src + ((int64_t(b) * heads + head) * kk + j) * hd;
-  float v[8];
-  *reinterpret_cast<float4*>(v) = *reinterpret_cast<const float4*>(row + dim0);
-  *reinterpret_cast<float4*>(v + 4) = *reinterpret_cast<const float4*>(row + dim0 + 4);
-  if (rot && dim0 < R) {
-    const int half = R / 2;
-    const bool lo = dim0 < half;
-    const float* pr = row + (lo ? dim0 + half : dim0 - half);
-    float pv[8];
-    *reinterpret_cast<float4*>(pv) = *reinterpret_cast<const float4*>(pr);
-    *reinterpret_cast<float4*>(pv + 4) = *reinterpret_cast<const float4*>(pr + 4);
-    const float4* cs = reinterpret_cast<const float4*>(table + (int64_t(p) * half + (lo ? dim0 : dim0 - half)) * 2);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = cs[q];
-      v[2 * q] = lo ? v[2 * q] * t.x + pv[2 * q] * t.y : v[2 * q] * t.x - pv[2 * q] * t.y;
-      v[2 * q + 1] = lo ? v[2 * q + 1] * t.z + pv[2 * q + 1] * t.w : v[2 * q + 1] * t.z - pv[2 * q + 1] * t.w;
-    }
-  }
-  store_vec(out + int64_t(m) * (int64_t(cpr) * 8) + col0, v);
-}
-
-hipError_t launch_rope_bwd(const float* dq, const float* dk, const float* dv, const float* table, const int32_t* idx,
-                           int B, int kk, int T, int Hq, int Hkv, int hd, int R, void* out, hipStream_t s) {
-  const int64_t n = int64_t(B) * kk * (Hq + 2 * Hkv) * hd;
-  if (n == 0) return hipSuccess;
-  const int64_t chunks = n / 8;
-  if (R % 16 == 0 && (hd & (hd - 1)) == 0 && hd >= 8 && chunks < (int64_t(1) << 31) &&
-      (reinterpret_cast<uintptr_t>(out) & 15) == 0 && (reinterpret_cast<uintptr_t>(dq) & 15) == 0 &&
-      (reinterpret_cast<uintptr_t>(dk) & 15) == 0 && (reinterpret_cast<uintptr_t>(dv) & 15) == 0 &&
-      (reinterpret_cast<uintptr_t>(table) & 15) == 0) {
-    int hshift = 0;
-    while ((1 << hshift) < hd) ++hshift;
-    rope_bwd_vec_kernel<<<unsigned((chunks + 255) / 256), 256, 0, s>>>(dq, dk, dv, table, idx, kk, T, Hq, Hkv, hshift,
-                                                                        R, uint32_t(chunks), (uint16_t*)out);
-    return hipGetLastError();
-  }
-  rope_bwd_kernel<<<int((n + 255) / 256), 256, 0, s>>>(dq, dk, dv, table, idx, kk, T, Hq, Hkv, hd, R, B * kk,
-                                                       (uint16_t*)out);
-  return hipGetLastError();
-}
-
 // ----------------------------------------------------- the final scatter
 
 // x_grad[b][idx[m]][:] = dy[b][idx[m]][:] + acc[m][:] (fp32 add, one rounding);
@@ -565,6 +448,76 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kAttnBwdWide = 512;  // workgroups of 128 queries (keys) from which they are used
 
+// The gradients at q, k and v leave as the rows of dqkv [B n, (Hq + 2 Hkv) HD]
+// (bf16, token-major), q and k turned back through the rotary embedding: a
+// rotated pair (i, i + R/2) at position p was turned by the angle
+// a = p * theta^(-2i/R); its gradient turns back,
+//   d_i' = d_i cos a + d_{i+R/2} sin a, d_{i+R/2}' = d_{i+R/2} cos a - d_i sin a.
+// A pair's halves lie in different lanes, so the fp32 rows go through the LDS
+// of the finished tiles. (As a kernel of its own behind fp32 head-major
+// outputs the turn read 115 MB and wrote 58 MB again at 12504 NeoX-160M rows:
+// 29 us.) table: [T][R/2][2] (cos, sin).
+struct RopeOut {
+  const float* table; const int32_t* idx;  // positions [B, n]
+  int T, R;
+  uint16_t* out;
+  int cols;
+};
+
+// Four columns 4 c4 .. + 3 of row r of the staged [rows][HD] fp32 gradients.
+template <int HD>
+__device__ __forceinline__ float* staged4(float* stage, int r, int c4) {
+  return stage + r * HD + ((c4 ^ (r & 7)) << 2);
+}
+
+// Rows `first` .. of `rows` staged rows (those below n) to columns col .. of dqkv.
+template <int HD>
+__device__ __forceinline__ void store_rows(float* stage, int rows, int first, int n, int b, int col, bool rope,
+                                           const RopeOut& o) {
+  constexpr int V = HD / 8;
+  const int half = o.R / 2;
+  for (int t = threadIdx.x; t < rows * V; t += 256) {
+    const int r = t / V, c0 = (t % V) * 8, tok = first + r;
+    if (tok >= n) break;  // (r grows with t)
+    const int64_t m = int64_t(b) * n + tok;
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(staged4<HD>(stage, r, c0 / 4 + q));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * q + e] = x[e];
+    }
+    if (rope && c0 < o.R) {
+      const float* tab = o.table + int64_t(clamp_pos(o.idx[m], o.T)) * o.R;
+      if (o.R % 16 == 0) {  // the eight columns lie in one half, their partners are eight columns too
+        const bool lo = c0 < half;
+        const int pc = lo ? c0 + half : c0 - half;
+        const f32x4* cs = reinterpret_cast<const f32x4*>(tab + 2 * (lo ? c0 : pc));
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(staged4<HD>(stage, r, pc / 4 + q));
+          const f32x4 t0 = cs[2 * q], t1 = cs[2 * q + 1];
+          const float c[4] = {t0[0], t0[2], t1[0], t1[2]}, sn[4] = {t0[1], t0[3], t1[1], t1[3]};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[4 * q + e] = lo ? v[4 * q + e] * c[e] + x[e] * sn[e] : v[4 * q + e] * c[e] - x[e] * sn[e];
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int dim = c0 + e;
+          if (dim >= o.R) continue;
+          const bool lo = dim < half;
+          const int pc = lo ? dim + half : dim - half, i = lo ? dim : pc;
+          const float x = staged4<HD>(stage, r, pc >> 2)[pc & 3];
+          v[e] = lo ? v[e] * tab[2 * i] + x * tab[2 * i + 1] : v[e] * tab[2 * i] - x * tab[2 * i + 1];
+        }
+      }
+    }
+    store_vec(o.out + m * o.cols + col + c0, v);
+  }
+}
+
 // Pass 1: one workgroup per (sequence, query head, block of 64 G queries);
 // wave w owns queries q0 + 16 G w .. + 16 G - 1 (lane l: query l % 16 of each
 // group). Scores are formed transposed (S^T = K Q^T, keys as MFMA rows), so a
@@ -579,7 +532,7 @@ __global__ __launch_bounds__(256, HD == 64 && G == 2 ? 3 : 1) void attn_bwd_dq_k
                                                           const uint16_t* __restrict__ O,
                                                           const uint16_t* __restrict__ dO, int n, int Hq, int Hkv,
                                                           int nbh, const float* __restrict__ lse,
-                                                          float* __restrict__ dvec_out, float* __restrict__ dq_out) {
+                                                          float* __restrict__ dvec_out, RopeOut ro) {
   using A = AttnTile<HD>;
   constexpr int NS = HD / 32, NC = HD / 16;
   __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes];  // stage: K tile, then V tile
@@ -690,14 +643,15 @@ __global__ __launch_bounds__(256, HD == 64 && G == 2 ? 3 : 1) void attn_bwd_dq_k
     }
   }
   // lane holds dQ^T[16 cb + 4 grp + e][query] / scale
+  float* stage = reinterpret_cast<float*>(smem);
+  __syncthreads();  // every wave is done with the tiles
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int query = qw + 16 * g + r16;
-    if (query >= n) continue;
-    float* dst = dq_out + (int64_t(bh) * n + query) * HD;
+  for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int cb = 0; cb < NC; ++cb) *reinterpret_cast<f32x4*>(dst + 16 * cb + 4 * grp) = acc[g][cb] * scale;
-  }
+    for (int cb = 0; cb < NC; ++cb)
+      *reinterpret_cast<f32x4*>(staged4<HD>(stage, 16 * (G * wave + g) + r16, 4 * cb + grp)) = acc[g][cb] * scale;
+  __syncthreads();
+  store_rows<HD>(stage, kAB * G, qb * kAB * G, n, b, h * HD, true, ro);
 }
 
 // Pass 2: one workgroup per (sequence, kv head, block of 64 G keys); wave w
@@ -718,8 +672,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
                                                            const uint16_t* __restrict__ dO,
                                                            const float* __restrict__ lse,
                                                            const float* __restrict__ dvec, int n, int Hq, int Hkv,
-                                                           int nbkv, float* __restrict__ dk_out,
-                                                           float* __restrict__ dv_out) {
+                                                           int nbkv, RopeOut ro) {
   using A = AttnTile<HD>;
   constexpr int NS = HD / 32, NC = HD / 16;
   __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes];  // stage: Q tile, then dout tile
@@ -844,35 +797,37 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
         }
     }
   }
+  float* stage = reinterpret_cast<float*>(smem);
+  auto put = [&](const f32x4(&acc)[G][NC], float mul, int col, bool rope) {
+    __syncthreads();  // every wave is done with the tiles (with the rows staged before)
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int key = kw + 16 * g + r16;
-    if (key >= n) continue;
-    float* dk = dk_out + (int64_t(bkv) * n + key) * HD;
-    float* dv = dv_out + (int64_t(bkv) * n + key) * HD;
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int cb = 0; cb < NC; ++cb) {
-      *reinterpret_cast<f32x4*>(dk + 16 * cb + 4 * grp) = adk[g][cb] * scale;
-      *reinterpret_cast<f32x4*>(dv + 16 * cb + 4 * grp) = adv[g][cb];
-    }
-  }
+      for (int cb = 0; cb < NC; ++cb)
+        *reinterpret_cast<f32x4*>(staged4<HD>(stage, 16 * (G * wave + g) + r16, 4 * cb + grp)) = acc[g][cb] * mul;
+    __syncthreads();
+    store_rows<HD>(stage, kAB * G, kb * kAB * G, n, b, col, rope, ro);
+  };
+  put(adk, scale, (Hq + kvh) * HD, true);
+  put(adv, 1.f, (Hq + Hkv + kvh) * HD, false);
 }
 
 hipError_t launch_attention_bwd(const void* q, const void* k, const void* v, const void* o, const void* dout, int B,
-                                int Hq, int Hkv, int n, int hd, const float* lse, float* dvec, float* dq, float* dk,
-                                float* dv, hipStream_t s) {
+                                int Hq, int Hkv, int n, int hd, const float* lse, float* dvec, const float* table,
+                                const int32_t* idx, int T, int R, void* dqkv, hipStream_t s) {
   if (B == 0 || n == 0) return hipSuccess;
+  const RopeOut ro{table, idx, T, R, (uint16_t*)dqkv, (Hq + 2 * Hkv) * hd};
   const auto *Qp = (const uint16_t*)q, *Kp = (const uint16_t*)k, *Vp = (const uint16_t*)v;
   const auto *Op = (const uint16_t*)o, *Dp = (const uint16_t*)dout;
   auto run_dq = [&](auto hdc, auto gc) {
     constexpr int HD = decltype(hdc)::value, G = decltype(gc)::value;
     attn_bwd_dq_kernel<HD, G><<<B * Hq * ((n + kAB * G - 1) / (kAB * G)), 256, 0, s>>>(Qp, Kp, Vp, Op, Dp, n, Hq, Hkv,
-                                                                                       B * Hq, lse, dvec, dq);
+                                                                                       B * Hq, lse, dvec, ro);
   };
   auto run_dkv = [&](auto hdc, auto gc) {
     constexpr int HD = decltype(hdc)::value, G = decltype(gc)::value;
     attn_bwd_dkv_kernel<HD, G><<<B * Hkv * ((n + kAB * G - 1) / (kAB * G)), 256, 0, s>>>(
-        Qp, Kp, Vp, Dp, lse, dvec, n, Hq, Hkv, B * Hkv, dk, dv);
+        Qp, Kp, Vp, Dp, lse, dvec, n, Hq, Hkv, B * Hkv, ro);
   };
   std::integral_constant<int, 1> one;
   std::integral_constant<int, 2> two;

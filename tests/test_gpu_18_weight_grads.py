@@ -23,11 +23,15 @@ def _case(block, d, hq, hkv, hd, f, B, T, k):
     base = workload("neox_bf16_small" if block == S.NEOX else "qwen_bf16_small")
     w = base.replace(name="wgrad", d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=f,
                      rotary_dims=hd if block == S.QWEN else hd // 4, batch=B, seq=T)
+    return _inputs(w, k)
+
+
+def _inputs(w, k):
     W = S.layer_weights(w, 0)
     x = S.hidden_states(w)
-    g = torch.Generator().manual_seed(d + k)
-    dy = torch.randn(B, T, d, generator=g).to(torch.bfloat16)
-    idx = np.stack([np.sort(torch.randperm(T, generator=g)[:k].numpy()) for _ in range(B)])
+    g = torch.Generator().manual_seed(w.d_model + k)
+    dy = torch.randn(w.batch, w.seq, w.d_model, generator=g).to(torch.bfloat16)
+    idx = np.stack([np.sort(torch.randperm(w.seq, generator=g)[:k].numpy()) for _ in range(w.batch)])
     return w, W, x, dy, idx
 
 
@@ -37,6 +41,8 @@ def _case(block, d, hq, hkv, hd, f, B, T, k):
     (S.NEOX, 264, 4, 4, 64, 576, 1, 70, 65),
     (S.NEOX, 520, 4, 4, 64, 1088, 2, 300, 257),    # 9 token tiles: two slices
     (S.NEOX, 128, 2, 2, 64, 512, 8, 300, 290),     # 37: eight slices of few tiles
+    (S.NEOX, 768, 12, 12, 64, 3072, 2, 300, 290),  # 10 token tiles: two slices, either tile width
+    (S.NEOX, 776, 12, 12, 64, 2944, 8, 300, 290),  # tiles of 192 columns with remainders
     (S.QWEN, 136, 3, 1, 64, 192, 1, 70, 64),
     (S.QWEN, 1032, 4, 1, 128, 320, 2, 170, 161),
     (S.QWEN, 2056, 2, 1, 64, 128, 1, 40, 33),

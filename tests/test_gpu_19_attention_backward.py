@@ -9,11 +9,29 @@ import torch
 
 import synthetic as S
 
-from gpu_util import announce
+from gpu_util import announce, workload
 from test_gpu_12_backward import check_backward, run_backward
-from test_gpu_18_weight_grads import _case
+from test_gpu_18_weight_grads import _case, _inputs
 
 pytestmark = pytest.mark.gpu
+
+
+def _workload_case(name, B, T, k, rot):
+    w = workload(name).replace(batch=B, seq=T)
+    if rot:
+        w = w.replace(rotary_dims=rot)
+    return _inputs(w, k)
+
+
+@pytest.mark.parametrize("rot", [None, 8, 20])
+@pytest.mark.parametrize("name,B,T,k", [("neox_bf16_small", 2, 90, 77), ("qwen_bf16_hd128", 1, 140, 130)])
+def test_rotary_dims(dev, name, B, T, k, rot):
+    # rotated dims in multiples of 16 (None: the workload's), which are turned
+    # back eight at a time, and others
+    w, W, x, dy, idx = _workload_case(name, B, T, k, rot)
+    announce(f"attention backward {name} rotary_dims={w.rotary_dims}")
+    dx, g = run_backward(dev, w, W, x, dy, idx, False)
+    check_backward(w, W, x, dy, idx, False, dx, g)
 
 
 @pytest.mark.parametrize("case", [
