@@ -1594,17 +1594,20 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   }
 
   // ---- the adjoint: d(delta) = gate * dy at the kept rows
+  const TransposeArgs wt[] = {{weights->w_down, P(p.wdT), d, f},
+                              {weights->w_up, P(p.wuT), fup, d},
+                              {weights->w_o, P(p.woT), d, dq},
+                              {weights->w_qkv, P(p.wqT), cq, d}};
+  DSF_HIP(launch_transpose(wt, 4, s));
   DSF_HIP(launch_gather_scale(dy, B, T, d, idx, k, gate ? scores : nullptr, P(p.dd), s));
   // FFN down projection (the adjoint's epilogue rebuilds the activation, the
   // weight gradient's other factor)
-  DSF_HIP(launch_transpose(weights->w_down, d, f, f, P(p.wdT), d, s));
   rc = bwd_gemm(qwen ? EPI_SWIGLU_BWD : EPI_GELU_BWD, N, f, d, P(p.dd), d, P(p.wdT), d, P(p.du), fup, nullptr, P(p.u),
                 f, s, G.w_down ? P(p.act) : nullptr);
   if (rc) return rc;
   DSF_HIP(wgrad(P(p.dd), d, P(p.act), f, G.w_down, qwen ? nullptr : G.b_down));
   // FFN up projection
   DSF_HIP(wgrad(P(p.du), fup, mrows, d, G.w_up, qwen ? nullptr : G.b_up));
-  DSF_HIP(launch_transpose(weights->w_up, fup, d, d, P(p.wuT), fup, s));
   rc = bwd_gemm(EPI_STORE, N, d, fup, P(p.du), fup, P(p.wuT), fup, P(p.dm), d, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // second norm: NeoX's LN2 of the kept rows, Qwen's RMS2 of h = x + attention
@@ -1617,7 +1620,6 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
   }
   // attention output projection
   DSF_HIP(wgrad(P(p.dao), d, P(p.attn), dq, G.w_o, qwen ? nullptr : G.b_o));
-  DSF_HIP(launch_transpose(weights->w_o, d, dq, dq, P(p.woT), d, s));
   rc = bwd_gemm(EPI_STORE, N, dq, d, P(p.dao), d, P(p.woT), d, P(p.dattn), dq, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // attention over the kept tokens, RoPE turned back, into token-major dqkv
@@ -1625,7 +1627,6 @@ extern "C" int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_l
                                F(p.dvec), F(p.rope), idx, T, D.rotary_dims, P(p.dqkv), s));
   // QKV projection
   DSF_HIP(wgrad(P(p.dqkv), cq, P(p.a1), d, G.w_qkv, G.b_qkv));
-  DSF_HIP(launch_transpose(weights->w_qkv, cq, d, d, P(p.wqT), cq, s));
   rc = bwd_gemm(EPI_STORE, N, d, cq, P(p.dqkv), cq, P(p.wqT), cq, P(p.da), d, nullptr, nullptr, 0, s);
   if (rc) return rc;
   // first norm of the kept rows

@@ -260,8 +260,14 @@ hipError_t launch_wgrad(const void* p, int ldp, int M, const void* q, int ldq, i
                         const WgradScratch& ws, hipStream_t s);
 
 // ---- backward of the routed layer (kernels_bwd.hip) ----
-// out[c][r] = in[r][c], bf16 [R, C] (leading dimension ldi) to [C, ldo], ldo >= R.
-hipError_t launch_transpose(const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s);
+// out[c][r] = in[r][c], dense bf16 [R, C] to [C, R], of n matrices in one launch.
+constexpr int kTransposeMax = 4;
+struct TransposeArgs {
+  const void* in;
+  void* out;
+  int R, C;
+};
+hipError_t launch_transpose(const TransposeArgs* m, int n, hipStream_t s);
 // out[b kk + j] = (scores ? sigmoid(scores[b, idx]) : 1) * dy[b, idx[b kk + j]]
 hipError_t launch_gather_scale(const void* dy, int B, int T, int d, const int32_t* idx, int kk, const float* scores,
                                void* out, hipStream_t s);

@@ -25,68 +25,59 @@ namespace dsf {
 
 // ----------------------------------------------------------- transposes
 
-// out[c][r] = in[r][c] for r < R, c < C; out has leading dimension ldo >= R
-// and its columns R .. ldo-1 are written as zeros. (The weights, which the
-// adjoint GEMMs read along their other dimension.)
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in, int R, int C, int ldi,
-                                                        uint16_t* __restrict__ out, int ldo) {
-  __shared__ uint16_t tile[64][66];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int rr = ty; rr < 64; rr += 4) {
-    const int r = r0 + rr, c = c0 + tx;
-    tile[rr][tx] = r < R && c < C ? in[int64_t(r) * ldi + c] : uint16_t(0);
-  }
-  __syncthreads();
-  for (int cc = ty; cc < 64; cc += 4) {
-    const int c = c0 + cc, r = r0 + tx;
-    if (c < C && r < ldo) out[int64_t(c) * ldo + r] = tile[tx][cc];
-  }
-}
+// out[c][r] = in[r][c] of up to four dense matrices in one launch, a 64 x 64
+// tile per workgroup: the weights, which the adjoint GEMMs read along their
+// other dimension. R and C are multiples of 8 and the bases 16-byte aligned: a
+// thread loads 8 columns of an input row and stores 8 rows of an output row.
+// (With a launch each, 5 us apiece, of which the copying takes one.)
+struct TransposeBatch {
+  TransposeArgs m[kTransposeMax];
+  int tile0[kTransposeMax + 1], n;
+};
 
-// The same with 16-byte accesses on both sides (C, ldi and ldo multiples of
-// 8, 16-byte aligned bases): a thread loads 8 columns of an input row and
-// stores 8 rows of an output row.
-__global__ __launch_bounds__(256) void transpose_vec_kernel(const uint16_t* __restrict__ in, int R, int C, int ldi,
-                                                            uint16_t* __restrict__ out, int ldo) {
+__global__ __launch_bounds__(256) void transpose_kernel(TransposeBatch g) {
   __shared__ float tile[64][65];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  const int t = threadIdx.x, v = t & 7, q = t >> 3;  // vector index, row (column) within a pass
+  int k = 0;
+  while (k + 1 < g.n && int(blockIdx.x) >= g.tile0[k + 1]) ++k;
+  const int R = g.m[k].R, C = g.m[k].C;
+  const auto* in = (const uint16_t*)g.m[k].in;
+  auto* out = (uint16_t*)g.m[k].out;
+  const int ntc = (C + 63) / 64, t = int(blockIdx.x) - g.tile0[k];
+  const int c0 = (t % ntc) * 64, r0 = (t / ntc) * 64;
+  const int v = threadIdx.x & 7, q = threadIdx.x >> 3;  // vector index, row (column) within a pass
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int rr = q + 32 * i, r = r0 + rr, c = c0 + 8 * v;
-    float x[8];
     if (r < R && c < C) {
-      load_vec(in + int64_t(r) * ldi + c, x);
-    } else {
+      float x[8];
+      load_vec(in + int64_t(r) * C + c, x);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = 0.f;
+      for (int e = 0; e < 8; ++e) tile[rr][8 * v + e] = x[e];
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[rr][8 * v + e] = x[e];
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int cc = q + 32 * i, c = c0 + cc, r = r0 + 8 * v;
-    if (c < C && r < ldo) {
+    if (c < C && r < R) {
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = tile[8 * v + e][cc];
-      store_vec(out + int64_t(c) * ldo + r, x);
+      store_vec(out + int64_t(c) * R + r, x);
     }
   }
 }
 
-hipError_t launch_transpose(const void* in, int R, int C, int ldi, void* out, int ldo, hipStream_t s) {
-  if (R <= 0 || C <= 0) return hipSuccess;
-  const dim3 grid((C + 63) / 64, (ldo + 63) / 64);
-  const auto* i = (const uint16_t*)in;
-  auto* o = (uint16_t*)out;
-  const bool vec = C % 8 == 0 && ldi % 8 == 0 && ldo % 8 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 &&
-                   reinterpret_cast<uintptr_t>(out) % 16 == 0;
-  if (vec) transpose_vec_kernel<<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
-  else transpose_kernel<<<grid, 256, 0, s>>>(i, R, C, ldi, o, ldo);
+hipError_t launch_transpose(const TransposeArgs* m, int n, hipStream_t s) {
+  if (n > kTransposeMax) return hipErrorInvalidValue;
+  TransposeBatch g{};
+  for (g.n = 0; g.n < n; ++g.n) {
+    const TransposeArgs& t = m[g.n];
+    if (t.R <= 0 || t.C <= 0 || t.R % 8 != 0 || t.C % 8 != 0) return hipErrorInvalidValue;
+    g.m[g.n] = t;
+    g.tile0[g.n + 1] = g.tile0[g.n] + ((t.R + 63) / 64) * ((t.C + 63) / 64);
+  }
+  transpose_kernel<<<g.tile0[g.n], 256, 0, s>>>(g);
   return hipGetLastError();
 }
 
