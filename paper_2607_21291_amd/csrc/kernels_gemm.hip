@@ -1042,8 +1042,10 @@ __global__ __launch_bounds__((DmaCfg<BM, BN, WM, WN, NS, BK>::kThreads)) void ge
 template <int EPI, int BM, int BN, int WM, int WN, int NS, int BK>
 __global__ __launch_bounds__((DmaCfg<BM, BN, WM, WN, NS, BK>::kThreads)) void gemm_bf16_tail_kernel(GemmArgs g) {
   using G = DmaGemm<EPI, BM, BN, WM, WN, NS, BK>;
-  __shared__ __attribute__((aligned(1024))) char smem[G::C::kSmem];
-  __shared__ int n_seen;
+  // One LDS object: beside a second one the compiler orders every LDS read
+  // behind the DMA in flight, which then has nothing left to hide under.
+  __shared__ __attribute__((aligned(1024))) char smem[G::C::kSmem + 16];
+  int& n_seen = *reinterpret_cast<int*>(smem + G::C::kSmem);
   const int s = g.tail_s;
   const int x = int(blockIdx.x) % kXcds, m = int(blockIdx.x) / kXcds;
   const int q = m / s, p = m - q * s, t = x + kXcds * q;
@@ -1112,8 +1114,9 @@ __global__ __launch_bounds__((DmaCfg<BM, BN, WM, WN, NS, BK>::kThreads)) void ge
 template <int EPI, int BM, int BN, int WM, int WN, int NS, int BK>
 __global__ __launch_bounds__((DmaCfg<BM, BN, WM, WN, NS, BK>::kThreads)) void gemm_bf16_sk_kernel(GemmArgs g) {
   using G = DmaGemm<EPI, BM, BN, WM, WN, NS, BK>;
-  __shared__ __attribute__((aligned(1024))) char smem[G::C::kSmem];
-  __shared__ int spin_failed;
+  // one LDS object, as in the split last round
+  __shared__ __attribute__((aligned(1024))) char smem[G::C::kSmem + 16];
+  int& spin_failed = *reinterpret_cast<int*>(smem + G::C::kSmem);
   const int ntn = EPI == EPI_SWIGLU ? g.f / (BN / 2) : (g.N + BN - 1) / BN;
   const int nt = g.ntm * ntn, nk = g.K / BK, px = g.px;
   const int x = int(blockIdx.x) % kXcds, j = int(blockIdx.x) / kXcds;
@@ -1726,10 +1729,10 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
 constexpr int kRowTileCols = 256 * 128;
 static bool use_rowgemm(const GemmArgs& g) {
   if (!rowgemm_ok(g)) return false;
-  const char* e = getenv("DSF_ROWGEMM");
-  if (e && e[0] == '0') return false;
-  for (const char* n : {"DSF_GEMM_SCHEDULE", "DSF_GEMM_TILE", "DSF_GEMM_TAIL"})
-    if ((e = getenv(n)) && *e) return false;
+  for (const char* n : {"DSF_GEMM_SCHEDULE", "DSF_GEMM_TILE", "DSF_GEMM_TAIL"}) {
+    const char* e = getenv(n);
+    if (e && *e) return false;
+  }
   if (g.M <= 16) return true;
   const int cols = g.epi == EPI_SWIGLU ? 2 * g.f : g.N;
   return g.dtype == DSF_F32 || cols < kRowTileCols;

@@ -622,27 +622,6 @@ static RowProb row_prob(const GemmArgs& g) {
   return r;
 }
 
-hipError_t launch_row_tiles(const GemmArgs* p, int np, int mb, int nb, hipStream_t s) {
-  RowGemmArgs a{};
-  for (int i = 0; i < np; ++i) a.p[i] = row_prob(p[i]);
-  a.splits = 1;
-  a.mtiles = (p[0].M + 16 * mb - 1) / (16 * mb);
-  a.tiles0 = (a.p[0].nsub + nb - 1) / nb;
-  const int nt = a.tiles0 + (np > 1 ? (a.p[1].nsub + nb - 1) / nb : 0);
-  const dim3 grid(unsigned(nt) * unsigned(a.mtiles)), block(512);
-#define DSF_ROWTILES(T)                                                                                       \
-  do {                                                                                                        \
-    if (mb == 4 && nb == 4) launch_with_timing(rowgemm_kernel<T, 4, 4, 8, false, false>, grid, block, s, a);  \
-    else if (mb == 4) launch_with_timing(rowgemm_kernel<T, 4, 2, 8, false, false>, grid, block, s, a);        \
-    else if (nb == 4) launch_with_timing(rowgemm_kernel<T, 2, 4, 8, false, false>, grid, block, s, a);        \
-    else launch_with_timing(rowgemm_kernel<T, 2, 2, 8, false, false>, grid, block, s, a);                     \
-  } while (0)
-  if (p[0].dtype == DSF_BF16) DSF_ROWTILES(uint16_t);
-  else DSF_ROWTILES(float);
-#undef DSF_ROWTILES
-  return hipGetLastError();
-}
-
 // fp32 projections of more rows, on the fp32 matrix cores: the same kernel
 // over tiles of 16 MB x 16 NB outputs, K split between the tile's eight waves.
 // One MFMA step of a 64 x 64 tile is 2048 cycles of a SIMD's matrix core for
@@ -658,7 +637,17 @@ static hipError_t launch_row_tiles_f32(const GemmArgs* p, int np, hipStream_t s)
   auto tiles = [&](int mb, int nb) { return int64_t((M + 16 * mb - 1) / (16 * mb)) * ((nsub + nb - 1) / nb); };
   const int mb = tiles(4, 4) >= kRowTilesF32 ? 4 : 2;
   const int nb = mb == 4 || tiles(2, 4) >= kRowTilesF32 ? 4 : 2;
-  return launch_row_tiles(p, np, mb, nb, s);
+  RowGemmArgs a{};
+  for (int i = 0; i < np; ++i) a.p[i] = row_prob(p[i]);
+  a.splits = 1;
+  a.mtiles = (M + 16 * mb - 1) / (16 * mb);
+  a.tiles0 = (a.p[0].nsub + nb - 1) / nb;
+  const int nt = a.tiles0 + (np > 1 ? (a.p[1].nsub + nb - 1) / nb : 0);
+  const dim3 grid(unsigned(nt) * unsigned(a.mtiles)), block(512);
+  if (mb == 4) launch_with_timing(rowgemm_kernel<float, 4, 4, 8, false, false>, grid, block, s, a);
+  else if (nb == 4) launch_with_timing(rowgemm_kernel<float, 2, 4, 8, false, false>, grid, block, s, a);
+  else launch_with_timing(rowgemm_kernel<float, 2, 2, 8, false, false>, grid, block, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, const RouterRows* router,
