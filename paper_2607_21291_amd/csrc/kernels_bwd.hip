@@ -653,9 +653,10 @@ __global__ __launch_bounds__(256, HD == 64 && G == 2 ? 3 : 1) void attn_bwd_dq_k
 // own keys, and
 //   dV^T[c][key] += sum_queries dout^T[c][query] P[query][key],
 //   dK^T[c][key] += scale * sum_queries Q^T[c][query] dS[query][key].
-// Each item's lse and D are loaded by wave 0 one item ahead and published in
-// LDS with the item's tiles. Queries past the end are zero rows of Q and dout
-// (finite probabilities times zeros); keys past it are not stored.
+// Each item's lse and D come with its tiles, by DMA (as register loads their
+// arrival was waited for, and with it the DMA in flight). Queries past the
+// end are zero rows of Q and dout (finite probabilities times zeros); keys
+// past it are not stored.
 template <int HD, int G>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ K,
@@ -666,8 +667,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
                                                            int nbkv, RopeOut ro) {
   using A = AttnTile<HD>;
   constexpr int NS = HD / 32, NC = HD / 16;
-  __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes];  // stage: Q tile, then dout tile
-  __shared__ __attribute__((aligned(16))) float lse_s[2][kAB], dvec_s[2][kAB];
+  // stage: Q tile, then dout tile; then per stage lse and D of its queries.
+  // One object: with several, the compiler orders every LDS read behind the
+  // DMA in flight.
+  __shared__ __attribute__((aligned(16))) char smem[2 * 2 * A::kTileBytes + 2 * 2 * kAB * 4];
+  float* stats = reinterpret_cast<float*>(smem + 2 * 2 * A::kTileBytes);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, grp = lane >> 4;
   const int kb = int(blockIdx.x) / nbkv, bkv = int(blockIdx.x) % nbkv;
@@ -687,16 +691,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
     attn_tile_dma<HD>(Q + bh * n * HD, HD, qb * kAB, n, st, wave, lane);
     attn_tile_dma<HD>(dO + int64_t(b) * n * (int64_t(Hq) * HD) + int64_t(h) * HD, int64_t(Hq) * HD, qb * kAB, n,
                       st + A::kTileBytes, wave, lane);
-  };
-  float pl = 0.f, pd = 0.f;  // wave 0, lane = query of the next item: its lse (base 2) and D
-  auto fetch_stats = [&](int i) {
-    const int h = kvh * R + i / nq, qq = (qb0 + i % nq) * kAB + lane;
-    const int64_t bh = int64_t(b) * Hq + h;
-    pl = qq < n ? lse[bh * n + qq] * kLog2e : 0.f;
-    pd = qq < n ? dvec[bh * n + qq] : 0.f;
+    if (wave == 0) {  // lane: query of the item; zeros past the end
+      const auto lr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lse + bh * n), (short)0, n * 4, 0x00020000);
+      const auto dr =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dvec + bh * n), (short)0, n * 4, 0x00020000);
+      const int voff = (qb * kAB + lane) * 4;
+      float* sp = stats + (i & 1) * 2 * kAB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(lr, (__attribute__((address_space(3))) void*)(sp), 4, voff, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(dr, (__attribute__((address_space(3))) void*)(sp + kAB), 4, voff, 0, 0,
+                                               0);
+    }
   };
   issue(0);
-  if (wave == 0) fetch_stats(0);
 
   bf16x8 kf[G][NS], vf[G][NS];
 #pragma unroll
@@ -709,6 +715,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
         kv = *reinterpret_cast<const u32x4*>(Kh + int64_t(key) * HD + 32 * s + 8 * grp);
         vv = *reinterpret_cast<const u32x4*>(Vh + int64_t(key) * HD + 32 * s + 8 * grp);
       }
+      // wait for them here: left to their first use, the wait would sit in the
+      // loop, behind the DMA of the next item
+      asm volatile("" : "+v"(kv), "+v"(vv));
       kf[g][s] = __builtin_bit_cast(bf16x8, kv);
       vf[g][s] = __builtin_bit_cast(bf16x8, vv);
     }
@@ -721,16 +730,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
     for (int cb = 0; cb < NC; ++cb) adk[g][cb] = adv[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int i = 0; i < items; ++i) {
     const int slot = i & 1;
-    if (wave == 0) {  // slot's previous readers finished item i - 2 before the last barrier
-      lse_s[slot][lane] = pl;
-      dvec_s[slot][lane] = pd;
-    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's share of item i's tiles has landed
     __syncthreads();                                   // ... and every wave's; item i - 1 is retired
-    if (i + 1 < items) {
-      issue(i + 1);
-      if (wave == 0) fetch_stats(i + 1);
-    }
+    if (i + 1 < items) issue(i + 1);
     const int q0 = (qb0 + i % nq) * kAB;
     if (q0 + kAB - 1 < kw) continue;  // every query before the wave's keys
     const bool edge = q0 < kw + 16 * G - 1;  // some of the block's queries come before some of the keys
@@ -756,8 +758,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
             dp[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, vf[g][s], dp[g], 0, 0, 0);
           }
         }
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&lse_s[slot][16 * blk + 4 * grp]);
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&dvec_s[slot][16 * blk + 4 * grp]);
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(stats + slot * 2 * kAB + 16 * blk + 4 * grp) * kLog2e;
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(stats + slot * 2 * kAB + kAB + 16 * blk + 4 * grp);
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
