@@ -47,6 +47,27 @@ struct WgArgs {
   int ntn, nt, splits;
 };
 
+// 16-byte chunk c of row r lies at chunk c ^ wg_swz(r): the sixteen rows of a
+// transpose load, 32 bytes each, then cover the 64 banks twice, the minimum
+// (with the attention tiles' swizzle half of the LDS cycles were conflicts:
+// 84 against 81 us for 768 x 3072 outputs over 12504 tokens).
+__device__ __forceinline__ int wg_swz(int r) { return (r & 7) << 1; }
+
+// LDS byte addresses of the transpose loads of a subtile (the lane's part as
+// in AttnTrans, with this swizzle).
+struct WgTrans {
+  uint32_t base, u;
+  __device__ __forceinline__ explicit WgTrans(int lane) {
+    const int row = 4 * (lane >> 4) + ((lane >> 2) & 3);
+    base = uint32_t(row * kWgSub * 2 + (lane & 1) * 8);
+    u = uint32_t(((lane & 3) >> 1) ^ wg_swz(row));
+  }
+  __device__ __forceinline__ uint32_t addr(const char* tile, int blk) const {
+    return uint32_t(size_t((__attribute__((address_space(3))) const char*)(tile))) + base +
+           ((uint32_t(2 * blk) ^ u) * 16);
+  }
+};
+
 // Tokens r0 .. r0 + 63, columns c0 .. c0 + 127 of src [T, ld] into a subtile.
 // The resource ends with the matrix, so rows past T land as zeros; columns
 // past ld hold the next row's values and only reach outputs that are dropped.
@@ -61,7 +82,7 @@ __device__ __forceinline__ void wg_dma(const uint16_t* src, int ld, int T, int r
   for (int e = 0; e < A::kDmaPerWave; ++e) {
     const int byte = 1024 * (wave * A::kDmaPerWave + e) + 16 * lane;
     const int r = byte / A::kRowBytes, c = (byte % A::kRowBytes) / 16;
-    const uint32_t voff = uint32_t(r) * uint32_t(ld) * 2u + uint32_t((c ^ (r & A::kSwz)) * 16);
+    const uint32_t voff = uint32_t(r) * uint32_t(ld) * 2u + uint32_t((c ^ wg_swz(r)) * 16);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         rsrc, (__attribute__((address_space(3))) void*)(lds + 1024 * (wave * A::kDmaPerWave + e)), 16, int(voff), 0,
         0, 0);
@@ -141,7 +162,7 @@ __global__ __launch_bounds__(LARGE ? 512 : 256, 2) void wgrad_kernel(WgArgs g) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
 
-  const AttnTrans<kWgSub> tr(lane);
+  const WgTrans tr(lane);
   // subtile and first 16-column block of this wave's rows and columns
   const int ps = (wm * 64) / kWgSub, pb = (wm * 4) % 8, qs = (wn * WN) / kWgSub, qb = (wn * NI) % 8;
   if (kb < ke) issue(kb);
