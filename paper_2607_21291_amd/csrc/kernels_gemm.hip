@@ -11,8 +11,9 @@
 // back row-wise, so every epilogue (RoPE pairs dims i and i + R/2; SwiGLU
 // pairs gate and up columns) sees whole rows and stores 16-byte vectors.
 //
-// fp32 path: a plain LDS-tiled FMA kernel (32 x 128 tiles) that shares the
-// epilogue. It exists for the fp32 workload and is not tuned.
+// fp32 path: the row tiles of kernels_rowgemm.hip on the fp32 matrix cores; a
+// plain LDS-tiled FMA kernel (32 x 128 tiles) that shares the epilogue takes
+// reductions and rotary dims that are no multiple of 16.
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
@@ -580,7 +581,7 @@ constexpr int kSkMinK = 32;    // k-iterations per tile below which the partial 
 constexpr int kTailMaxSplit = 4;
 constexpr int kTailMinK = 8;
 // Grids of at most one workgroup per CU (choose_deep): the same limits.
-constexpr int kDeepMaxSplit = 4, kDeepMinSplit = 3;
+constexpr int kDeepMaxSplit = 4;
 constexpr int kDeepMinK = 8;
 constexpr int kGroupM = 4;      // tile rows per band of the grouped tile order
 constexpr int kGroupMinCols = 8;  // below this many tile columns row-major order is already compact
@@ -1332,6 +1333,33 @@ static Schedule choose_schedule(int nt, int nk, int slots) {
   return {0, 0};
 }
 
+// Whether a whole grid of nt tiles, each cut along K into s pieces, has all its
+// pieces resident at one per CU. The pieces of a tile stay on one XCD, so each
+// XCD has to hold its share (84 tiles in three pieces leave four XCDs with 33
+// workgroups for 32 CUs, and take longer than in two: 122 against 97 us).
+static bool split_fits(int nt, int s, int nk, int cus, int beside, int part_slots) {
+  return s * ((nt + kXcds - 1) / kXcds) <= (cus - beside) / kXcds && nt * (s - 1) <= part_slots && nk / s >= kDeepMinK;
+}
+
+// A grid of large tiles that leaves CUs idle, every tile cut along K. Measured
+// per launch, warm: 1.0-1.25 us per k-tile of a piece, growing with the share
+// of the CUs in use, and 32 us (Qwen2.5-7B down projection: 42 tiles in four
+// pieces 119 us, 84 in two 204; unsplit 331). Returns the pieces per tile, 1:
+// no split worth it.
+static double large_split_us(int nt, int nk, int s, int cus) {
+  return (1.0 + 0.25 * nt * s / cus) * nk / s + 32.0;
+}
+static int choose_large_split(int nt, int nk, int cus, int part_slots) {
+  int best = 1;
+  double t = 1.08 * nk + 12.0;  // unsplit
+  for (int s = 2; s <= kTailMaxSplit; ++s)
+    if (split_fits(nt, s, nk, cus, 0, part_slots) && large_split_us(nt, nk, s, cus) < t) {
+      best = s;
+      t = large_split_us(nt, nk, s, cus);
+    }
+  return best;
+}
+
 // Split last round of a one-tile-per-workgroup grid of large tiles: with nt
 // tiles on P resident workgroups, the last nt mod P tiles would run alone in
 // a last round that leaves most CUs idle (the 3584-wide O and down
@@ -1349,6 +1377,10 @@ static TailSplit choose_tail(int nt, int nk, int slots, int part_slots, bool ava
   if (!avail || (e && e[0] == '0')) return {0, 1};
   const bool force = e && !strcmp(e, "force");
   const int P = force ? kXcds : slots;
+  if (P > 0 && nt <= P && !force) {
+    const int sp = choose_large_split(nt, nk, P, part_slots);
+    return {sp > 1 ? nt : 0, sp};
+  }
   if (P <= 0 || nt <= P) return {0, 1};
   const int r = nt % P;
   if (r == 0) return {0, 1};
@@ -1358,23 +1390,27 @@ static TailSplit choose_tail(int nt, int nk, int slots, int part_slots, bool ava
 }
 
 // A grid of small tiles that leaves every CU at most one workgroup. With the
-// two-stage ring such a workgroup takes 0.7-0.9 us per k-tile whatever the
-// width of the projection, the latency of its loads (Qwen2.5-7B down
-// projection of 70-900 rows, 296 k-tiles: 257-289 us); four stages keep three
-// tiles in flight (172-206 us), and while three or four workgroups per tile
-// fit the CUs, its k-tiles are split between them (gemm_bf16_tail_kernel;
-// 113 us at 70-150 rows; two pieces lost to the unsplit ring at every width
-// tried, 96-128 tiles). beside: tiles of a launch that runs at the same time
-// on another stream. Returns the pieces per tile, 0: not such a grid.
-// DSF_GEMM_TAIL=0 (read at every launch) turns the split off.
+// two-stage ring such a workgroup takes 0.7-0.9 us per k-tile, the latency of
+// its loads; four stages keep three tiles in flight, and while up to four
+// workgroups per tile fit the CUs, its k-tiles are split between them
+// (gemm_bf16_tail_kernel). Measured per launch, warm: 0.55 us per k-tile of a
+// piece and 7 us, 17 with the hand-over (Qwen2.5-7B down projection, 296
+// k-tiles, 307 rows: 198 us with two stages, 158 with four, 97 in two pieces;
+// Qwen2.5-0.5B, 76 k-tiles, 307 rows: 54, 47 and in four pieces 26; below about
+// 30 k-tiles the hand-over costs more than it saves). beside: tiles of a launch
+// that runs at the same time on another stream. Returns the pieces per tile, 0:
+// not such a grid. DSF_GEMM_TAIL=0 (read at every launch) turns the split off.
+static double deep_us(int nk, int s) { return 0.55 * nk / s + (s > 1 ? 17.0 : 7.0); }
 static int choose_deep(int nt, int nk, int cus, int beside, int part_slots, bool avail) {
   if (schedule_override() || nt + beside > cus) return 0;
   const char* e = getenv("DSF_GEMM_TAIL");
   if (!avail || (e && e[0] == '0')) return 1;
-  for (int sp = kDeepMaxSplit; sp >= kDeepMinSplit; --sp)
-    if (sp * nt + beside <= cus && nt * (sp - 1) <= part_slots && nk / sp >= kDeepMinK) return sp;
-  return 1;
+  int best = 1;
+  for (int s = 2; s <= kDeepMaxSplit; ++s)
+    if (split_fits(nt, s, nk, cus, beside, part_slots) && deep_us(nk, s) < deep_us(nk, best)) best = s;
+  return best;
 }
+
 
 // The DMA kernels address each operand through a buffer resource with a
 // 32-bit byte range and 32-bit offsets: every operand, padded to whole tiles,
@@ -1574,8 +1610,11 @@ static void skinny_split(int ntn, int K, int* splits, int* kc) {
 // sweep the rule's choice is within 9 % of the better size, and it replaces
 // one that took the large tiles from 320 of them: the Qwen2.5-1.5B down
 // projection of 7000-9800 rows (168-234 large tiles) 276-295 -> 217-232 us, the
-// NeoX-1.4B one 301 -> 240, Qwen2.5-7B QKV at 2718 rows 108 -> 97. Grids that
-// leave each CU at most one small workgroup keep the small tiles (choose_deep).
+// NeoX-1.4B one 301 -> 240, Qwen2.5-7B QKV at 2718 rows 108 -> 97.
+// Where both grids fit one round, the large tiles are taken if in pieces
+// (choose_large_split) they beat the small ones by a tenth: Qwen2.5-7B down
+// projection of 640 rows 161 -> 119 us, 1500 rows 240 -> 204; shorter
+// reductions keep the small tiles (NeoX-160M, 4096 rows: 40 against 50).
 // The NeoX QKV and up projections, which share the chip on two streams, take
 // one size for both, from the sum of their tiles (GemmArgs::tile_hint): a
 // 256 x 256 workgroup takes most of a CU's LDS and cannot share the CU with a
@@ -1602,7 +1641,17 @@ static double large_tile_us(int64_t nt, int nk, int cus, bool tail) {
 }
 static bool large_tiles_win(int64_t nt_small, int64_t nt_large, int nk, bool tail, bool stream_k, bool wide) {
   const int cus = device_cus();
-  if (nt_small <= cus || cus <= 0) return false;
+  if (cus <= 0) return false;
+  if (nt_large <= cus && tail) {
+    // both grids within a round: large tiles only in pieces, and by a margin
+    const int slots = kSkMaxSlots / 2, sp = choose_large_split(int(nt_large), nk, cus, slots);
+    if (sp > 1) {
+      const int sd = nt_small <= cus ? choose_deep(int(nt_small), nk, cus, 0, slots, true) : 0;
+      const double small = sd > 0 ? deep_us(nk, sd) : 0.8 * nk + 6.0;
+      return large_split_us(int(nt_large), nk, sp, cus) < 0.9 * small;
+    }
+  }
+  if (nt_small <= cus) return false;
   return large_tile_us(nt_large, nk, cus, tail) < small_tile_us(nt_small, nk, cus, stream_k, wide);
 }
 template <class TC>
@@ -1711,8 +1760,10 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
         ga.tail_r = ts.r;
         ga.tail_s = ts.s;
         ga.spin_limit = spin_limit();
-        launch_timed(fn, dim3(nt - ts.r), dim3(Cfg::kThreads), s, ga);
-        timing_continue();
+        if (nt > ts.r) {
+          launch_timed(fn, dim3(nt - ts.r), dim3(Cfg::kThreads), s, ga);
+          timing_continue();
+        }
         launch_timed(gemm_bf16_tail_kernel<EPI, BM, BN, WM, WN, NS, BK>,
                      dim3(kXcds * ts.s * ((ts.r + kXcds - 1) / kXcds)), dim3(Cfg::kThreads), s, ga);
         return;

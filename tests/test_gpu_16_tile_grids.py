@@ -1,18 +1,19 @@
 """Grids of bf16 projection tiles around the sizes where their form changes:
 at most one workgroup per CU (the four-stage ring), with reductions long
-enough to be split between three or four workgroups per tile or just too
-short, one row past a tile and past the chip, and a NeoX layer whose up
-projection shares the chip with QKV. Each layer is held to the oracle at the
-bf16 tolerance. Without the split, the ring multiplies in the order of the
-two-stage loop, so its results are bitwise those of one tile per workgroup;
-the split adds its pieces in a fixed order, so repeated runs are equal.
+enough to be split between two to four workgroups per tile or too short, one
+row past a tile and past the chip, a NeoX layer whose up projection shares the
+chip with QKV, and large tiles cut in pieces. Each layer is held to the oracle
+or to the unsplit grid at the bf16 tolerance. Without the split, the ring
+multiplies in the order of the two-stage loop, so its results are bitwise
+those of one tile per workgroup; the split adds its pieces in a fixed order,
+so repeated runs are equal.
 """
 import pytest
 import torch
 
 import synthetic as S
 
-from gpu_util import announce, check_layer, run_layer, workload
+from gpu_util import TOL, announce, check_layer, rel_inf, run_layer, to_np, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -24,12 +25,13 @@ def _w(block, d, hq, hkv, hd, f, B, T):
 
 
 CASES = [
-    (S.QWEN, 512, 8, 2, 64, 1472, 1, 140, 127),   # down: 23 k-tiles, too few for three pieces
-    (S.QWEN, 512, 8, 2, 64, 1536, 1, 140, 128),   # 24: three pieces
+    (S.QWEN, 512, 8, 2, 64, 1472, 1, 140, 127),   # down: 23 k-tiles, one piece
+    (S.QWEN, 512, 8, 2, 64, 1536, 1, 140, 128),   # 24
     (S.QWEN, 512, 8, 2, 64, 2112, 1, 140, 129),   # 33: four uneven pieces
     (S.QWEN, 640, 5, 1, 128, 2560, 2, 140, 129),  # 15 tiles: a padded last group of the split grid
     (S.QWEN, 512, 8, 2, 64, 2048, 1, 1030, 1024), # gate|up: 256 tiles, one per CU
     (S.QWEN, 512, 8, 2, 64, 2048, 1, 1030, 1025), # 288: past it
+    (S.QWEN, 1536, 12, 2, 128, 2560, 1, 800, 769),  # down: 84 tiles, which fit in two pieces but not in three
     (S.NEOX, 512, 8, 8, 64, 2048, 1, 140, 100),   # up beside QKV
     (S.NEOX, 512, 8, 8, 64, 2048, 1, 1200, 1153), # up and QKV: 280 tiles together
     (S.NEOX, 1536, 24, 24, 64, 2048, 1, 140, 129),  # reductions of 24 and 56 k-tiles
@@ -67,3 +69,36 @@ def test_large_tile_rule(dev, B, T, k):
     check_layer(w, W, x, y, scores, idx, k, sample=[B - 1])
     y2, _, _ = run_layer(dev, w, W, x, k)
     assert torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("d,f,T,k", [(512, 8192, 300, 299), (1792, 2560, 2600, 2561), (2560, 4096, 2500, 2496)])
+def test_large_tiles_in_pieces(dev, monkeypatch, d, f, T, k):
+    # large tiles that leave CUs idle, forced: the down projection in four
+    # pieces (4 tiles), three (77) and two (100), against the unsplit grid
+    w = _w(S.QWEN, d, 8, 2, 64, f, 1, T)
+    W = S.layer_weights(w, 0)
+    x = S.hidden_states(w)
+    monkeypatch.setenv("DSF_GEMM_TILE", "large")
+    announce(f"large tiles in pieces d={d} f={f} k={k}")
+    y, scores, idx = run_layer(dev, w, W, x, k)
+    if d == 512:
+        check_layer(w, W, x, y, scores, idx, k)
+    y2, _, _ = run_layer(dev, w, W, x, k)
+    assert torch.equal(y, y2)
+    monkeypatch.setenv("DSF_GEMM_TAIL", "0")
+    yu, _, _ = run_layer(dev, w, W, x, k)
+    assert rel_inf(to_np(y) - to_np(x), to_np(yu) - to_np(x)) < TOL[w.dtype]
+    assert not torch.equal(y, yu)  # the split ran (it rounds differently)
+
+
+def test_large_tiles_chosen_in_pieces(dev, monkeypatch):
+    # 1300 Qwen2.5-1.5B rows: the rule takes large tiles in pieces for the down projection
+    w = S.WORKLOADS["qwen15b"].replace(batch=1, seq=1400, n_layers=1)
+    W = S.layer_weights(w, 0)
+    x = S.hidden_states(w)
+    announce("large tiles chosen in pieces")
+    y, _, idx = run_layer(dev, w, W, x, 1300)
+    monkeypatch.setenv("DSF_GEMM_TILE", "small")
+    ys, _, idxs = run_layer(dev, w, W, x, 1300)
+    assert torch.equal(idx, idxs)
+    assert rel_inf(to_np(y) - to_np(x), to_np(ys) - to_np(x)) < TOL[w.dtype]
