@@ -286,16 +286,17 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * projections, which run side by side, take one size for both); the
  * environment variable DSF_GEMM_TILE=small or =large, read at every launch,
  * forces one size. A grid that gives each CU at most one 128 x 128 tile
- * keeps four LDS stages in flight and, while three or four workgroups per
- * tile still fit the CUs and the reduction is long enough, cuts each tile
- * along K into as many pieces. With 256 x 256 tiles each workgroup runs one
- * tile; for the forward projections other than the SwiGLU gate|up (bf16, on
- * the call's workspace), when the tiles would end in a last round at most
- * half as many as the resident workgroups, those last tiles go to a second
- * launch that cuts each along K into 2-4 pieces. In both, the last piece
- * adds the others' partial sums in a fixed order (deterministic; rounds
- * differently from the unsplit grid), and DSF_GEMM_TAIL=0, read at every
- * launch, turns the split off. With more 128 x 128 tiles than resident
+ * keeps four LDS stages in flight; short reductions (other than SwiGLU's and
+ * those of 128-wide heads' QKV) then take 64 x 64 tiles, long ones are cut
+ * along K into up to four pieces per tile while those fit the CUs. With
+ * 256 x 256 tiles each workgroup runs one tile; for the forward projections
+ * other than the SwiGLU gate|up (bf16, on the call's workspace), when the
+ * tiles would end in a last round at most half as many as the resident
+ * workgroups, those last tiles go to a second launch that cuts each along K
+ * into 2-4 pieces, and a grid that leaves CUs idle may cut every tile so. In
+ * all of these the last piece adds the others' partial sums in a fixed order
+ * (deterministic; rounds differently from the unsplit grid), and
+ * DSF_GEMM_TAIL=0, read at every launch, turns the split off. With more 128 x 128 tiles than resident
  * workgroups, one output tile per workgroup; or a persistent grid taking
  * whole tiles (same arithmetic); or, when that would end in a short last
  * round of tiles on a long reduction, a stream-K grid (workgroups split the
@@ -308,9 +309,8 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * Call status. The first 4 bytes of the workspace hold a status word that
  * each call of dsf_sparse_block_forward, dsf_stack_forward,
  * dsf_stack_prefill, dsf_align_stack_forward and dsf_sparse_block_backward
- * clears at its start and that
- * its kernels OR bits into; read it with dsf_workspace_status once the call's
- * work is enqueued. A call with nothing to do (B, T or k zero), which
+ * clears at its start and that its kernels OR bits into; read it with
+ * dsf_workspace_status once the call's work is enqueued. A call with nothing to do (B, T or k zero), which
  * launches nothing, leaves the word as it was. DSF_WS_STATUS_SK_TIMEOUT: a
  * stream-K workgroup, or the last piece of a split tile, that must add an
  * earlier workgroup's partial sum waits for it with a bounded spin of

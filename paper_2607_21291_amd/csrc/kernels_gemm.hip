@@ -566,6 +566,11 @@ struct TileSmall {
 struct TileDeep {
   static constexpr int BM = 128, BN = 128, WM = 64, WN = 64, NS = 4, BK = 64;
 };
+// Quarter tiles for such grids with short reductions, two workgroups per CU
+// (tiny_us).
+struct TileTiny {
+  static constexpr int BM = 64, BN = 64, WM = 32, WN = 32, NS = 4, BK = 64;
+};
 struct TileLarge {
   static constexpr int BM = 256, BN = 256, WM = 64, WN = 128, NS = 2, BK = 64;
 };
@@ -1389,6 +1394,20 @@ static TailSplit choose_tail(int nt, int nk, int slots, int part_slots, bool ava
   return {0, 1};
 }
 
+// 64 x 64 tiles: a quarter of the products per barrier and per LDS fill, and
+// four times the workgroups. Measured per launch, warm: 6 us and 0.31 us per
+// k-tile up to one workgroup per CU, 0.45 at two. 307 rows of 896-deep
+// reductions 15 -> 10 us, 1536-deep ones 20 -> 13 us; from about 50 k-tiles the
+// split 128 x 128 tiles win (4864-deep, 307 rows: 26 against 29). Not for SwiGLU,
+// whose gate and up columns make its grids wide, nor for heads of 128, whose
+// rotary pairs do not fit a tile.
+static double tiny_us(int nt, int nk, int cus) { return 6.0 + (nt <= cus ? 0.31 : 0.45) * nk; }
+template <int EPI>
+static bool tiny_ok(const GemmArgs& g) {
+  const char* e = getenv("DSF_GEMM_TILE");  // forced sizes are 128 and 256
+  return !(e && *e) && !(EPI == EPI_QKV_ROPE && g.hd > TileTiny::BN);
+}
+
 // A grid of small tiles that leaves every CU at most one workgroup. With the
 // two-stage ring such a workgroup takes 0.7-0.9 us per k-tile, the latency of
 // its loads; four stages keep three tiles in flight, and while up to four
@@ -1703,8 +1722,19 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
       const int nt = ntn * ga.ntm, cus = resident_slots<std::integral_constant<int, 96 + EPI>>((const void*)fn, Cfg::kThreads);
       const int sp = choose_deep(nt, g.K / BK, cus, g.beside, std::min(kPartSlots, gemm_flag_count()), g.part && g.flags);
       if (sp > 0) {
-        ga.ntn = ntn;
         ga.group_m = 0;
+        if constexpr (EPI != EPI_SWIGLU) {
+          using TT = TileTiny;
+          const int tm = (g.M + TT::BM - 1) / TT::BM, tn = (g.N + TT::BN - 1) / TT::BN, all = tm * tn + 4 * g.beside;
+          if (tiny_ok<EPI>(g) && all <= 2 * cus && tiny_us(all, g.K / BK, cus) < 0.95 * deep_us(g.K / BK, sp)) {
+            ga.ntm = tm;
+            ga.ntn = tn;
+            launch_timed(gemm_bf16_dma_kernel<EPI, TT::BM, TT::BN, TT::WM, TT::WN, TT::NS, TT::BK>, dim3(tm * tn),
+                         dim3(Cfg::kThreads), s, ga);
+            return;
+          }
+        }
+        ga.ntn = ntn;
         if constexpr (EPI < EPI_STORE) {
           if (sp > 1) {
             ga.tail0 = 0;

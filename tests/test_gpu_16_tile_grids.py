@@ -32,6 +32,8 @@ CASES = [
     (S.QWEN, 512, 8, 2, 64, 2048, 1, 1030, 1024), # gate|up: 256 tiles, one per CU
     (S.QWEN, 512, 8, 2, 64, 2048, 1, 1030, 1025), # 288: past it
     (S.QWEN, 1536, 12, 2, 128, 2560, 1, 800, 769),  # down: 84 tiles, which fit in two pieces but not in three
+    (S.QWEN, 576, 3, 1, 32, 640, 1, 70, 65),      # 64 x 64 tiles: one row past a tile, half a tile of columns
+    (S.QWEN, 1024, 16, 4, 64, 1024, 1, 2000, 1985),  # o: 497 of them, two per CU
     (S.NEOX, 512, 8, 8, 64, 2048, 1, 140, 100),   # up beside QKV
     (S.NEOX, 512, 8, 8, 64, 2048, 1, 1200, 1153), # up and QKV: 280 tiles together
     (S.NEOX, 1536, 24, 24, 64, 2048, 1, 140, 129),  # reductions of 24 and 56 k-tiles
