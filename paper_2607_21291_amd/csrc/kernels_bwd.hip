@@ -1,19 +1,16 @@
 // Backward of the routed layer (the training side of Section 3.4) on gfx950:
 // the kernels of the block's adjoint on the kept rows that are not projection
-// GEMMs (those run on the forward's GEMM kernels with backward epilogues).
+// GEMMs (those run on the forward's GEMM kernels with backward epilogues) nor
+// weight gradients (kernels_wgrad.hip).
 //
-//   - transposes of [rows, cols] bf16 matrices (weights, and activations
-//     whose token dimension becomes the reduction of a weight gradient),
-//     optionally applying the forward activation on the way (GELU of the up
-//     projection, or SiLU(gate) * up);
-//   - column sums in a fixed order (bias and norm-gain gradients);
+//   - transposes of the weights;
 //   - gather of the output gradient at the kept rows, scaled by the gate;
-//   - LayerNorm / RMSNorm adjoints of one row per wavefront;
-//   - the RoPE adjoint with the head-major -> token-major relayout of q/k/v;
+//   - LayerNorm / RMSNorm adjoints with the gradients of gain and bias;
 //   - causal attention backward over the kept tokens in two passes, both on
 //     v_mfma_f32_16x16x32_bf16 and both deterministic (no atomics): one pass
 //     per query block for dQ (and the softmax statistics), one per key block
 //     for dK and dV, which adds the query heads of a GQA group in order;
+//     both turn RoPE back and write token-major rows;
 //   - the final scatter: dx = dy, plus the block's gradient at the kept rows.
 #include <hip/hip_ext.h>
 
