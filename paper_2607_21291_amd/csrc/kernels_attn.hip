@@ -426,7 +426,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
       float sum = 0.f;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        const float p = in[kb][i] ? expf(sc[kb][i] - mn) : 0.f;
+        // a score of -inf weighs nothing, also beside no other score (mn = -inf)
+        const float p = in[kb][i] && sc[kb][i] != -INFINITY ? expf(sc[kb][i] - mn) : 0.f;
         sum += p;
         ps[w][4 * grp + i][16 * kb + r16] = p;
       }

@@ -83,6 +83,27 @@ def test_attention_future_values_do_not_leak(dev, bad):
     assert torch.equal(o[~hit], ref.cpu().reshape(n, 2, hd)[~hit])
 
 
+@pytest.mark.parametrize("key", [32, 37, 64])
+def test_attention_infinitely_low_scores_weigh_nothing(dev, key):
+    # a key whose score is -inf for every query: the first or only visible key
+    # of a wave's tile for some of them
+    n, hd = 70, 64
+    g = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(1, 1, n, hd, generator=g) for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k[0, 0, key, 0] = -float("inf")
+    out = torch.empty(1, n, hd, device=dev)
+    announce(f"fp32 attention with scores of -inf at key {key}")
+    P.attention_forward(q.to(dev), k.to(dev), v.to(dev), out)
+    s = to_np(q[0, 0]) @ to_np(k[0, 0]).T / np.sqrt(hd)
+    s[np.triu_indices(n, 1)] = -np.inf
+    e = np.exp(s - s.max(1, keepdims=True))
+    ref = (e / e.sum(1, keepdims=True)) @ to_np(v[0, 0])
+    # the bound of test_attention, with the largest finite score
+    smax = np.max(np.abs(s[np.isfinite(s)])) * hd
+    assert np.max(np.abs(to_np(out[0]) - ref)) < U32 * (2 * smax * (hd + 4) + n + 8) * np.max(np.abs(to_np(v)))
+
+
 @pytest.mark.parametrize("d_r", [16, 32, 48, 64])
 @pytest.mark.parametrize("n,d", [(1, 128), (16, 136), (17, 768), (100, 8)])
 def test_router(dev, n, d, d_r):
