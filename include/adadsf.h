@@ -276,7 +276,8 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * records too). There is one such stream per device and host thread,
  * created by the thread's first call and destroyed with its events when the
  * thread exits. DSF_SINGLE_STREAM=1, read at every call, keeps all work on
- * the caller's stream (results are bitwise the same).
+ * the caller's stream, with the grids of two streams (results are bitwise
+ * the same); that projection is never cut along K.
  *
  * Projection schedule. Up to 64 rows (kept tokens of all sequences), a
  * projection runs on the few-row kernel, which streams the weights; the

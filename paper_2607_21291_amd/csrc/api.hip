@@ -730,9 +730,11 @@ int run_layer(const Ctx& c, const dsf_layer_weights* W, void* x, int k, bool den
   g.idx = idx;
   // NeoX: the FFN up projection reads only LN2 of the kept rows, so it runs
   // on the second stream beside QKV and attention, launched first so that
-  // their workgroups fill the CU slots it leaves (never stream-K there: the
+  // their workgroups fill the CU slots it leaves (never cut along K: the
   // partial-sum workspace belongs to the main stream's GEMMs). Measured:
   // 3.59 against 3.64 ms per neox160m step; forking after QKV gained nothing.
+  // On one stream both projections keep the grids they have on two, so that
+  // the results are the same bits.
   hipStream_t us = c.s;
   if (!qwen && c.aux) {
     DSF_HIP(hipEventRecord(c.aux->fork, c.s));
@@ -745,14 +747,13 @@ int run_layer(const Ctx& c, const dsf_layer_weights* W, void* x, int k, bool den
   if (!qwen) {  // FFN up + GELU on LN2 of the kept rows
     GemmArgs u = g;
     u.tile_hint = pair_hint;
-    u.beside = us != c.s ? tiles128(dq + 2 * dkv) : 0;
+    u.beside = tiles128(dq + 2 * dkv);
     u.M = M; u.N = f; u.K = d; u.K1 = d;
     u.a = na.out2; u.lda = d;
     u.b = W->w_up; u.ldb = d;
     u.epi = EPI_BIAS_GELU; u.bias = W->b_up;
     u.out = at<char>(c, c.plan.act); u.ldo = f;
     TimedScope ts(DSF_KIND_GEMM_UP, us, true);
-    if (us == c.s) use_stream_k(c, u);
     DSF_HIP(launch_gemm(u, us));
   }
   {  // QKV projection, bias, RoPE at the kept tokens' original positions
@@ -762,7 +763,7 @@ int run_layer(const Ctx& c, const dsf_layer_weights* W, void* x, int k, bool den
     q.b = W->w_qkv; q.ldb = d;
     q.epi = EPI_QKV_ROPE;
     q.tile_hint = pair_hint;
-    q.beside = us != c.s ? tiles128(f) : 0;
+    q.beside = qwen ? 0 : tiles128(f);
     q.bias = W->b_qkv;
     q.q = at<char>(c, c.plan.q); q.k = at<char>(c, c.plan.k); q.v = at<char>(c, c.plan.v);
     q.Hq = Hq; q.Hkv = Hkv; q.hd = hd; q.R = D.rotary_dims;

@@ -207,7 +207,7 @@ struct GemmArgs {
   // tile size chosen by the caller for a pair of GEMMs that share the chip
   // (0: the launcher's own rule, 1: 128 x 128, 2: 256 x 256)
   int tile_hint;
-  // 128 x 128 tiles of a launch that runs at the same time on another stream
+  // 128 x 128 tiles of a launch that may run at the same time on another stream
   int beside;
 };
 // Kinds whose epilogue reads the rows' sequence positions.

@@ -104,6 +104,26 @@ def test_second_stream_matches_one_stream(dev, monkeypatch, name):
     assert torch.equal(x1, x2)
 
 
+@pytest.mark.parametrize("name,shape", [
+    # at 65-128 rows either projection alone would be cut along K, both together would not
+    ("neox14b", dict(d_model=4096, n_heads=32, n_kv_heads=32, d_ff=16384, batch=1, seq=100)),
+    # up and QKV grids of large tiles that end in a short round
+    ("neox14b", dict(batch=2, seq=2200)),
+])
+def test_second_stream_long_reductions_match_one_stream(dev, monkeypatch, name, shape):
+    # grids whose tiles can be cut along K, which rounds differently: the same
+    # projections have to be cut, into the same pieces, with and without the
+    # second stream
+    w = workload(name).replace(n_layers=1, **shape)
+    W = S.layer_weights(w, 0)
+    x = S.hidden_states(w)
+    announce(f"two streams vs one: {name} {shape}")
+    y2, _, _ = run_layer(dev, w, W, x, w.seq)
+    monkeypatch.setenv("DSF_SINGLE_STREAM", "1")
+    y1, _, _ = run_layer(dev, w, W, x, w.seq)
+    assert torch.equal(y1, y2)
+
+
 @pytest.mark.parametrize("name,k", [("neox_bf16_small", 150), ("qwen_bf16_small", 299)])
 def test_streamk_wait_timeout_is_reported(dev, monkeypatch, name, k):
     # The stream-K finisher waits for earlier pieces' partial sums with a
