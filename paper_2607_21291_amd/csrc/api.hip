@@ -1070,7 +1070,8 @@ int run_decode_layer(const DecCtx& c, const dsf_layer_weights* W, void* x, const
     u.out = dat<char>(c, c.plan.act); u.ldo = f;
   }
   const int np = qwen ? 1 : 2;
-  const bool rows_ok = B <= kRowGemmMaxRows && rowgemm_ok(front[0]) && (qwen || rowgemm_ok(front[1]));
+  const bool rows_ok = B <= kRowGemmMaxRows && rowgemm_ok(front[0]) && (qwen || rowgemm_ok(front[1])) &&
+                       !gemm_tiles_forced();
   const bool bf = c.dtype == DSF_BF16;
   // the launch's workgroups each take the rows' statistics: worth it for few rows
   const bool norm_ok = rows_ok && B <= kRowGemmNormRows && size_t(d) * elem_bytes(c.dtype) <= 1024u * kRowGemmNormVecs;

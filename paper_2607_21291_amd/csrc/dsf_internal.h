@@ -233,6 +233,10 @@ bool rowgemm_ok(const GemmArgs& g);
 hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, const RouterRows* router,
                           const RowGemmSplit* split, hipStream_t s);
 
+// Whether an environment variable (read at every call) forces the projections'
+// tile size or schedule: few-row projections then run on the tiles too.
+bool gemm_tiles_forced();
+
 // Timing of a GEMM launched as two kernels: closes the record the first
 // launch claimed and opens another of the same kind for the second.
 void timing_continue();

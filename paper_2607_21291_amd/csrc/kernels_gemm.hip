@@ -1803,17 +1803,21 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
   }
 }
 
+bool gemm_tiles_forced() {
+  for (const char* n : {"DSF_GEMM_SCHEDULE", "DSF_GEMM_TILE", "DSF_GEMM_TAIL"}) {
+    const char* e = getenv(n);
+    if (e && *e) return true;
+  }
+  return false;
+}
+
 // Few-row launches (kernels_rowgemm.hip), unless a schedule is forced. Above
 // 16 rows the widest projections keep the tile grid: from 256 tile columns on
 // it fills the chip and streams the weights as fast (Qwen2.5-7B gate|up, 37888
 // columns, 32 rows: 64 us, 4.3 TB/s).
 constexpr int kRowTileCols = 256 * 128;
 static bool use_rowgemm(const GemmArgs& g) {
-  if (!rowgemm_ok(g)) return false;
-  for (const char* n : {"DSF_GEMM_SCHEDULE", "DSF_GEMM_TILE", "DSF_GEMM_TAIL"}) {
-    const char* e = getenv(n);
-    if (e && *e) return false;
-  }
+  if (!rowgemm_ok(g) || gemm_tiles_forced()) return false;
   if (g.M <= 16) return true;
   const int cols = g.epi == EPI_SWIGLU ? 2 * g.f : g.N;
   return g.dtype == DSF_F32 || cols < kRowTileCols;
@@ -1843,7 +1847,7 @@ static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
   }
   if constexpr (EPI == EPI_QKV_ROPE) {
     if (g.dtype == DSF_BF16 && g.M <= kSkinnyRows && g.spart && g.scount && g.K % 32 == 0 && g.K1 == g.K &&
-        g.lda % 8 == 0 && g.ldb % 8 == 0) {
+        g.lda % 8 == 0 && g.ldb % 8 == 0 && !gemm_tiles_forced()) {
       const int ntn = (g.N + kSkinnyBN - 1) / kSkinnyBN;
       if (ntn <= kSkinnyCounters) {
         int splits = 1, kc = g.K;

@@ -63,7 +63,7 @@ def _delta_check(w, x, y, y_ref):
                                       ("qwen_bf16_hd128", 37, 2), ("neox_bf16_small", 24, 20),
                                       ("qwen_bf16_small", 20, 17)])
 def test_decode_with_forced_keeps_matches_full_sequence(dev, name, T, B):
-    """B <= 16 runs the projections on the few-row split-K GEMM, B > 16 on the tile GEMMs."""
+    """B <= 16 normalises within the few-row projections, B > 16 ahead of them."""
     w = workload(name).replace(n_layers=2)
     L = 2
     Ws = S.stack_weights(w)

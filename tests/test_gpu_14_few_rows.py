@@ -141,3 +141,42 @@ def test_short_layer_matches_oracle(dev, name, k, flags):
     check_layer(w, W, x, y, scores, idx, k, **({"gate": True} if flags else {}))
     y2, _, _ = run_layer(dev, w, W, x, k, flags=flags)
     assert torch.equal(y, y2)
+
+
+def _decode(dev, w, Ws, x, pos, cap, max_pos, ck, cv, lens):
+    """One step of len(Ws) layers, every token kept; returns x, caches."""
+    L, B = len(Ws), x.shape[0]
+    dls = [P.DeviceLayer(W, dev) for W in Ws]
+    xd, cks, cvs = x.to(dev), [c.to(dev) for c in ck], [c.to(dev) for c in cv]
+    clen = torch.tensor(lens, dtype=torch.int32).repeat(L, 1).to(dev)
+    thr = torch.full((L, B), -float("inf"), device=dev)
+    ws = torch.empty(P.decode_workspace_size(make_desc(w), dtype_code(w), B, max_pos, cap), dtype=torch.uint8, device=dev)
+    P.decode_step(make_desc(w), [d.weights for d in dls], xd, pos.to(dev), max_pos, thr, cks, cvs, clen, ws)
+    torch.cuda.synchronize()
+    return xd.cpu(), [c.cpu() for c in cks], [c.cpu() for c in cvs]
+
+
+@pytest.mark.parametrize("block,B", [(S.NEOX, 24), (S.NEOX, 16), (S.QWEN, 24), (S.QWEN, 16)])
+@pytest.mark.parametrize("var,val", [("DSF_GEMM_TILE", "small"), ("DSF_GEMM_SCHEDULE", "classic")])
+def test_forced_tiles_reach_the_decode_step(dev, monkeypatch, block, B, var, val):
+    # a forced tile or schedule takes a step's projections to the tile grids:
+    # on empty caches they then give the bits of a prefill of one token, whose
+    # projections run there too (in the NeoX block also the layer's output:
+    # attention over one token is its value; its reductions are too short to be
+    # cut along K, which only the prefill could)
+    w = _w(block, 1024, 16, 16 if block == S.NEOX else 4, 64, 512, 16 if block == S.NEOX else 64, "bf16")
+    W = S.layer_weights(w, 0)
+    g = torch.Generator().manual_seed(B)
+    x = (torch.randn(B, 1024, generator=g) * 0.02).to(torch.bfloat16)
+    ck = cv = torch.zeros(B, w.n_kv_heads, 4, 64, dtype=torch.bfloat16)
+    monkeypatch.setenv(var, val)
+    announce(f"decode step and prefill with {var}={val} B={B}")
+    y, dk, dv = _decode(dev, w, [W], x, torch.zeros(B, dtype=torch.int32), 4, 4, [ck], [cv], [0] * B)
+    xp, pk, pv = x.to(dev).view(B, 1, 1024), ck.to(dev), torch.zeros_like(cv).to(dev)
+    clen = torch.zeros(1, B, dtype=torch.int32, device=dev)
+    ws = torch.empty(P.workspace_size(make_desc(w), P.BF16, B, 1, 1, False), dtype=torch.uint8, device=dev)
+    P.stack_prefill(make_desc(w), [P.DeviceLayer(W, dev).weights], [1], xp, [pk], [pv], clen, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dk[0], pk.cpu()) and torch.equal(dv[0], pv.cpu())
+    if block == S.NEOX:
+        assert torch.equal(y, xp.cpu().view(B, 1024))
