@@ -434,7 +434,11 @@ int dsf_sparse_block_backward(const dsf_layer_desc* desc, const dsf_layer_weight
 
 /* Workspace bytes of dsf_decode_step for batch B, positions < max_pos and
  * caches of cap slots (0 on a bad argument, or cap > 65536). No
- * initialisation needed; overlapping calls need separate workspaces. */
+ * initialisation needed; overlapping calls need separate workspaces. For
+ * bf16 batches of 17 to 64 it holds 4 MiB for the projections' partial sums;
+ * dsf_decode_step also runs with a workspace (or static scratch) that lacks
+ * them, and then takes what the attention's partial sums leave: the
+ * projections are slower, and their rounding depends on cap. */
 size_t dsf_decode_workspace_size(const dsf_layer_desc* desc, int dtype, int B, int max_pos, int cap);
 
 /* One decode step of the L-layer stack. x (device [B, d] in dtype, in place)
@@ -466,8 +470,8 @@ int dsf_decode_step(const dsf_layer_desc* desc, const dsf_layer_weights* weights
  * a workspace argument: its scratch is a static device array of
  * dsf_decode_static_scratch_bytes() bytes (32 MiB) that the library holds on
  * each device it runs on until the process ends. The call allocates nothing
- * (no hipMalloc or hipFree). A step whose dsf_decode_workspace_size exceeds
- * the array returns DSF_EWORKSPACE and enqueues nothing. Every call on one
+ * (no hipMalloc or hipFree). A step that the array is too small for returns
+ * DSF_EWORKSPACE and enqueues nothing. Every call on one
  * device shares that device's array and leaves its contents behind; the step
  * clears what must start at zero itself. Two calls that can overlap on one
  * device (different streams or host threads) race: serialise them, or give

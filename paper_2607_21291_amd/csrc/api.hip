@@ -945,7 +945,9 @@ struct DecodePlan {
   int64_t ncounters;
 };
 
-DecodePlan make_decode_plan(const dsf_layer_desc& D, int dtype, int B, int max_pos, int cap) {
+// row_split: room for the split few-row projections, so that their pieces (and
+// with them the bits of a step) do not depend on cap.
+DecodePlan make_decode_plan(const dsf_layer_desc& D, int dtype, int B, int max_pos, int cap, bool row_split = true) {
   const size_t eb = elem_bytes(dtype), n = size_t(B);
   const bool qwen = D.block == DSF_BLOCK_QWEN_SEQ;
   DecodePlan p{};
@@ -968,7 +970,10 @@ DecodePlan make_decode_plan(const dsf_layer_desc& D, int dtype, int B, int max_p
   p.h = qwen ? take(eb * n * D.d_model) : 0;
   p.m2 = qwen ? take(eb * n * D.d_model) : 0;
   p.rope = take(4 * size_t(max_pos) * D.rotary_dims);
+  // the decode attention's partial sums, and in turn those of the projections
   p.part_bytes = 4 * n * D.n_heads * size_t(decode_attn_chunks(cap)) * (D.head_dim + 2);
+  if (row_split && dtype == DSF_BF16 && B > 16 && B <= kRowGemmMaxRows)
+    p.part_bytes = std::max(p.part_bytes, rowgemm_split_bytes());
   p.part = take(p.part_bytes);
   // few-row GEMMs (bf16, B <= 16): split-K partial tiles
   const bool few = dtype == DSF_BF16 && B <= 16;
@@ -1194,7 +1199,10 @@ int decode_step_impl(const dsf_layer_desc* desc, const dsf_layer_weights* weight
   DSF_CHECK(aligned16(x), DSF_EINVAL, "x must be 16-byte aligned");
   rc = check_caches(cache_k, cache_v, L);
   if (rc) return rc;
-  const DecodePlan plan = make_decode_plan(*desc, dtype, B, max_pos, cap);
+  DecodePlan plan = make_decode_plan(*desc, dtype, B, max_pos, cap);
+  // less will do: the projections then split K as far as the attention's partial sums leave room
+  if ((use_static ? kStaticScratchBytes : workspace_bytes) < plan.total)
+    plan = make_decode_plan(*desc, dtype, B, max_pos, cap, false);
   if (use_static) {
     DSF_CHECK(plan.total <= kStaticScratchBytes, DSF_EWORKSPACE,
               "this step needs %zu bytes of scratch, above the static scratch of %zu bytes (use dsf_decode_step "

@@ -230,6 +230,9 @@ bool rowgemm_ok(const GemmArgs& g);
 // One or two projections (np) of the same M rows in one launch. norm: A is
 // the raw rows, normalised by the launch (M <= kRowGemmNormRows, K = d);
 // router (bf16): the rows' router scores too; split (nullable).
+// Bytes of RowGemmSplit::part with which no launch splits K less than it would
+// with more.
+size_t rowgemm_split_bytes();
 hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, const RouterRows* router,
                           const RowGemmSplit* split, hipStream_t s);
 

@@ -650,6 +650,9 @@ static hipError_t launch_row_tiles_f32(const GemmArgs* p, int np, hipStream_t s)
   return hipGetLastError();
 }
 
+// the split forms' tiles are 128 items of 64 bytes (32 x 64 or 64 x 32 outputs)
+size_t rowgemm_split_bytes() { return size_t(kRowSplitWgs) * 128 * 64; }
+
 hipError_t launch_rowgemm(const GemmArgs* p, int np, const RowGemmNorm* norm, const RouterRows* router,
                           const RowGemmSplit* split, hipStream_t s) {
   const int M = p[0].M, epi = p[0].epi;

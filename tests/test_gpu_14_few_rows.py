@@ -143,14 +143,15 @@ def test_short_layer_matches_oracle(dev, name, k, flags):
     assert torch.equal(y, y2)
 
 
-def _decode(dev, w, Ws, x, pos, cap, max_pos, ck, cv, lens):
+def _decode(dev, w, Ws, x, pos, cap, max_pos, ck, cv, lens, spare=0):
     """One step of len(Ws) layers, every token kept; returns x, caches."""
     L, B = len(Ws), x.shape[0]
     dls = [P.DeviceLayer(W, dev) for W in Ws]
     xd, cks, cvs = x.to(dev), [c.to(dev) for c in ck], [c.to(dev) for c in cv]
     clen = torch.tensor(lens, dtype=torch.int32).repeat(L, 1).to(dev)
     thr = torch.full((L, B), -float("inf"), device=dev)
-    ws = torch.empty(P.decode_workspace_size(make_desc(w), dtype_code(w), B, max_pos, cap), dtype=torch.uint8, device=dev)
+    size = P.decode_workspace_size(make_desc(w), dtype_code(w), B, max_pos, cap) - spare
+    ws = torch.empty(size, dtype=torch.uint8, device=dev)
     P.decode_step(make_desc(w), [d.weights for d in dls], xd, pos.to(dev), max_pos, thr, cks, cvs, clen, ws)
     torch.cuda.synchronize()
     return xd.cpu(), [c.cpu() for c in cks], [c.cpu() for c in cvs]
@@ -180,3 +181,30 @@ def test_forced_tiles_reach_the_decode_step(dev, monkeypatch, block, B, var, val
     assert torch.equal(dk[0], pk.cpu()) and torch.equal(dv[0], pv.cpu())
     if block == S.NEOX:
         assert torch.equal(y, xp.cpu().view(B, 1024))
+
+
+@pytest.mark.parametrize("B", [20, 37])
+def test_cache_capacity_does_not_change_the_bits(dev, B):
+    # the down projection is split along K over workgroups, as far at any capacity
+    w = _w(S.QWEN, 512, 8, 2, 64, 8192, 64, "bf16")
+    W = S.layer_weights(w, 0)
+    g = torch.Generator().manual_seed(B)
+    rn = lambda *s: (torch.randn(*s, generator=g) * 0.5).to(torch.bfloat16)
+    x, k, v = (rn(B, 512) * 0.04).to(torch.bfloat16), rn(B, 2, 100, 64), rn(B, 2, 100, 64)
+    pos, lens = torch.arange(B, dtype=torch.int32), [(7 * b) % 100 for b in range(B)]
+    out = []
+    for cap in (101, 4000):
+        announce(f"decode step B={B} cap={cap}")
+        pad = torch.zeros(B, 2, cap - 100, 64, dtype=torch.bfloat16)
+        y, _, _ = _decode(dev, w, [W], x, pos, cap, 128, [torch.cat([k, pad], 2)], [torch.cat([v, pad], 2)], lens)
+        out.append(y)
+    assert torch.equal(out[0], out[1])
+    # a workspace without the projections' partial sums (those of the attention stay: one chunk of keys)
+    announce(f"decode step B={B} short workspace")
+    part = -(-4 * B * w.n_heads * (w.head_dim + 2) // 256) * 256
+    pad = torch.zeros(B, 2, 1, 64, dtype=torch.bfloat16)
+    args = (dev, w, [W], x, pos, 101, 128, [torch.cat([k, pad], 2)], [torch.cat([v, pad], 2)], lens)
+    y, _, _ = _decode(*args, spare=(4 << 20) - part)
+    assert rel_inf(to_np(y) - to_np(x), to_np(out[0]) - to_np(x)) < TOL["bf16"]
+    with pytest.raises(RuntimeError, match="workspace"):
+        _decode(*args, spare=(4 << 20) - part + 256)
