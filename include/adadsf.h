@@ -279,9 +279,10 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * the caller's stream, with the grids of two streams (results are bitwise
  * the same); that projection is never cut along K.
  *
- * Projection schedule. Up to 64 rows (kept tokens of all sequences), a
- * projection runs on the few-row kernel, which streams the weights; the
- * widest bf16 ones (32768 columns) only up to 16 rows. Above, each bf16
+ * Projection schedule. Up to 24 rows (kept tokens of all sequences; 64 in
+ * a decode step), a projection runs on the few-row kernel, which streams the
+ * weights; the widest bf16 ones (32768 columns) only up to 16 rows. fp32
+ * projections of any size run on that kernel's row tiles. Above, each bf16
  * projection takes 128 x 128 or 256 x 256 output tiles, whichever an
  * estimate of both grids' rounds puts first (the GPT-NeoX QKV and up
  * projections, which run side by side, take one size for both); the

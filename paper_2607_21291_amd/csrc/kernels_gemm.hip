@@ -1814,13 +1814,22 @@ bool gemm_tiles_forced() {
 // Few-row launches (kernels_rowgemm.hip), unless a schedule is forced. Above
 // 16 rows the widest projections keep the tile grid: from 256 tile columns on
 // it fills the chip and streams the weights as fast (Qwen2.5-7B gate|up, 37888
-// columns, 32 rows: 64 us, 4.3 TB/s).
+// columns, 32 rows: 64 us, 4.3 TB/s). Without the scratch of a decode step the
+// few-row kernel cannot split K, and from about 24 rows on re-reading the rows
+// for every column group costs more than the tile grids' hand-over (a layer
+// of a stack on few rows / on tiles, us: 24 rows GPT-NeoX-160M 57 / 60, 1.4B 97
+// / 101, Qwen2.5-0.5B 73 / 78, 1.5B 103 / 107, 7B 206 / 202; 32 rows 57 / 60, 105
+// / 101, 78 / 79, 111 / 108, 222 / 204; 64 rows 65 / 62, 139 / 107, 94 / 82,
+// 144 / 112, 283 / 213). A decode step keeps it up to 64 rows (32 rows, caches
+// of 256 slots, on few rows / on tiles: 37 / 59, 76 / 122, 64 / 83, 91 / 123, 184 /
+// 255; 64 rows: 43 / 64, 108 / 139, 72 / 87, 108 / 129, 218 / 269).
 constexpr int kRowTileCols = 256 * 128;
+constexpr int kRowUnsplitRows = 24;
 static bool use_rowgemm(const GemmArgs& g) {
   if (!rowgemm_ok(g) || gemm_tiles_forced()) return false;
-  if (g.M <= 16) return true;
+  if (g.M <= 16 || g.dtype == DSF_F32) return true;
   const int cols = g.epi == EPI_SWIGLU ? 2 * g.f : g.N;
-  return g.dtype == DSF_F32 || cols < kRowTileCols;
+  return cols < kRowTileCols && (g.row_split.part || g.M <= kRowUnsplitRows);
 }
 
 template <int EPI>

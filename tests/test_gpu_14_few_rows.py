@@ -4,7 +4,8 @@ workgroup, output widths that are no multiple of 16, reductions that fall back
 to the other kernels, query groups of 1 to 20 heads per kv head, cache lengths
 around the chunk of 256 keys, empty and full caches. One decode step on random
 caches is compared with the oracle's norms, rotation and activations composed
-in float64; short routed layers (at most 64 kept rows) with the oracle's layer."""
+in float64; short routed layers (at most 64 kept rows, the few-row kernel
+without split scratch up to 24) with the oracle's layer."""
 import numpy as np
 import pytest
 import torch
@@ -129,8 +130,9 @@ def test_decode_step_on_random_caches(dev, case):
 
 
 @pytest.mark.parametrize("flags", [0, P.FLAG_GATE])
-@pytest.mark.parametrize("name,k", [("neox_bf16_small", 8), ("neox_bf16_small", 32), ("qwen_bf16_small", 9),
-                                    ("qwen_bf16_hd128", 64), ("neox_bf16_hd128", 17), ("tiny_neox_f32", 7),
+@pytest.mark.parametrize("name,k", [("neox_bf16_small", 8), ("neox_bf16_small", 12), ("neox_bf16_small", 13),
+                                    ("neox_bf16_small", 32), ("qwen_bf16_small", 9),
+                                    ("qwen_bf16_small", 12), ("qwen_bf16_hd128", 25), ("qwen_bf16_hd128", 64), ("neox_bf16_hd128", 17), ("tiny_neox_f32", 7),
                                     ("tiny_qwen_f32", 32)])
 def test_short_layer_matches_oracle(dev, name, k, flags):
     w = workload(name)
