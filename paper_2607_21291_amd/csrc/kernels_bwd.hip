@@ -652,8 +652,9 @@ __global__ __launch_bounds__(256, HD == 64 && G == 2 ? 3 : 1) void attn_bwd_dq_k
 //   dK^T[c][key] += scale * sum_queries Q^T[c][query] dS[query][key].
 // Each item's lse and D come with its tiles, by DMA (as register loads their
 // arrival was waited for, and with it the DMA in flight). Queries past the
-// end are zero rows of Q and dout (finite probabilities times zeros); keys
-// past it are not stored.
+// end are zero rows of Q and dout, masked so that an infinite key (whose
+// product with a zero row is NaN) keeps its own gradient; keys past it are not
+// stored.
 template <int HD, int G>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __restrict__ Q,
                                                            const uint16_t* __restrict__ K,
@@ -732,7 +733,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
     if (i + 1 < items) issue(i + 1);
     const int q0 = (qb0 + i % nq) * kAB;
     if (q0 + kAB - 1 < kw) continue;  // every query before the wave's keys
-    const bool edge = q0 < kw + 16 * G - 1;  // some of the block's queries come before some of the keys
+    // some of the block's queries come before some of the keys, or past the end
+    const bool edge = q0 < kw + 16 * G - 1 || q0 + kAB > n;
     const char* Qt = smem + slot * 2 * A::kTileBytes;
     const char* Dt = Qt + A::kTileBytes;
     bf16x8 pb[G][2], db[G][2];
@@ -762,7 +764,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const uint16_t* __res
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             float pv = __builtin_amdgcn_exp2f(fmaf(st[g][e], scale2, -l4[e]));
-            if (edge && kw + 16 * g + r16 > q0 + 16 * blk + 4 * grp + e) pv = 0.f;
+            // key <= query < n, as one unsigned comparison of their distances
+            const int key = kw + 16 * g + r16;
+            if (edge && uint32_t(q0 + 16 * blk + 4 * grp + e - key) >= uint32_t(n - key)) pv = 0.f;
             p[g][4 * hb + e] = pv;
             ds[g][4 * hb + e] = pv * (dp[g][e] - d4[e]);
           }

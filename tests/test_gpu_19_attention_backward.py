@@ -51,3 +51,22 @@ def test_attention_blocks(dev, case):
     check_backward(w, W, x, dy, idx, False, dx, g)
     dx2, g2 = run_backward(dev, w, W, x, dy, idx, False)
     assert torch.equal(dx, dx2) and all(torch.equal(g[n], g2[n]) for n in g)
+
+
+def test_infinite_key_of_no_weight_keeps_its_value_gradient(dev):
+    # 70 tokens, the block of keys padded to 128 queries. Token 20's key has
+    # -inf in dim 63 of head 0, where every query is positive: its score is
+    # -inf and its weight zero for all of them, so its value's gradient is
+    # zero, also after the padding (zero rows, whose score with it is NaN)
+    w, W, x, dy, idx = _case(S.NEOX, 128, 2, 2, 64, 192, 1, 70, 70)
+    dq, c, t = w.d_attn, 5, 20
+    x[0, t, c] = 100.0                  # normalises to sqrt(d - 1) = 11.3, the others stay below 5
+    W["w_qkv"][63] = 0.0
+    W["b_qkv"][63] = 2.0 ** -120
+    W["w_qkv"][dq + 63] = 0.0
+    W["w_qkv"][dq + 63, c] = -3.75e37   # 11.3 times it is beyond the largest bf16
+    W["b_qkv"][dq + 63] = 0.0
+    announce("attention backward with an infinite key")
+    _, g = run_backward(dev, w, W, x, dy, idx, False)
+    assert torch.isfinite(g["b_qkv"][2 * dq:]).all() and torch.isfinite(g["w_qkv"][2 * dq:]).all()
+    assert not torch.isfinite(g["w_qkv"][:dq]).all()  # the key was infinite: queries' gradients hold 0 x inf
