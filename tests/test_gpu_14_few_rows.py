@@ -69,6 +69,7 @@ STEPS = [
     (S.QWEN, 256, 4, 2, 64, 8192, 64, "bf16", 3, 520),   # two column groups per workgroup, norm inside
     (S.QWEN, 256, 6, 2, 64, 8192, 64, "bf16", 20, 520),  # the same, norm apart, 3 heads per kv head
     (S.QWEN, 256, 14, 2, 64, 512, 64, "bf16", 40, 257),  # 7 heads per kv head
+    (S.QWEN, 256, 4, 2, 64, 8192, 64, "bf16", 37, 520),  # down: K split over workgroups, 33-64 rows
     (S.QWEN, 256, 20, 1, 32, 512, 32, "bf16", 2, 257),   # 20 heads: two head blocks
     (S.QWEN, 128, 7, 1, 128, 17408, 128, "bf16", 20, 257),  # gate|up wide enough for the tile grid
     (S.QWEN, 256, 7, 1, 128, 512, 128, "f32", 3, 520),
@@ -210,3 +211,21 @@ def test_cache_capacity_does_not_change_the_bits(dev, B):
     assert rel_inf(to_np(y) - to_np(x), to_np(out[0]) - to_np(x)) < TOL["bf16"]
     with pytest.raises(RuntimeError, match="workspace"):
         _decode(*args, spare=(4 << 20) - part + 256)
+
+
+@pytest.mark.parametrize("B", [20, 37])
+def test_split_projections_leave_their_counters_clear(dev, B):
+    # two layers in one step, whose launches share the split's counters, give
+    # the bits of one layer after the other
+    w = _w(S.QWEN, 256, 4, 2, 64, 8192, 64, "bf16")
+    Ws = [S.layer_weights(w, l) for l in range(2)]
+    cap, g = 300, torch.Generator().manual_seed(B)
+    rn = lambda *s: (torch.randn(*s, generator=g) * 0.5).to(torch.bfloat16)
+    x, ck, cv = rn(B, 256), [rn(B, 2, cap, 64) for _ in Ws], [rn(B, 2, cap, 64) for _ in Ws]
+    pos, lens = torch.arange(B, dtype=torch.int32), [(37 * b) % cap for b in range(B)]
+    announce(f"two-layer decode step B={B}")
+    y, _, _ = _decode(dev, w, Ws, x, pos, cap, cap, ck, cv, lens)
+    one = x
+    for l, W in enumerate(Ws):
+        one, _, _ = _decode(dev, w, [W], one, pos, cap, cap, ck[l:l + 1], cv[l:l + 1], lens)
+    assert torch.equal(y, one)
