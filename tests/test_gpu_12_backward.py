@@ -140,8 +140,9 @@ def test_backward_full_shapes(dev, name, B, T, k, gate):
 
 def test_backward_streamk_wait_timeout_is_reported(dev, monkeypatch):
     """The weight gradients of a full-width NeoX-160M layer (B 2, k 1563 of
-    2048: 3126 kept rows) take the stream-K grid. DSF_SK_SPIN_LIMIT=0 makes
-    every wait for an earlier piece give up at once (every kernel still exits
+    2048: 3126 kept rows) split the tokens between workgroups, the last of
+    which waits for the others' partial sums. DSF_SK_SPIN_LIMIT=0 makes
+    every such wait give up at once (every kernel still exits
     normally); the status word reports it, and the next normal call clears it
     and is correct again."""
     w = S.WORKLOADS["neox160m"].replace(batch=2, seq=2048)
@@ -157,7 +158,7 @@ def test_backward_streamk_wait_timeout_is_reported(dev, monkeypatch):
     dx = torch.empty_like(xd)
     gr = _grads(w, dev)
     ws = torch.empty(P.backward_workspace_size(desc, P.BF16, 2, 2048, 1563), dtype=torch.uint8, device=dev)
-    announce("backward stream-K give-up reported")
+    announce("backward give-up reported")
     monkeypatch.setenv("DSF_SK_SPIN_LIMIT", "0")
     P.sparse_block_backward(desc, dl.weights, xd, dyd, idd, dx, gr, ws)
     torch.cuda.synchronize()

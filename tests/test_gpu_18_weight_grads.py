@@ -41,14 +41,15 @@ def _inputs(w, k):
     (S.NEOX, 264, 4, 4, 64, 576, 1, 70, 65),
     (S.NEOX, 520, 4, 4, 64, 1088, 2, 300, 257),    # 9 token tiles: two slices
     (S.NEOX, 128, 2, 2, 64, 512, 8, 300, 290),     # 37: eight slices of few tiles
-    (S.NEOX, 768, 12, 12, 64, 3072, 2, 300, 290),  # 10 token tiles: two slices, either tile width
-    (S.NEOX, 776, 12, 12, 64, 2944, 8, 300, 290),  # tiles of 192 columns with remainders
+    (S.NEOX, 768, 12, 12, 64, 3072, 2, 300, 290),  # 10 token tiles: two slices
+    (S.NEOX, 776, 12, 12, 64, 2944, 8, 300, 290),  # three slices, remainders in both directions
     (S.QWEN, 136, 3, 1, 64, 192, 1, 70, 64),
     (S.QWEN, 1032, 4, 1, 128, 320, 2, 170, 161),
     (S.QWEN, 2056, 2, 1, 64, 128, 1, 40, 33),
     (S.NEOX, 2056, 2, 2, 64, 128, 1, 40, 17),
     (S.QWEN, 4104, 2, 1, 64, 64, 1, 40, 33),
     (S.NEOX, 8192, 2, 2, 64, 64, 1, 40, 16),
+    (S.NEOX, 2056, 2, 2, 64, 9152, 1, 140, 129),   # up and down: 324 tiles of 256 with remainders, and bias sums
 ], ids=lambda c: f"{c[0]}-d{c[1]}-f{c[5]}-B{c[6]}-k{c[8]}")
 def test_all_gradients(dev, case):
     w, W, x, dy, idx = _case(*case)
