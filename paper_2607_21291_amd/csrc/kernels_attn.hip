@@ -502,15 +502,6 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   }
 }
 
-// Launch kern<<<grid, block>>>(args...), through hipExtLaunchKernelGGL when
-// the enclosing timing scope hands over its events.
-template <typename K, typename... A>
-static void launch_timed(K kern, dim3 grid, dim3 block, hipStream_t s, A... args) {
-  hipEvent_t e0, e1;
-  if (timing_claim(&e0, &e1)) hipExtLaunchKernelGGL(kern, grid, block, 0, s, e0, e1, 0, args...);
-  else kern<<<grid, block, 0, s>>>(args...);
-}
-
 // Keys per sequence up to which one query group per wave is faster
 // (measured, per head dim): at head dim 64 the two forms are within 2 % up to
 // 2k keys and two groups win beyond (-10 % at 2362); at head dim 128 one group
@@ -527,9 +518,9 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
     dim3 grid((n + 15) / 16, Hq, B);
     auto Qp = (const float*)q; auto Kp = (const float*)k; auto Vp = (const float*)v; auto O = (float*)out;
     switch (hd) {
-      case 32: launch_timed(attn_f32_kernel<32>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
-      case 64: launch_timed(attn_f32_kernel<64>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
-      case 128: launch_timed(attn_f32_kernel<128>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 32: launch_with_timing(attn_f32_kernel<32>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 64: launch_with_timing(attn_f32_kernel<64>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
+      case 128: launch_with_timing(attn_f32_kernel<128>, grid, dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O); break;
       default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -545,8 +536,8 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
   switch (hd) {
 #define DSF_ATTN_LAUNCH(H)                                                                                      \
   case H:                                                                                                       \
-    if (groups == 1) launch_timed(attn_bf16_dma_kernel<H, 1>, grid(1), dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O, lse); \
-    else launch_timed(attn_bf16_dma_kernel<H, 2, true>, grid(2), dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O, lse);      \
+    if (groups == 1) launch_with_timing(attn_bf16_dma_kernel<H, 1>, grid(1), dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O, lse); \
+    else launch_with_timing(attn_bf16_dma_kernel<H, 2, true>, grid(2), dim3(256), s, Qp, Kp, Vp, Hq, Hkv, n, O, lse);      \
     break;
     DSF_ATTN_LAUNCH(32)
     DSF_ATTN_LAUNCH(64)

@@ -4,8 +4,8 @@
 // causally over the layer's cached kept tokens).
 //
 // The projections of a decode step run on the few-row GEMM and the routing
-// flags come from the router kernel; the kernels here are the other pieces
-// decoding adds:
+// flags come from the router (bf16: workgroups of that GEMM's first launch);
+// the kernels here are the other pieces decoding adds:
 // - attention of one query per (sequence, head) over its cache and the new
 //   token, split into chunks of keys whose last-arriving workgroup combines
 //   them in chunk order (memory-bound: it reads the cache once), which also
@@ -23,17 +23,10 @@ namespace dsf {
 // ------------------------------------------------------- decode attention
 
 template <typename T>
-struct DecElem;
-template <>
-struct DecElem<float> {
-  static __device__ __forceinline__ float to_f(float v) { return v; }
-  static __device__ __forceinline__ float from_f(float v) { return v; }
-};
-template <>
-struct DecElem<uint16_t> {
-  static __device__ __forceinline__ float to_f(uint16_t v) { return bf2f(v); }
-  static __device__ __forceinline__ uint16_t from_f(float v) { return f2bf(v); }
-};
+__device__ __forceinline__ T round_to(float v) {
+  if constexpr (sizeof(T) == 2) return f2bf(v);
+  else return v;
+}
 
 __device__ __forceinline__ float wave_max_dec(float v) {
 #pragma unroll
@@ -312,7 +305,7 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(const T* __restrict
     }
     const int64_t bh = int64_t(b) * Hq + h0 + h;
     if (nch == 1) {
-      out[bh * HD + dim] = DecElem<T>::from_f(L > 0.f ? O / L : 0.f);
+      out[bh * HD + dim] = round_to<T>(L > 0.f ? O / L : 0.f);
     } else {
       float* dst = part + (bh * nch_max + c) * (HD + 2);
       __hip_atomic_store(dst + 2 + dim, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -382,7 +375,7 @@ __global__ __launch_bounds__(256, 2) void decode_attn_kernel(const T* __restrict
     for (int i = 0; i < IG; ++i) {
       const int e = tid + 256 * (i0 + i);
       if (e < ng * HD)
-        out[(int64_t(b) * Hq + h0) * HD + e] = DecElem<T>::from_f(L[i] > 0.f ? O[i] / L[i] : 0.f);
+        out[(int64_t(b) * Hq + h0) * HD + e] = round_to<T>(L[i] > 0.f ? O[i] / L[i] : 0.f);
     }
   }
 }

@@ -1,15 +1,20 @@
 // Projection GEMMs of the decoder block on the kept tokens (Eqs. 1-2),
 // C[M, N] = A[M, K] . B[N, K]^T with fused epilogues, for gfx950.
 //
-// bf16 path: 128 x 128 x 64 workgroup tiles, four wavefronts of 64 x 64, each
-// built from v_mfma_f32_16x16x32_bf16. Global tiles are staged through LDS
-// (double buffered, 16-byte chunks XOR-swizzled by row so that the 16 rows an
-// MFMA operand read touches fall in distinct bank groups). The next tile's
-// global loads are in flight while the current tile is multiplied.
+// bf16 path: workgroup tiles of 64 x 64, 128 x 128 or 256 x 256 outputs and 64
+// of K, wavefronts of v_mfma_f32_16x16x32_bf16 blocks. Global tiles arrive in
+// an LDS ring of two or four stages by buffer DMA (16-byte chunks XOR-swizzled
+// by row so that the 16 rows an MFMA operand read touches fall in distinct
+// bank groups). A launch takes one tile per workgroup, a persistent or
+// stream-K grid, or tiles cut along K between workgroups (launch_dma says
+// which). Reductions that are no multiple of 64, and operands of 4 GiB or
+// more, take a 128 x 128 kernel that stages its tiles through registers. Few
+// rows go to kernels_rowgemm.hip.
 //
-// After the K loop the fp32 tile is written to LDS and the epilogue reads it
-// back row-wise, so every epilogue (RoPE pairs dims i and i + R/2; SwiGLU
-// pairs gate and up columns) sees whole rows and stores 16-byte vectors.
+// After the K loop the fp32 tile (256 x 256: 32 rows of a wave's part at a time)
+// is written to LDS and the epilogue reads it back row-wise, so every epilogue
+// (RoPE pairs dims i and i + R/2; SwiGLU pairs gate and up columns) sees whole
+// rows and stores 16-byte vectors.
 //
 // fp32 path: the row tiles of kernels_rowgemm.hip on the fp32 matrix cores; a
 // plain LDS-tiled FMA kernel (32 x 128 tiles) that shares the epilogue takes
@@ -777,8 +782,6 @@ struct DmaGemm {
                                                   Acc& acc) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / (BN / WN), wn = wave % (BN / WN);
-    const int r16 = lane & 15, grp = lane >> 4;
     const int m0 = tm * BM;
     // DMA sources are buffer resources over A, A2, B, B2 whose size is the
     // matrix's rows x leading dimension: a row beyond M (or N) is out of range
@@ -1442,23 +1445,16 @@ static bool dma_addressable(const GemmArgs& g, int rows_b) {
          (!g.b2 || np * g.ldb2 * 2 < lim);
 }
 
-// Launch kern<<<grid, block>>>(g), through hipExtLaunchKernelGGL when an
-// enclosing timing scope hands over its events.
-template <typename K, typename... A>
-static void launch_timed(K kern, dim3 grid, dim3 block, hipStream_t s, const A&... args) {
-  hipEvent_t e0, e1;
-  if (timing_claim(&e0, &e1)) hipExtLaunchKernelGGL(kern, grid, block, 0, s, e0, e1, 0, args...);
-  else kern<<<grid, block, 0, s>>>(args...);
-}
+// ---------------------------------- QKV projection of few rows, split along K
 
-// ------------------------------------------- few-row GEMM (decode steps)
-
-// For M <= 16 rows the tile GEMMs leave most of the chip idle (N / 128
-// workgroups). Here a workgroup takes 128 output columns and one slice of K:
-// each of its four wavefronts computes a 16 x 32 block (two
-// v_mfma_f32_16x16x32_bf16 blocks) from operands loaded straight from global
-// memory (16 bytes per lane, 64 contiguous bytes per weight row and k-step),
-// so the weights stream once over ~256-512 workgroups. With one slice the
+// The QKV projection of a bf16 decode step of up to 16 rows whose rotary dims
+// are no multiple of 16 (launch_rowgemm's column groups need that); the tile
+// GEMMs would leave most of the chip idle (N / 128 workgroups). A workgroup
+// takes 128 output columns and one slice of K: each of its four wavefronts
+// computes a 16 x 32 block (two v_mfma_f32_16x16x32_bf16 blocks) from operands
+// loaded straight from global memory (16 bytes per lane, 64 contiguous bytes
+// per weight row and k-step), so the weights stream once over ~256-512
+// workgroups. With one slice the
 // workgroup finishes its tile; otherwise it publishes its fp32 partial tile
 // with device-coherent stores, and the last of the tile's workgroups to
 // arrive (a device-scope counter, reset by that workgroup) adds the slices in
@@ -1471,7 +1467,6 @@ constexpr int kSkinnyCounters = 1024;   // column tiles per launch
 size_t gemm_skinny_partial_bytes() { return size_t(kSkinnyMaxParts) * kSkinnyRows * kSkinnyBN * sizeof(float); }
 int gemm_skinny_counters() { return kSkinnyCounters; }
 
-template <int EPI>  // EPI_QKV_ROPE only: the other kinds always fit the few-row kernel
 __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits, int kc) {
   constexpr int LD = kSkinnyBN + 4;
   __shared__ float stage[kSkinnyRows * LD];
@@ -1482,32 +1477,19 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits
   const int k0 = sl * kc, k1 = min(g.K, k0 + kc);
   // the B rows (output columns) of this lane in the wave's two 16-column blocks
   const uint16_t* brow[2];
-  const uint16_t* brow2[2];
   bool bok[2];
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
-    const int c = wave * 32 + nb * 16 + r16;  // column within the tile
-    int r;
-    if constexpr (EPI == EPI_SWIGLU) {
-      // tile columns [0, 64) are gate units, [64, 128) the matching up units
-      r = c < kSkinnyBN / 2 ? tn * (kSkinnyBN / 2) + c : g.f + tn * (kSkinnyBN / 2) + (c - kSkinnyBN / 2);
-      bok[nb] = true;
-    } else {
-      r = tn * kSkinnyBN + c;
-      bok[nb] = r < g.N;
-      if (!bok[nb]) r = 0;
-    }
-    brow[nb] = (const uint16_t*)g.b + int64_t(r) * g.ldb;
-    brow2[nb] = g.b2 ? (const uint16_t*)g.b2 + int64_t(r) * g.ldb2 : nullptr;
+    const int r = tn * kSkinnyBN + wave * 32 + nb * 16 + r16;
+    bok[nb] = r < g.N;
+    brow[nb] = (const uint16_t*)g.b + int64_t(bok[nb] ? r : 0) * g.ldb;
   }
   const bool aok = r16 < g.M;
   const uint16_t* arow = (const uint16_t*)g.a + int64_t(aok ? r16 : 0) * g.lda;
-  const uint16_t* arow2 = g.a2 ? (const uint16_t*)g.a2 + int64_t(aok ? r16 : 0) * g.lda2 : nullptr;
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
   const bf16x8 zero = {};
-  // k-steps of 32 (the slice is a multiple of 32; k chunks of 8 never
-  // straddle K1, a multiple of 32), up to 8 at a time: every load of a group
-  // is issued before its MFMAs
+  // k-steps of 32 (the slice is a multiple of 32), up to 8 at a time: every
+  // load of a group is issued before its MFMAs
   constexpr int kGroup = 8;
   const int nsteps = (k1 - k0) / 32;
   for (int st0 = 0; st0 < nsteps; st0 += kGroup) {
@@ -1515,12 +1497,9 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits
 #pragma unroll
     for (int it = 0; it < kGroup; ++it) {
       const int k = k0 + 32 * min(st0 + it, nsteps - 1) + 8 * grp;  // past the end: repeat the last step (unused)
-      const bool first = k < g.K1;
-      const int kk = first ? k : k - g.K1;
-      af[it] = aok ? *reinterpret_cast<const bf16x8*>((first ? arow : arow2) + kk) : zero;
+      af[it] = aok ? *reinterpret_cast<const bf16x8*>(arow + k) : zero;
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-        bf[it][nb] = bok[nb] ? *reinterpret_cast<const bf16x8*>((first ? brow[nb] : brow2[nb]) + kk) : zero;
+      for (int nb = 0; nb < 2; ++nb) bf[it][nb] = bok[nb] ? *reinterpret_cast<const bf16x8*>(brow[nb] + k) : zero;
     }
 #pragma unroll
     for (int it = 0; it < kGroup; ++it)
@@ -1536,7 +1515,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits
 #pragma unroll
       for (int i = 0; i < 4; ++i) stage[(4 * grp + i) * LD + wave * 32 + nb * 16 + r16] = acc[nb][i];
     __syncthreads();
-    gemm_epilogue<uint16_t, kSkinnyRows, kSkinnyBN, 256, EPI>(g, stage, 0, tn, tid);
+    gemm_epilogue<uint16_t, kSkinnyRows, kSkinnyBN, 256, EPI_QKV_ROPE>(g, stage, 0, tn, tid);
     return;
   }
   float* part = g.spart + (int64_t(tn) * splits + sl) * (kSkinnyRows * kSkinnyBN);
@@ -1597,7 +1576,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmArgs g, int splits
     stage[m * LD + c0 + 4 + i] = vhi[i];
   }
   __syncthreads();
-  gemm_epilogue<uint16_t, kSkinnyRows, kSkinnyBN, 256, EPI>(g, stage, 0, tn, tid);
+  gemm_epilogue<uint16_t, kSkinnyRows, kSkinnyBN, 256, EPI_QKV_ROPE>(g, stage, 0, tn, tid);
 }
 
 // Slices of K for a few-row launch: enough workgroups to cover the chip
@@ -1729,7 +1708,7 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
           if (tiny_ok<EPI>(g) && all <= 2 * cus && tiny_us(all, g.K / BK, cus) < 0.95 * deep_us(g.K / BK, sp)) {
             ga.ntm = tm;
             ga.ntn = tn;
-            launch_timed(gemm_bf16_dma_kernel<EPI, TT::BM, TT::BN, TT::WM, TT::WN, TT::NS, TT::BK>, dim3(tm * tn),
+            launch_with_timing(gemm_bf16_dma_kernel<EPI, TT::BM, TT::BN, TT::WM, TT::WN, TT::NS, TT::BK>, dim3(tm * tn),
                          dim3(Cfg::kThreads), s, ga);
             return;
           }
@@ -1741,12 +1720,12 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
             ga.tail_r = nt;
             ga.tail_s = sp;
             ga.spin_limit = spin_limit();
-            launch_timed(gemm_bf16_tail_kernel<EPI, TD::BM, TD::BN, TD::WM, TD::WN, TD::NS, TD::BK>,
+            launch_with_timing(gemm_bf16_tail_kernel<EPI, TD::BM, TD::BN, TD::WM, TD::WN, TD::NS, TD::BK>,
                          dim3(kXcds * sp * ((nt + kXcds - 1) / kXcds)), dim3(Cfg::kThreads), s, ga);
             return;
           }
         }
-        launch_timed(fn, dim3(nt), dim3(Cfg::kThreads), s, ga);
+        launch_with_timing(fn, dim3(nt), dim3(Cfg::kThreads), s, ga);
         return;
       }
     }
@@ -1762,7 +1741,7 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
         // tile order as for one tile per workgroup
         ga.group_m = ntn >= kGroupMinCols ? kGroupM : 0;
         if (ga.px > 0) {
-          launch_timed(fn, dim3(ga.px * kXcds), dim3(Cfg::kThreads), s, ga);
+          launch_with_timing(fn, dim3(ga.px * kXcds), dim3(Cfg::kThreads), s, ga);
           return;
         }
       }
@@ -1791,15 +1770,15 @@ static void launch_dma(const GemmArgs& g, hipStream_t s) {
         ga.tail_s = ts.s;
         ga.spin_limit = spin_limit();
         if (nt > ts.r) {
-          launch_timed(fn, dim3(nt - ts.r), dim3(Cfg::kThreads), s, ga);
+          launch_with_timing(fn, dim3(nt - ts.r), dim3(Cfg::kThreads), s, ga);
           timing_continue();
         }
-        launch_timed(gemm_bf16_tail_kernel<EPI, BM, BN, WM, WN, NS, BK>,
+        launch_with_timing(gemm_bf16_tail_kernel<EPI, BM, BN, WM, WN, NS, BK>,
                      dim3(kXcds * ts.s * ((ts.r + kXcds - 1) / kXcds)), dim3(Cfg::kThreads), s, ga);
         return;
       }
     }
-    launch_timed(fn, dim3(nt), dim3(Cfg::kThreads), s, ga);
+    launch_with_timing(fn, dim3(nt), dim3(Cfg::kThreads), s, ga);
   }
 }
 
@@ -1847,7 +1826,7 @@ static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
         return;
       }
     }
-    launch_timed(gemm_bf16_kernel<EPI>, dim3((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM), dim3(kThreads), s, g);
+    launch_with_timing(gemm_bf16_kernel<EPI>, dim3((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM), dim3(kThreads), s, g);
     return;
   } else {
   if (use_rowgemm(g)) {
@@ -1861,7 +1840,7 @@ static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
       if (ntn <= kSkinnyCounters) {
         int splits = 1, kc = g.K;
         skinny_split(ntn, g.K, &splits, &kc);
-        launch_timed(gemm_skinny_kernel<EPI>, dim3(ntn * splits), dim3(256), s, g, splits, kc);
+        launch_with_timing(gemm_skinny_kernel, dim3(ntn * splits), dim3(256), s, g, splits, kc);
         return;
       }
     }
@@ -1880,10 +1859,10 @@ static void launch_gemm_t(const GemmArgs& g, hipStream_t s) {
   }
   if (g.dtype == DSF_BF16) {
     const int ntn = EPI == EPI_SWIGLU ? g.f / (kBN / 2) : (g.N + kBN - 1) / kBN;
-    launch_timed(gemm_bf16_kernel<EPI>, dim3(ntn, (g.M + kBM - 1) / kBM), dim3(kThreads), s, g);
+    launch_with_timing(gemm_bf16_kernel<EPI>, dim3(ntn, (g.M + kBM - 1) / kBM), dim3(kThreads), s, g);
   } else {
     const int ntn = EPI == EPI_SWIGLU ? g.f / (kFBN / 2) : (g.N + kFBN - 1) / kFBN;
-    launch_timed(gemm_f32_kernel<EPI>, dim3(ntn, (g.M + kFBM - 1) / kFBM), dim3(256), s, g);
+    launch_with_timing(gemm_f32_kernel<EPI>, dim3(ntn, (g.M + kFBM - 1) / kFBM), dim3(256), s, g);
   }
   }
 }
