@@ -59,12 +59,39 @@ struct RowProb {
   const int32_t* idx;
   int M, N, K, K1, lda, lda2, ldb, ldb2, epi, kk, T, f, ldo, Hq, Hkv, hd, R, nsub;
 };
-constexpr int kRowWideMin = 1024;     // 16-column groups from which a workgroup takes two
-constexpr int kRowNarrowMax = 128;    // 16-column groups up to which groups of 8 are taken
-constexpr int kRowSplitMinSteps = 64;  // k-steps from which K is split over workgroups,
-constexpr int kRowSplitWgs = 512;      // into about this many of them
+// Where the forms change. The figures are microseconds per layer of a decode
+// step over 300 keys, with the form / without it.
+//
+// 16-column groups from which a workgroup takes two, which halves the re-reads
+// of A and, below some count, leaves CUs idle. 16 rows: Qwen2.5-7B gate|up
+// (2368 groups) 201 / 226, 1.5B (1120) 90 / 92; below the line NeoX-1.4B QKV
+// and up (896) 64 / 69, Qwen2.5-0.5B (608) 63 / 64, NeoX-160M (336) 35 / 35. 4 rows:
+// 165 / 172, 77 / 77, 56 / 57, 56 / 55, 28.5 / 27.7.
+constexpr int kRowWideMin = 1024;
+// Groups up to which groups of 8 columns double the workgroups of a down or O
+// projection. 16 rows: NeoX-160M (48 groups) 35 / 37, Qwen2.5-0.5B (56) 64 / 66,
+// 1.5B (96) 90 / 94, NeoX-1.4B (128) 69 / 73; beyond, Qwen2.5-7B (224) 227 / 201.
+constexpr int kRowNarrowMax = 128;
+// k-steps from which more than 16 rows split K. 48 rows: 120 steps (NeoX-160M
+// down) 44 / 53, 152 (Qwen2.5-0.5B) 71 / 83, 64 and 320 (NeoX-1.4B) 100 / 121, of
+// which the 64 give nothing; 24 rows: 38 / 41, 64 / 69, 72 / 82 (the 64: 72 / 73).
+// Below, 48 steps (Qwen2.5-1.5B QKV): 102 -> 98 at 48 rows, 88 -> 90 at 24.
+constexpr int kRowSplitMinSteps = 64;
+// Workgroups that a split aims at, two per CU. 128 / 256 / 512 / 1024 at 24 rows:
+// NeoX-1.4B 74 / 68 / 72 / 79, Qwen2.5-1.5B 87 / 84 / 88 / 88, 7B 204 / 166 / 179 /
+// 185; at 48 rows 109 / 97 / 100 / 110, 113 / 99 / 102 / 110, 245 / 214 / 209 / 231;
+// the small models the same throughout.
+constexpr int kRowSplitWgs = 512;
+// Pieces of a tile, at most: the last adds them all. 4 / 8 / 16 / 32 at 24 rows:
+// NeoX-160M 39 / 38 / 38 / 38, Qwen2.5-0.5B 65 / 63 / 64 / 64, 1.5B 89 / 84 / 88 / 89,
+// 7B 172 / 180 / 179 / 179; at 48 rows within 4 % of each other.
 constexpr int kRowSplitMax = 16;
-constexpr int kRowTilesF32 = 192;      // fp32: workgroups below which a smaller tile is taken
+// fp32: workgroups below which a smaller tile is taken. A layer of one sequence,
+// line at 96 / 192 / 300: NeoX-160M 100 rows 94 / 89 / 92, 307 rows 128 / 118 / 116,
+// 600 rows 200 / 176 / 187; Qwen2.5-1.5B 307 rows 468 / 410 / 440, 600 rows 674 / 674 /
+// 726; Qwen2.5-0.5B 307 rows 200 / 222 / 222, 600 rows 312 / 337 / 336; from 1200 rows
+// on the same.
+constexpr int kRowTilesF32 = 192;
 struct RowGemmArgs {
   int router_wgs;
   int tiles0;    // tiles of the first projection

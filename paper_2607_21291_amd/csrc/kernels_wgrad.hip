@@ -32,8 +32,15 @@ namespace {
 constexpr int kWgK = kAttnTileRows;      // tokens per LDS tile
 constexpr int kWgSub = 128;              // columns per LDS subtile
 constexpr int kWgSubBytes = kWgK * kWgSub * 2;
-constexpr int kWgMinTiles = 4;           // token tiles per slice, at least
-constexpr int kWgLargeMin = 320;         // 256 x 256 tiles from which they are taken
+// Token tiles per slice, at least: a hand-over costs a few of them. Training
+// step of a NeoX-160M layer, 300 rows, with 1 / 2 / 4 / 8: 249 / 226 / 209 / 209 us; 1400
+// rows 330 / 328 / 317 / 310; 12504 rows 1099 / 1098 / 1103 / 1103.
+constexpr int kWgMinTiles = 4;
+// 256 x 256 tiles from which they are taken: more than a round of the CUs, as
+// their grids are not split. Training step of a layer with large / small tiles:
+// Qwen2.5-1.5B, 6000 rows (420 for the up projection) 2370 / 2390 us; at 256 tiles
+// (NeoX-1.4B, 6000 rows), where the line keeps the small ones, 2087 / 2145.
+constexpr int kWgLargeMin = 320;
 
 struct WgArgs {
   const uint16_t* p; const uint16_t* q;
