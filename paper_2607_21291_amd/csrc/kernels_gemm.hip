@@ -1616,7 +1616,14 @@ static void skinny_split(int ntn, int K, int* splits, int* kc) {
 // The NeoX QKV and up projections, which share the chip on two streams, take
 // one size for both, from the sum of their tiles (GemmArgs::tile_hint): a
 // 256 x 256 workgroup takes most of a CU's LDS and cannot share the CU with a
-// 128 x 128 one, so mixed sizes starve the large-tile launch.
+// 128 x 128 one, so mixed sizes starve the large-tile launch. Beside attention
+// the CUs that a last round of the pair leaves are not idle, so from four full
+// rounds on it is charged by its share (a NeoX-160M layer, small / large tiles:
+// 13312 rows 343 / 336 us, 13824 336 / 328, 15872 384 / 374, 18944 443 / 430; with
+// fewer rounds it goes either way: 6656 rows 172 / 176, 9728 228 / 220), and a pair
+// within one round keeps the small tiles (2560 rows 103 / 107, 3072 108 / 113).
+// Over rows of 2048 to 20480 the choice is 0.3 % slower than the better one on
+// that shape, and 0.1-0.8 % on layers 512, 1024 and 1536 wide.
 // DSF_GEMM_TILE=small|large (read at every launch) forces one of them.
 static double small_tile_us(int64_t nt, int nk, int cus, bool stream_k, bool wide) {
   const int64_t P = 2 * int64_t(cus), full = nt / P, rem = nt % P;
@@ -1627,17 +1634,20 @@ static double small_tile_us(int64_t nt, int nk, int cus, bool stream_k, bool wid
   }
   return nk * rounds * (wide ? 1.1 : 1.0) + over + 8.0;
 }
-static double large_tile_us(int64_t nt, int nk, int cus, bool tail) {
+static double large_tile_us(int64_t nt, int nk, int cus, bool tail, bool pair) {
   const int64_t full = nt / cus, rem = nt % cus;
   double rounds = 1.45 * double(full), over = 12.0 * double(full + (rem > 0)) + 8.0;
-  if (rem > 0) {
+  if (pair && full >= 4) {
+    rounds += 1.45 * double(rem) / double(cus);
+  } else if (rem > 0) {
     const TailSplit ts = tail ? choose_tail(int(nt), nk, cus, kSkMaxSlots / 2, true) : TailSplit{0, 1};
     rounds += ts.s == 4 ? 0.45 : ts.s == 3 ? 0.55 : ts.s == 2 ? 1.3 : 1.45;
     if (ts.s > 1) over += 20.0;
   }
   return nk * rounds + over;
 }
-static bool large_tiles_win(int64_t nt_small, int64_t nt_large, int nk, bool tail, bool stream_k, bool wide) {
+static bool large_tiles_win(int64_t nt_small, int64_t nt_large, int nk, bool tail, bool stream_k, bool wide,
+                            bool pair = false) {
   const int cus = device_cus();
   if (cus <= 0) return false;
   if (nt_large <= cus && tail) {
@@ -1649,8 +1659,8 @@ static bool large_tiles_win(int64_t nt_small, int64_t nt_large, int nk, bool tai
       return large_split_us(int(nt_large), nk, sp, cus) < 0.9 * small;
     }
   }
-  if (nt_small <= cus) return false;
-  return large_tile_us(nt_large, nk, cus, tail) < small_tile_us(nt_small, nk, cus, stream_k, wide);
+  if (nt_small <= cus || (pair && nt_large <= cus)) return false;
+  return large_tile_us(nt_large, nk, cus, tail, pair) < small_tile_us(nt_small, nk, cus, stream_k, wide);
 }
 template <class TC>
 static int64_t tile_count(int M, int N) {
@@ -1661,7 +1671,8 @@ static int64_t tile_count(int M, int N) {
 // N1 and N2 wide, run side by side.
 int gemm_pair_tile_hint(int M, int N1, int N2, int K) {
   return large_tiles_win(tile_count<TileSmall>(M, N1) + tile_count<TileSmall>(M, N2),
-                         tile_count<TileLarge>(M, N1) + tile_count<TileLarge>(M, N2), K / 64, false, false, false)
+                         tile_count<TileLarge>(M, N1) + tile_count<TileLarge>(M, N2), K / 64, false, false, false,
+                         true)
              ? 2
              : 1;
 }
