@@ -272,12 +272,13 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  *
  * Second stream. For GPT-NeoX blocks the FFN up projection runs on a
  * library-owned stream beside QKV and attention on the caller's stream,
- * ordered by event waits (which a graph capture of the caller's stream
- * records too). There is one such stream per device and host thread,
- * created by the thread's first call and destroyed with its events when the
- * thread exits. DSF_SINGLE_STREAM=1, read at every call, keeps all work on
- * the caller's stream, with the grids of two streams (results are bitwise
- * the same); that projection is never cut along K.
+ * ordered by event waits. There is one such stream per device and host
+ * thread, created by the thread's first call and destroyed with its events
+ * when the thread exits. DSF_SINGLE_STREAM=1, read at every call, keeps all
+ * work on the caller's stream, with the grids of two streams (results are
+ * bitwise the same); that projection is never cut along K. Capturing such a
+ * call into a HIP graph is not tested (a decode step, which runs on the
+ * caller's stream alone, is).
  *
  * Projection schedule. Up to 24 rows (kept tokens of all sequences; 64 in
  * a decode step), a projection runs on the few-row kernel, which streams the
@@ -298,7 +299,8 @@ int dsf_attention_forward(const void* q, const void* k, const void* v, int dtype
  * into 2-4 pieces, and a grid that leaves CUs idle may cut every tile so. In
  * all of these the last piece adds the others' partial sums in a fixed order
  * (deterministic; rounds differently from the unsplit grid), and
- * DSF_GEMM_TAIL=0, read at every launch, turns the split off. With more 128 x 128 tiles than resident
+ * DSF_GEMM_TAIL=0, read at every launch, turns the split off. With more
+ * 128 x 128 tiles than resident
  * workgroups, one output tile per workgroup; or a persistent grid taking
  * whole tiles (same arithmetic); or, when that would end in a short last
  * round of tiles on a long reduction, a stream-K grid (workgroups split the
@@ -551,7 +553,10 @@ int dsf_align_stack_forward(const dsf_layer_desc* desc, const dsf_layer_weights*
  * classes whose bit (1 << DSF_KIND_*) is set in mask; n == 0 disarms and
  * frees the events. dsf_timing_read waits for the recorded events and
  * returns, for the kernel class `kind`, the number of launches and their
- * summed duration in milliseconds, then clears that class. */
+ * summed duration in milliseconds, then clears that class. The projections of
+ * a decode step and of the backward have no class; a bf16 decode step of up
+ * to 64 rows scores its tokens within them (no DSF_KIND_ROUTER record), and
+ * one of up to 16 rows normalises there too (no DSF_KIND_NORM record). */
 enum {
   DSF_KIND_SIM = 0, DSF_KIND_ROUTER = 1, DSF_KIND_TOPK = 2, DSF_KIND_NORM = 3,
   DSF_KIND_GEMM_QKV = 4, DSF_KIND_ATTN = 5, DSF_KIND_GEMM_O = 6, DSF_KIND_GEMM_UP = 7,

@@ -564,9 +564,8 @@ namespace {
 // and host thread, created on the thread's first such call, non-blocking,
 // default priority, and destroyed with its events when the thread exits (a
 // per-thread stream never joins another thread's graph capture). Fork and
-// join are event waits, which a caller capturing the stream into a graph
-// records as well. DSF_SINGLE_STREAM=1 (read at every call) keeps everything
-// on one stream.
+// join are event waits. DSF_SINGLE_STREAM=1 (read at every call) keeps
+// everything on one stream.
 // The fork and join events only order the two streams of one device: the
 // kernels' own end-of-kernel releases make their results visible device-wide,
 // so the events skip the system-scope fence (measured 1.2 % per stack step).
@@ -975,12 +974,12 @@ DecodePlan make_decode_plan(const dsf_layer_desc& D, int dtype, int B, int max_p
   if (row_split && dtype == DSF_BF16 && B > 16 && B <= kRowGemmMaxRows)
     p.part_bytes = std::max(p.part_bytes, rowgemm_split_bytes());
   p.part = take(p.part_bytes);
-  // few-row GEMMs (bf16, B <= 16): split-K partial tiles
+  // split-K QKV projection (bf16, B <= 16, rotary dims that are no multiple of 16): partial tiles
   const bool few = dtype == DSF_BF16 && B <= 16;
   p.spart = few ? take(gemm_skinny_partial_bytes()) : 0;
   // counters, zero at the start of a step: decode attention (B * Hq chunk
   // counters), the lengths the current layer starts from (B words, written by
-  // its router), then the few-row GEMMs' tile counters
+  // its router), then the split-K QKV projection's tile counters
   const int64_t na = int64_t(n) * D.n_heads + n, ns = few ? gemm_skinny_counters() : 0;
   p.ncounters = na + ns;
   p.counters = take(sizeof(uint32_t) * size_t(p.ncounters));

@@ -12,7 +12,7 @@
 // operands straight from global memory into the MFMA (16 bytes per lane; the
 // next group's loads are issued before the current group's MFMAs), and the
 // eight partial tiles meet in LDS, added in wave order (deterministic).
-// Nothing is handed over between workgroups.
+// Nothing is handed over between workgroups (but see SPLIT).
 //
 // Column groups. An epilogue item is one row of a 16-column group, held by
 // one thread as two chunks of 8 columns, chosen so that whatever the epilogue
